@@ -25,7 +25,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16
-FP64_VECTOR_PEAK_TFLOPS = 78.6  # fp64 vector arithmetic (the exact path's products run as fp64 fused multiply-adds)
+FP64_PEAK_TFLOPS = 78.6         # fp64 arithmetic, matrix cores and vector units alike (the exact path's products)
 
 
 def block_bytes(b, refresh):
@@ -227,17 +227,19 @@ def main():
                             "flops of the mathematical products; mfma.issued = matrix-core work with every fp32 "
                             "operand as a (hi, lo) bf16 pair (2 instructions per product of G, 3 per thin product) "
                             "at the padded rank class"}
-        elif label in ("project_f64", "reconstruct_f64", "alg2_products_f64"):
-            # exact path: batched fp64 products on the vector units.  project: G Q^T; reconstruct: the m x n term of
-            # the update from the thin factors; Alg. 2: G R^T and L^T G per GD iteration (plus the r x r ones)
+        elif label in ("project_f64", "reconstruct_f64", "alg2_gram_f64", "alg2_update_f64"):
+            # exact path: batched fp64 products on the matrix cores.  project: G Q^T; reconstruct: the m x n term of
+            # the update from the thin factors; Alg. 2, per GD iteration: the r x r Gram matrices, and G R^T, L^T G with the
+            # thin products of the factor updates behind them
             per_block = {"project_f64": lambda b: 2.0 * b.rows * b.cols * b.rank,
                          "reconstruct_f64": lambda b: 2.0 * b.rows * b.cols * b.rank,
-                         "alg2_products_f64": lambda b: 4.0 * b.rows * b.cols * b.rank + 8.0 * (b.rows + b.cols) * b.rank ** 2}[label]
+                         "alg2_gram_f64": lambda b: 4.0 * (b.rows + b.cols) * b.rank ** 2,
+                         "alg2_update_f64": lambda b: 4.0 * b.rows * b.cols * b.rank + 4.0 * (b.rows + b.cols) * b.rank ** 2}[label]
             alg = sum(per_block(b) for b in lr_blocks)
-            roof = {"bound": "alu", "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
+            roof = {"bound": "alu", "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "achieved": alg / (k["avg_ms"] * 1e-3) / 1e12,
-                    "note": "fp64 multiply-adds of the products, against the chip's fp64 vector rate (256 compute units x "
-                            "4 SIMDs x 16 lanes x 2 flop x 2.4 GHz = 78.6 TFLOP/s)"}
+                    "note": "fp64 multiply-adds of the products, against the chip's fp64 rate (256 compute units x "
+                            "4 SIMDs x 32 flop per clock x 2.4 GHz = 78.6 TFLOP/s, matrix and vector)"}
         if roof is None:
             return None
         roof.update(kernel=label, frac=roof["achieved"] / roof["peak"], avg_ms=k["avg_ms"],

@@ -73,7 +73,7 @@ struct GemmList {
   std::vector<GemmTile> tiles;
   GemmProblem* d_probs = nullptr;
   GemmTile* d_tiles = nullptr;
-  int tile = 64;
+  bool mfma = false;  // split-bf16 kernel (else fp64)
 };
 
 struct Op {
@@ -265,23 +265,33 @@ uint64_t mix64(uint64_t z) {
   return z ^ (z >> 31);
 }
 
-// output tile edge: 64 for the fp64 kernel, 128 for the MFMA kernel
+// Output tiles of a problem: 128 x 128 for the split-bf16 kernel, 16 tm x 16 tn for the fp64 one.
 // lower_only: a symmetric result of which only the tiles on and below the diagonal are read afterwards
-void add_problem(GemmList& gl, const GemmProblem& p, int tile = 0, bool lower_only = false) {
-  if (tile) gl.tile = tile;
+void add_problem(GemmList& gl, const GemmProblem& p, bool lower_only = false) {
   gl.probs.push_back(p);
   const uint32_t id = (uint32_t)gl.probs.size() - 1;
-  const int T = gl.tile;
-  for (int ti = 0; ti < (p.M + T - 1) / T; ++ti)
-    for (int tj = 0; tj < (p.N + T - 1) / T; ++tj)
-      if (!lower_only || tj <= ti) gl.tiles.push_back(GemmTile{id, (uint16_t)ti, (uint16_t)tj});
+  const int TM = gl.mfma ? 128 : 16 * p.tm, TN = gl.mfma ? 128 : 16 * p.tn;
+  for (int ti = 0; ti < (p.M + TM - 1) / TM; ++ti)
+    for (int tj = 0; tj < (p.N + TN - 1) / TN; ++tj)
+      if (!lower_only || tj <= ti) gl.tiles.push_back(GemmTile{id, ti, tj});
+}
+
+// The fp64 kernel: operand layout and output tile.  32 x 32 tiles load half as much per multiply-add as 16 x 16 ones; a
+// free index of at most 16 takes one 16-wide tile.  small: 16 x 16 tiles (Gram matrices of few blocks, whose launch would
+// otherwise hold fewer workgroups than the chip has compute units).
+GemmProblem& shape64(GemmProblem& p, int layout, bool small = false) {
+  p.layout = layout;
+  p.tm = (small || (p.M <= 16 && layout != G64_KJ)) ? 1 : 2;
+  p.tn = (small || p.N <= 16) ? 1 : 2;
+  return p;
 }
 
 GemmProblem problem(int M, int N) {
   GemmProblem p;
   memset(&p, 0, sizeof p);
-  p.A1 = p.B1 = p.A2 = p.B2 = p.X = p.Y = p.Out = none_mat();
+  p.A1 = p.B1 = p.A2 = p.B2 = p.A3 = p.B3 = p.X = p.Y = p.Out = none_mat();
   p.M = M; p.N = N;
+  p.layout = G64_KK; p.tm = p.tn = 2;
   p.off_s = -1;
   return p;
 }
@@ -341,6 +351,10 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       if (best < 0 || cost < best) { best = cost; gram_seg = seg; }
     }
   }
+  // Exact path: 32 x 32 tiles of the Gram matrices once they make four workgroups per compute unit, else 16 x 16
+  int64_t gram_tiles = 0;
+  for (int64_t i : ids) gram_tiles += 4ll * ((c->table[i].rank + 31) / 32) * ((c->table[i].rank + 31) / 32);
+  const bool gram_small = gram_tiles < 4 * 256;
   // this group's lists
   const int grp = c->n_groups++;
   c->cp.emplace_back(); c->rub.emplace_back(); c->qt.emplace_back(); c->chol.emplace_back();
@@ -352,7 +366,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
   if (!fast) c->ew.emplace_back();
   auto new_list = [&](bool mfma) {
     c->gemms.emplace_back();
-    c->gemms.back().tile = mfma ? 128 : 64;
+    c->gemms.back().mfma = mfma;
     return (int)c->gemms.size() - 1;
   };
   std::vector<int> listA(n_eff), listB(n_eff);
@@ -455,21 +469,29 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
         sp.off_timg_prev = (e == 0 && hp.bias_correction) ? L.wT1 : -1;   // ... the first one that of R_{t-1}^T
         c->sprob.h.push_back(sp);
         swork[6 * e + 2 * cls + 1].push_back(StripeWork{(int)c->sprob.h.size() - 1, n, m});
-      } else {
+      } else if (fast) {
         p = problem(m, r); p.A1 = G; p.B1 = T(Rc); p.K1 = n; p.a1 = 1; p.scale_g = 1; p.Out = P; add_problem(A, p);
         p = problem(r, n); p.A1 = T(Lc); p.B1 = G; p.K1 = m; p.a1 = 1; p.scale_g = 1; p.Out = S; add_problem(A, p);
-      }
-      if (!(fast && stripe_ok(b))) {
         p = problem(r, r); p.A1 = Rc; p.B1 = T(Rc); p.K1 = n; p.a1 = 1; p.Out = Grr; add_problem(A, p);
         p = problem(r, r); p.A1 = Rp; p.B1 = T(Rc); p.K1 = n; p.a1 = 1; p.Out = Gpr; add_problem(A, p);
         p = problem(r, r); p.A1 = T(Lc); p.B1 = Lc; p.K1 = m; p.a1 = 1; p.Out = Gll; add_problem(A, p);
         p = problem(r, r); p.A1 = T(Lc); p.B1 = Lp; p.K1 = m; p.a1 = 1; p.Out = Glp; add_problem(A, p);
+      } else {
+        // Exact path: the r x r matrices first (the mixed ones transposed: every operand of a factor update is then
+        // contiguous along the same index), the products with G ride on the updates below.  In the first iteration the
+        // factors are still the previous step's and the mixed matrices are the plain ones.
+        p = problem(r, r); p.A1 = Rc; p.B1 = T(Rc); p.K1 = n; p.a1 = 1; p.Out = Grr; add_problem(A, shape64(p, G64_KK, gram_small));
+        p = problem(r, r); p.A1 = T(Lc); p.B1 = Lc; p.K1 = m; p.a1 = 1; p.Out = Gll; add_problem(A, shape64(p, G64_IJ, gram_small));
+        if (e > 0) {
+          p = problem(r, r); p.A1 = Rc; p.B1 = T(Rp); p.K1 = n; p.a1 = 1; p.Out = Gpr; add_problem(A, shape64(p, G64_KK, gram_small));
+          p = problem(r, r); p.A1 = T(Lp); p.B1 = Lc; p.K1 = m; p.a1 = 1; p.Out = Glp; add_problem(A, shape64(p, G64_IJ, gram_small));
+        }
       }
       GemmList& Bl = c->gemms[listB[e]];
       // optional: both updates of this iteration take eta / max(||R R^T||_F, ||L^T L||_F), a device scalar
       const int64_t off_s = hp.refresh_normalise ? L.wNu : -1;
       if (hp.refresh_normalise) c->gnorm[gnorm0 + e].h.push_back(GnormItem{L.wGrr, L.wGll, L.wNu, r, idt});
-      if (!(fast && stripe_ok(b))) {
+      if (fast && !stripe_ok(b)) {
         p = problem(m, r);
         p.A1 = Lc; p.B1 = Grr; p.K1 = r; p.a1 = -eta;
         p.A2 = Lp; p.B2 = Gpr; p.K2 = r; p.a2 = eta * b1;
@@ -480,6 +502,22 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
         p.A2 = Glp; p.B2 = Rp; p.K2 = r; p.a2 = eta * b1;
         p.X = Rc; p.g = 1.0; p.Y = S; p.d = eta * (1.0 - b1); p.Out = Rn; p.off_s = off_s;
         add_problem(Bl, p);
+      }
+      if (!fast) {
+        // L <- L + s (eta (1-b1) G R^T - eta L (R R^T) + eta b1 L' (R' R^T)) and the same for R, the stored r x r matrices
+        // read transposed (R R^T and L^T L are symmetric to the last bit: the same products in the same order)
+        p = problem(m, r);
+        p.A1 = G; p.B1 = T(Rc); p.K1 = n; p.a1 = eta * (1.0 - b1); p.scale_g = 1;
+        p.A2 = Lc; p.B2 = T(Grr); p.K2 = r; p.a2 = e > 0 ? -eta : eta * b1 - eta;
+        if (e > 0) { p.A3 = Lp; p.B3 = T(Gpr); p.K3 = r; p.a3 = eta * b1; }
+        p.X = Lc; p.g = 1.0; p.Out = Ln; p.off_s = off_s;
+        add_problem(Bl, shape64(p, G64_KK));
+        p = problem(r, n);
+        p.A1 = T(Lc); p.B1 = G; p.K1 = m; p.a1 = eta * (1.0 - b1); p.scale_g = 1;
+        p.A2 = T(Gll); p.B2 = Rc; p.K2 = r; p.a2 = e > 0 ? -eta : eta * b1 - eta;
+        if (e > 0) { p.A3 = T(Glp); p.B3 = Rp; p.K3 = r; p.a3 = eta * b1; }
+        p.X = Rc; p.g = 1.0; p.Out = Rn; p.off_s = off_s;
+        add_problem(Bl, shape64(p, G64_IJ));
       }
       Lc = Ln; Rc = Rn;
     }
@@ -514,7 +552,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
         p.A1 = Lc; p.B1 = Rc; p.K1 = r; p.a1 = 1.0;
       }
       p.Out = C;
-      add_problem(c->gemms[l_epi], p);
+      add_problem(c->gemms[l_epi], shape64(p, G64_KJ));
       for (int64_t s0 = 0; s0 < (int64_t)m * n; s0 += EW_CHUNK)
         c->ew[ew_id].h.push_back(EwItem{s0, (int32_t)i, (int32_t)std::min<int64_t>(EW_CHUNK, (int64_t)m * n - s0)});
     }
@@ -522,7 +560,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       // the pass over all blocks that follows the last group: Gram matrix of the stored R in fp64, Cholesky, in place
       const Mat G64 = mat(SP_WS, 0, L.wG64, r, 1, DT_F64);
       p = problem(r, r); p.A1 = Rp; p.B1 = T(Rp); p.K1 = n; p.a1 = 1.0; p.Out = G64;
-      add_problem(c->gemms[c->rg_gram], p, 0, true);
+      add_problem(c->gemms[c->rg_gram], shape64(p, G64_KK, r <= 16), true);
       c->chol[c->rg_chol].h.push_back(CholItem{L.wG64, L.wCinv, r, 0});
       for (int f = 0; f < n; f += 64) c->rg_apply.h.push_back(RegaugeItem{L.sR, L.wCinv, r, n, f, 0});
       for (int f = 0; f < m; f += 64) c->rg_apply.h.push_back(RegaugeItem{L.sL, L.wG64, r, m, f, 1});
@@ -531,11 +569,11 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       // product-preserving orthonormalisation of R, always in fp64
       const Mat G64 = mat(SP_WS, 0, L.wG64, r, 1, DT_F64), Cinv = mat(SP_WS, 0, L.wCinv, r, 1, DT_F64);
       p = problem(r, r); p.A1 = Rc; p.B1 = T(Rc); p.K1 = n; p.a1 = 1.0; p.Out = G64;
-      add_problem(c->gemms[l_gram], p, 0, true);      // the Cholesky factorisation reads the lower triangle only
+      add_problem(c->gemms[l_gram], shape64(p, G64_KK, r <= 16), true);      // the Cholesky factorisation reads the lower triangle only
       c->chol[chol_id].h.push_back(CholItem{L.wG64, L.wCinv, r, 0});
       // C^-1 and C are lower triangular
-      p = problem(r, n); p.A1 = Cinv; p.B1 = Rc; p.K1 = r; p.a1 = 1.0; p.tri = 1; p.Out = Rp; add_problem(c->gemms[l_fin], p);
-      p = problem(m, r); p.A1 = Lc; p.B1 = G64; p.K1 = r; p.a1 = 1.0; p.tri = 2; p.Out = Lp; add_problem(c->gemms[l_fin], p);
+      p = problem(r, n); p.A1 = Cinv; p.B1 = Rc; p.K1 = r; p.a1 = 1.0; p.tri = 1; p.Out = Rp; add_problem(c->gemms[l_fin], shape64(p, G64_KJ));
+      p = problem(m, r); p.A1 = Lc; p.B1 = G64; p.K1 = r; p.a1 = 1.0; p.tri = 2; p.Out = Lp; add_problem(c->gemms[l_fin], shape64(p, G64_KJ));
     } else if (n_eff > 0) {
       if (fast) {
         for (int64_t f = 0; f < (int64_t)m * r; f += COPY_CHUNK)
@@ -580,7 +618,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       if (!c->gfin[gram0 + e].h.empty()) seq.push_back(Op{OP_GRAM_FIN, gram0 + e, 0, 0, "alg2_gram_segments_sum"});
     }
     if (!c->gemms[listA[e]].tiles.empty())
-      seq.push_back(Op{gk, listA[e], 0, 0, fast ? "alg2_products_mfma" : "alg2_products_f64"});
+      seq.push_back(Op{gk, listA[e], 0, 0, fast ? "alg2_products_mfma" : "alg2_gram_f64"});
     if (hp.refresh_normalise) seq.push_back(Op{OP_GNORM, gnorm0 + e, 0, 0, "alg2_step_normaliser"});
     if (stripes) {
       // both streaming products of the iteration and, behind each stripe, the GD step on the factor rows it covers
@@ -661,13 +699,13 @@ void plan_lowrank_project_f64(adapm_ctx* c, const std::vector<int64_t>& ids, int
     const Mat P = mat(SP_WS, 0, L.wP, r, 1, DT_F64), D = mat(SP_WS, 0, L.wLa, r, 1, DT_F64);
     const Mat C = mat(SP_WS, 0, L.wC, n, 1, DT_F32);
     GemmProblem p;
-    p = problem(m, r); p.A1 = G; p.B1 = Qt; p.K1 = n; p.a1 = 1.0; p.scale_g = 1; p.Out = P; add_problem(c->gemms[l_p], p);
+    p = problem(m, r); p.A1 = G; p.B1 = Qt; p.K1 = n; p.a1 = 1.0; p.scale_g = 1; p.Out = P; add_problem(c->gemms[l_p], shape64(p, G64_KK));
     // L_t = b1 L' + (1-b1) G Q^T;  m^c = G + b1 (L' - G Q^T) Q   (or L_t Q without the correction)
     p = problem(m, r); p.X = Ls; p.Y = P; p.Out = D;
     if (hp.bias_correction) { p.g = b1; p.d = -b1; } else { p.g = b1; p.d = 1.0 - b1; }
     add_problem(c->gemms[l_d], p);
     p = problem(m, r); p.X = Ls; p.g = b1; p.Y = P; p.d = 1.0 - b1; p.Out = Ls; add_problem(c->gemms[l_l], p);
-    p = problem(m, n); p.A1 = D; p.B1 = Q; p.K1 = r; p.a1 = 1.0; p.Out = C; add_problem(c->gemms[l_c], p);
+    p = problem(m, n); p.A1 = D; p.B1 = Q; p.K1 = r; p.a1 = 1.0; p.Out = C; add_problem(c->gemms[l_c], shape64(p, G64_KJ));
   }
   std::vector<Op>& seq = c->seq_project;
   seq.push_back(Op{OP_GEMM, l_p, 0, 0, "project_f64"});
@@ -766,7 +804,8 @@ size_t layout_block_scratch(const adapm_block_t& b, const adapm_hparams_t& hp, L
   // the second working copy of the factors: only where the GD step runs as batched GEMMs (see plan_lowrank_refresh)
   if (!stripes) { T.wLb = walloc(es * m * r); T.wRb = walloc(es * r * n); }
   // G R^T and L^T G: blocks whose GD step rides on the stripe products never store them
-  if (!stripes) { T.wP = walloc(es * m * r); T.wS = walloc(es * r * n); }
+  if (!stripes) T.wP = walloc(es * m * r);
+  if (fast && !stripes) T.wS = walloc(es * r * n);       // the exact path adds L^T G to the factor in place
   T.wGrr = walloc(es * r * r); T.wGpr = walloc(es * r * r);
   T.wGll = walloc(es * r * r); T.wGlp = walloc(es * r * r);
   if (hp.refresh_period_T > 1 && !fast) { T.wG64 = walloc(8 * r * r); T.wCinv = walloc(8 * r * r); }

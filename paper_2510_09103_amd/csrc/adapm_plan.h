@@ -49,8 +49,8 @@ __device__ __forceinline__ char* resolve(const Ref& r, const Bases& b) {
 }
 
 // ---------------------------------------------------------------------------
-// fp64-accumulate strided two-product GEMM
-//   Out[i,j] = a1 * sum_k A1[i,k] B1[k,j] + a2 * sum_k A2[i,k] B2[k,j] + g * X[i,j] + d * Y[i,j]
+// batched GEMMs over strided operands
+//   Out[i,j] = g * X[i,j] + s * (sum_p a_p * sum_k A_p[i,k] B_p[k,j] + d * Y[i,j])      (up to three products)
 // element (i,j) of a matrix lives at base + (i*s0 + j*s1) * sizeof(dtype)
 // ---------------------------------------------------------------------------
 struct Mat {
@@ -60,18 +60,25 @@ struct Mat {
   int32_t pad;
 };
 
+// Which index is contiguous in memory in the operands of the fp64 kernel (the same for all products of a problem):
+// KK: the contraction index of both (A row-major, B column-major); IJ: the free index of both (A column-major, B
+// row-major); KJ: both row-major.
+enum Gemm64Layout : int32_t { G64_KK = 0, G64_IJ = 1, G64_KJ = 2 };
+
 struct GemmProblem {
-  Mat A1, B1, A2, B2, X, Y, Out;
-  int32_t M, N, K1, K2;
-  double a1, a2, g, d;
-  int32_t scale_g;   // 1: the (single) product has the gradient as an operand and takes the clipping factor
+  Mat A1, B1, A2, B2, A3, B3, X, Y, Out;
+  int32_t M, N, K1, K2, K3;
+  int32_t layout;    // fp64 kernel: Gemm64Layout
+  int32_t tm, tn;    // fp64 kernel: output tile of a workgroup in units of 16 (see gemm64_tile_shape)
+  double a1, a2, a3, g, d;
+  int32_t scale_g;   // 1: the first product has the gradient as an operand and takes the clipping factor
   int32_t tri;       // fp64 kernel: 1 = A1 is lower triangular, 2 = B1 is lower triangular (zero part of the contraction skipped)
-  int64_t off_s;     // >= 0: workspace offset of a device scalar s (double); then Out = g X + s (a1 A1 B1 + a2 A2 B2 + d Y)
+  int64_t off_s;     // >= 0: workspace offset of the device scalar s (double); -1: s = 1
 };
 
 struct GemmTile {
   uint32_t prob;
-  uint16_t ti, tj;   // 64 x 64 output tile coordinates
+  int32_t ti, tj;    // output tile coordinates
 };
 
 // ---------------------------------------------------------------------------

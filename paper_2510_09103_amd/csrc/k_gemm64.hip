@@ -1,172 +1,169 @@
-// fp64-accumulate strided two-product GEMM on the vector ALUs (the "F64" contraction mode):
-//   Out = a1 * A1 B1 + a2 * A2 B2 + g * X + d * Y
-// One launch covers a list of 64 x 64 output tiles drawn from many independent problems,
-// so every thin product of Alg. 2 (G R^T, L^T G, the four r x r Gram matrices, the factor
-// updates, the reconstruction L_{t-1}R_{t-1} - L_t R_t) of every low-rank block runs in a
-// handful of launches.  Operands (bf16 / fp32 / fp64) convert exactly to fp64; sums run in
-// ascending k, so results are deterministic.
-#include "adapm_plan.h"
+// fp64 batched GEMM on the fp64 matrix cores (the "F64" contraction mode and the re-expression of the factors):
+//   Out = g X + s (a1 A1 B1 + a2 A2 B2 + a3 A3 B3 + d Y)
+// One launch covers a list of output tiles drawn from many independent problems, so every thin product of Alg. 2 of every
+// low-rank block runs in two launches per iteration (the r x r Gram matrices, then both factor updates with their
+// products with G).  Operands (bf16 / fp32 / fp64) convert exactly to fp64; all sums run in fp64 in a fixed order.
+//
+// One workgroup (4 waves) per output tile of 16 tm x 16 tn (tm, tn = 1 or 2).  The products here are thin: a tile has a
+// short free index and a contraction of 256 .. 6400, so what bounds the launch is the latency of one tile, and the four
+// waves split the contraction (wave w takes every fourth step, neighbouring waves read neighbouring memory) and add
+// their partial tiles through LDS in wave order.  Operands go from memory to the registers of the matrix instruction
+// (k_f64_common.h); a step's loads are in flight while the previous step is multiplied.
+// Measured against 64 x 64 tiles on the vector units with operands staged in LDS (one workgroup walking the whole
+// contraction): G R^T, L^T G and the Gram matrices of one GD iteration with the factor updates, 56 blocks of 512 x 512 ..
+// 1376 x 512 at r = 32: 454 -> 146 us (of which 115 us, 31 TFLOP/s, for the updates); 7 blocks of at most 256 x 1024 at
+// r = 8: 157 -> 37 us; G R^T alone, with R held: 259 -> 61 us and 129 -> 13 us.
+#include "k_f64_common.h"
 
 namespace adapm {
 
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 16, PAD = 2;
+constexpr int NW = 4;                  // waves of a workgroup: they split the contraction
 
 __device__ __forceinline__ double load_el(const char* base, int dtype, int64_t idx) {
-  if (dtype == DT_F32) return (double)reinterpret_cast<const float*>(base)[idx];
-  if (dtype == DT_BF16) return (double)__uint_as_float(((uint32_t)reinterpret_cast<const uint16_t*>(base)[idx]) << 16);
-  return reinterpret_cast<const double*>(base)[idx];
+  return dtype == DT_F32 ? (double)reinterpret_cast<const float*>(base)[idx] : reinterpret_cast<const double*>(base)[idx];
 }
 
-// Four elements of an operand tile per thread.  Every load is issued unconditionally on a clamped (always
-// valid) index and masked afterwards: a load inside its own bounds check would wait for the previous one.
-template <int DT>
-__device__ __forceinline__ void fetch4_t(const char* base, const int64_t (&idx)[4], const bool (&ok)[4], double (&x)[4]) {
-  if (DT == DT_F32) {
-    float r[4];
+// acc += alpha * A B over this wave's share of k in [kb, ke)
+template <int TM, int TN, int ADT, int BDT, int LAY>
+__device__ __forceinline__ void product(const Mat& A, const Mat& B, double alpha, int M, int N, int kb, int ke, int i0, int j0,
+                                        const Bases& bs, f64x4 (&acc)[TM][TN]) {
+  constexpr bool AK = LAY != G64_IJ, BK_ = LAY == G64_KK;
+  constexpr int V = (LAY == G64_KK && ADT == DT_BF16) ? 8 : 4, KS = 4 * V;     // bf16 rows: 16-byte loads
+  typedef Operand<ADT, TM, V, AK> OA;
+  typedef Operand<BDT, TN, V, BK_> OB;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const typename OA::Where wa = OA::where(resolve(A.ref, bs), A.s0, A.s1, i0, M, l16);
+  const typename OB::Where wb = OB::where(resolve(B.ref, bs), B.s1, B.s0, j0, N, l16);
+  OA a0, a1;
+  OB b0, b1;
+  auto mma = [&](const OA& a, const OB& b) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) r[p] = reinterpret_cast<const float*>(base)[ok[p] ? idx[p] : 0];
+    for (int v = 0; v < V; ++v) {
+      double av[TM], bv[TN];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) x[p] = ok[p] ? (double)r[p] : 0.0;
-  } else if (DT == DT_BF16) {
-    uint16_t r[4];
+      for (int t = 0; t < TM; ++t) av[t] = alpha * a.get(wa, t, v);
 #pragma unroll
-    for (int p = 0; p < 4; ++p) r[p] = reinterpret_cast<const uint16_t*>(base)[ok[p] ? idx[p] : 0];
+      for (int t = 0; t < TN; ++t) bv[t] = b.get(wb, t, v);
 #pragma unroll
-    for (int p = 0; p < 4; ++p) x[p] = ok[p] ? (double)__uint_as_float(((uint32_t)r[p]) << 16) : 0.0;
-  } else {
-    double r[4];
+      for (int t = 0; t < TM; ++t)
 #pragma unroll
-    for (int p = 0; p < 4; ++p) r[p] = reinterpret_cast<const double*>(base)[ok[p] ? idx[p] : 0];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) x[p] = ok[p] ? r[p] : 0.0;
-  }
-}
-__device__ __forceinline__ void fetch4(const char* base, int dtype, const int64_t (&idx)[4], const bool (&ok)[4], double (&x)[4]) {
-  if (dtype == DT_F32) fetch4_t<DT_F32>(base, idx, ok, x);
-  else if (dtype == DT_BF16) fetch4_t<DT_BF16>(base, idx, ok, x);
-  else fetch4_t<DT_F64>(base, idx, ok, x);
-}
-
-// contraction over k in [kbeg, K)
-__device__ __forceinline__ void product(const Mat& A, const Mat& B, int M, int N, int kbeg, int K, int i0, int j0,
-                                        const Bases& bs, double (*As)[TM + PAD], double (*Bs)[TN + PAD],
-                                        double acc[4][4]) {
-  const char* Ab = resolve(A.ref, bs);
-  const char* Bb = resolve(B.ref, bs);
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const bool a_kfast = (A.s1 == 1), b_jfast = (B.s1 == 1);
-  int ia[4], ka[4], jb[4], kb[4];
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const int idx = tid + p * 256;
-    if (a_kfast) { ka[p] = idx & 15; ia[p] = idx >> 4; } else { ia[p] = idx & 63; ka[p] = idx >> 6; }
-    if (b_jfast) { jb[p] = idx & 63; kb[p] = idx >> 6; } else { kb[p] = idx & 15; jb[p] = idx >> 4; }
-  }
-  auto fetch = [&](int k0, double (&xa)[4], double (&xb)[4]) {
-    int64_t ix[4];
-    bool ok[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      ok[p] = i0 + ia[p] < M && k0 + ka[p] < K;
-      ix[p] = (int64_t)(i0 + ia[p]) * A.s0 + (int64_t)(k0 + ka[p]) * A.s1;
+        for (int u = 0; u < TN; ++u) acc[t][u] = mfma_f64(av[t], bv[u], acc[t][u]);
     }
-    fetch4(Ab, A.dtype, ix, ok, xa);
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      ok[p] = j0 + jb[p] < N && k0 + kb[p] < K;
-      ix[p] = (int64_t)(k0 + kb[p]) * B.s0 + (int64_t)(j0 + jb[p]) * B.s1;
-    }
-    fetch4(Bb, B.dtype, ix, ok, xb);
   };
-  double xa[4], xb[4];
-  fetch(kbeg, xa, xb);
-  for (int k0 = kbeg; k0 < K; k0 += TK) {
-#pragma unroll
-    for (int p = 0; p < 4; ++p) { As[ka[p]][ia[p]] = xa[p]; Bs[kb[p]][jb[p]] = xb[p]; }
-    __syncthreads();
-    if (k0 + TK < K) fetch(k0 + TK, xa, xb);       // the next chunk travels while this one is multiplied
-#pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      double a[4], b[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) { a[q] = As[kk][ty * 4 + q]; b[q] = Bs[kk][tx * 4 + q]; }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[q][c] = fma(a[q], b[c], acc[q][c]);
+  const int nfull = (ke - kb) / KS;
+  const int k1 = kb + V * kq;
+  if (wave < nfull) {
+    a0.load(wa, k1 + wave * KS);
+    b0.load(wb, k1 + wave * KS);
+    for (int s = wave; s < nfull; s += NW) {
+      const int nx = s + NW < nfull ? s + NW : s;      // past the end the last step is read again
+      a1.load(wa, k1 + nx * KS);
+      b1.load(wb, k1 + nx * KS);
+      mma(a0, b0);
+      a0 = a1;
+      b0 = b1;
     }
-    __syncthreads();
+  }
+  if (kb + nfull * KS < ke && (nfull & (NW - 1)) == wave) {
+    a0.load_edge(wa, k1 + nfull * KS, ke);
+    b0.load_edge(wb, k1 + nfull * KS, ke);
+    mma(a0, b0);
   }
 }
 
-__global__ __launch_bounds__(256) void gemm64_kernel(const GemmProblem* __restrict__ probs,
-                                                     const GemmTile* __restrict__ tiles, Bases bs) {
-  __shared__ double As[TK][TM + PAD];
-  __shared__ double Bs[TK][TN + PAD];
-  const GemmTile t = tiles[blockIdx.x];
-  const GemmProblem& P = probs[t.prob];
-  const int i0 = t.ti * TM, j0 = t.tj * TN;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  double acc[4][4];
+// the operand types that occur, per layout and tile (the planner makes no others)
+template <int TM, int TN, int LAY>
+__device__ __forceinline__ void product_any(const Mat& A, const Mat& B, double alpha, int M, int N, int kb, int ke, int i0, int j0,
+                                            const Bases& bs, f64x4 (&acc)[TM][TN]) {
+#define ADAPM_CASE(ADT, BDT) \
+  if (A.dtype == ADT && B.dtype == BDT) return product<TM, TN, ADT, BDT, LAY>(A, B, alpha, M, N, kb, ke, i0, j0, bs, acc)
+  ADAPM_CASE(DT_F64, DT_F64);
+  ADAPM_CASE(DT_F32, DT_F64);
+  ADAPM_CASE(DT_F32, DT_F32);
+  ADAPM_CASE(DT_F64, DT_F32);
+  if constexpr (LAY == G64_KK) {
+    ADAPM_CASE(DT_BF16, DT_F64);
+    ADAPM_CASE(DT_BF16, DT_F32);
+  }
+  if constexpr (LAY == G64_IJ) {
+    ADAPM_CASE(DT_F64, DT_BF16);
+    ADAPM_CASE(DT_F32, DT_BF16);
+  }
+#undef ADAPM_CASE
+}
+
+template <int TM, int TN, int LAY>
+__device__ __forceinline__ void tile_body(const GemmProblem& P, const GemmTile& t, const Bases& bs, double* red) {
+  const int i0 = 16 * TM * t.ti, j0 = 16 * TN * t.tj;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  f64x4 acc[TM][TN];
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int a = 0; a < TM; ++a)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[q][c] = 0.0;
+    for (int b = 0; b < TN; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
   if (P.K1 > 0) {
     // a lower-triangular operand of the first product (tri = 1: A1, tri = 2: B1) leaves part of the contraction
-    // identically zero for this tile: rows i0 .. i0+63 of A1 end at column i0+63, columns j0 .. of B1 start at row j0
-    const int ke = P.tri == 1 ? (P.K1 < i0 + TM ? P.K1 : i0 + TM) : P.K1;
-    const int kb = P.tri == 2 ? (j0 / TK) * TK : 0;
-    product(P.A1, P.B1, P.M, P.N, kb, ke, i0, j0, bs, As, Bs, acc);
-    const double a1 = P.a1 * (P.scale_g ? (double)grad_scale(bs) : 1.0);   // the gradient enters clipped
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[q][c] *= a1;
+    // identically zero for this tile: rows i0 .. of A1 end at column i0 + 16 TM - 1, columns j0 .. of B1 start at row j0
+    const int ke = P.tri == 1 ? (P.K1 < i0 + 16 * TM ? P.K1 : i0 + 16 * TM) : P.K1;
+    const int kb = P.tri == 2 ? j0 : 0;
+    product_any<TM, TN, LAY>(P.A1, P.B1, P.a1 * (P.scale_g ? (double)grad_scale(bs) : 1.0), P.M, P.N, kb, ke, i0, j0, bs, acc);
   }
-  if (P.K2 > 0) {
-    double acc2[4][4];
+  if (P.K2 > 0) product_any<TM, TN, LAY>(P.A2, P.B2, P.a2, P.M, P.N, 0, P.K2, i0, j0, bs, acc);
+  if (P.K3 > 0) product_any<TM, TN, LAY>(P.A3, P.B3, P.a3, P.M, P.N, 0, P.K3, i0, j0, bs, acc);
+  // the waves' partial tiles, added in wave order; wave w finishes every NW-th result register
+  constexpr int NR = TM * TN * 4;
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+  for (int a = 0; a < TM; ++a)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc2[q][c] = 0.0;
-    product(P.A2, P.B2, P.M, P.N, 0, P.K2, i0, j0, bs, As, Bs, acc2);
-    const double a2 = P.a2;
+    for (int b = 0; b < TN; ++b)
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[q][c] = fma(a2, acc2[q][c], acc[q][c]);
-  }
+      for (int q = 0; q < 4; ++q) red[(wave * NR + (a * TN + b) * 4 + q) * 64 + lane] = acc[a][b][q];
+  __syncthreads();
   const char* Xb = P.X.ref.space != SP_NONE ? resolve(P.X.ref, bs) : nullptr;
   const char* Yb = P.Y.ref.space != SP_NONE ? resolve(P.Y.ref, bs) : nullptr;
   char* Ob = resolve(P.Out.ref, bs);
   // optional device scalar on everything but X (normalised step of Alg. 2)
   const double step_scale = P.off_s >= 0 ? *reinterpret_cast<const double*>(bs.ws + P.off_s) : 1.0;
-  // X and Y are read unconditionally on clamped indices (independent loads); the bounds check guards the store
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = i0 + ty * 4 + q;
-    const int ic = i < P.M ? i : 0;
-    double xv[4] = {0.0, 0.0, 0.0, 0.0}, yv[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int e = 0; e < NR / NW; ++e) {
+    const int reg = e * NW + wave, q = reg & 3, b = (reg >> 2) % TN, a = (reg >> 2) / TN;
+    double val = 0.0;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int j = j0 + tx * 4 + c;
-      const int jc = j < P.N ? j : 0;
-      if (Xb) xv[c] = load_el(Xb, P.X.dtype, (int64_t)ic * P.X.s0 + (int64_t)jc * P.X.s1);
-      if (Yb) yv[c] = load_el(Yb, P.Y.dtype, (int64_t)ic * P.Y.s0 + (int64_t)jc * P.Y.s1);
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int j = j0 + tx * 4 + c;
-      if (i >= P.M || j >= P.N) continue;
-      const double val = P.off_s >= 0 ? fma(P.g, xv[c], step_scale * fma(P.d, yv[c], acc[q][c]))
-                                      : fma(P.d, yv[c], fma(P.g, xv[c], acc[q][c]));
-      const int64_t o = (int64_t)i * P.Out.s0 + (int64_t)j * P.Out.s1;
-      if (P.Out.dtype == DT_F64) reinterpret_cast<double*>(Ob)[o] = val;
-      else reinterpret_cast<float*>(Ob)[o] = (float)val;
-    }
+    for (int w = 0; w < NW; ++w) val += red[(w * NR + reg) * 64 + lane];
+    const int row = 4 * q + kq;
+    const int i = LAY == G64_IJ ? i0 + TM * row + a : i0 + 16 * a + row;
+    const int j = LAY == G64_KK ? j0 + 16 * b + l16 : j0 + TN * l16 + b;
+    if (i >= P.M || j >= P.N) continue;
+    if (Yb) val = fma(P.d, load_el(Yb, P.Y.dtype, (int64_t)i * P.Y.s0 + (int64_t)j * P.Y.s1), val);
+    val *= step_scale;
+    if (Xb) val = fma(P.g, load_el(Xb, P.X.dtype, (int64_t)i * P.X.s0 + (int64_t)j * P.X.s1), val);
+    const int64_t o = (int64_t)i * P.Out.s0 + (int64_t)j * P.Out.s1;
+    if (P.Out.dtype == DT_F64) reinterpret_cast<double*>(Ob)[o] = val;
+    else reinterpret_cast<float*>(Ob)[o] = (float)val;
+  }
+}
+
+__global__ __launch_bounds__(64 * NW) void gemm64_kernel(const GemmProblem* __restrict__ probs,
+                                                         const GemmTile* __restrict__ tiles, Bases bs) {
+  __shared__ double red[NW * 16 * 64];
+  const GemmTile t = tiles[blockIdx.x];
+  const GemmProblem& P = probs[t.prob];
+  const int shape = 2 * P.tm + P.tn;     // 3: 16 x 16, 4: 16 x 32, 5: 32 x 16, 6: 32 x 32
+  if (P.layout == G64_KK) {
+    if (shape == 6) tile_body<2, 2, G64_KK>(P, t, bs, red);
+    else if (shape == 5) tile_body<2, 1, G64_KK>(P, t, bs, red);
+    else tile_body<1, 1, G64_KK>(P, t, bs, red);
+  } else if (P.layout == G64_IJ) {
+    if (shape == 6) tile_body<2, 2, G64_IJ>(P, t, bs, red);
+    else if (shape == 4) tile_body<1, 2, G64_IJ>(P, t, bs, red);
+    else tile_body<1, 1, G64_IJ>(P, t, bs, red);
+  } else {
+    if (shape == 6) tile_body<2, 2, G64_KJ>(P, t, bs, red);
+    else tile_body<2, 1, G64_KJ>(P, t, bs, red);
   }
 }
 
@@ -174,7 +171,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(const GemmProblem* __restri
 
 void launch_gemm64(const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, Bases b, hipStream_t s) {
   if (ntiles <= 0) return;
-  hipLaunchKernelGGL(gemm64_kernel, dim3((unsigned)ntiles), dim3(256), 0, s, probs, tiles, b);
+  hipLaunchKernelGGL(gemm64_kernel, dim3((unsigned)ntiles), dim3(64 * NW), 0, s, probs, tiles, b);
 }
 
 }  // namespace adapm

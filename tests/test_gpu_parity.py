@@ -124,6 +124,27 @@ def test_both_contraction_paths_in_one_table(hp):
     run(ragged_bf16_table(), 6, dict(hp), tol_state=TOL16, tol_param=TOL16, check_every=2)
 
 
+def exact_edges_table(gd, many):
+    """Blocks of the exact path at the edges of its output tiles (16 and 32 wide), of the steps of the contraction (16 and
+    32 long) and of the two-column loads: ranks around 16, 32 and 128, sizes one beside a multiple; many: enough Gram
+    matrices for the larger of their two tile shapes (1024 tiles of 32 x 32 over four matrices of every block)."""
+    mk = BlockSpec
+    if many:
+        sizes = [(131, 129, 128)] * 15 + [(129, 200, 127)] * 2
+    else:
+        sizes = [(2, 2, 1), (3, 2, 2), (17, 33, 1), (15, 16, 15), (16, 48, 16), (33, 17, 17), (31, 65, 16), (64, 31, 31),
+                 (32, 64, 32), (97, 63, 33), (140, 150, 129)]
+    return WL.Workload("exact_edges", tuple(mk(f"b{i}_{m}x{n}_r{r}", m, n, "f32", gd, "lowrank", r, "element", 1, 1.0, 0.1)
+                                            for i, (m, n, r) in enumerate(sizes)), steps=4, seed=31, signal_rank=24)
+
+
+@pytest.mark.parametrize("gd,many", [("f32", False), ("bf16", False), ("bf16", True)])
+@pytest.mark.parametrize("T", [1, 2])
+def test_exact_path_at_the_edges_of_its_tiles(gd, many, T):
+    """fp64 contractions with every intermediate in fp64: the fp32 tolerance (state rounded once per step)."""
+    run(exact_edges_table(gd, many), 4, dict(T=T), tol_state=TOL32, tol_param=TOL32)
+
+
 def odd_rank_table():
     """bf16 blocks whose rank is not 32, 64 or 128 (the paper takes r = 5 % of the smaller dimension): the
     MFMA kernels run them in the next rank class with zero-padded images of the factors.  Ranks that are
