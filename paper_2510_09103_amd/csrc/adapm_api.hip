@@ -44,6 +44,8 @@ adapm_status_t fail(adapm_status_t code, const char* fmt, ...) {
 constexpr size_t ALIGN = 256;
 size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
+constexpr size_t STATIC_SCRATCH_BYTES = (size_t)64 << 20;   // the library's own scratch array (adapm_step_static)
+
 constexpr int EW_CHUNK = 8192;      // elements per workgroup of the update kernel
 constexpr int VS_CHUNK = 16384;     // elements per wavefront of the v-statistics kernel
 
@@ -64,6 +66,7 @@ struct Layout {                      // byte offsets, -1 = absent
   int64_t wT1 = -1, wT2 = -1;                               // ws: images of R_{t-1}^T and R_t^T for the fused update after Alg. 2
   int64_t nv = 0;
   int path = PATH_NONE;
+  bool stripes = false;                                     // MFMA path: the products of Alg. 2 run as stripes (choose_stripes)
 };
 
 enum OpKind { OP_GEMM, OP_GEMM_MFMA, OP_CHOL, OP_VSTAT, OP_VFINAL, OP_UPDATE, OP_QSPLIT, OP_PROJ, OP_QFIMG, OP_STRIPE, OP_QTIMG, OP_REFRESH_UPDATE, OP_GRADNORM, OP_GRAM, OP_GNORM, OP_UPDATE_GROUPED, OP_COPY, OP_PROJ_KEEP, OP_GRAM_FIN, OP_REGAUGE_APPLY };
@@ -204,9 +207,6 @@ int path_of(const adapm_block_t& b, const adapm_hparams_t& hp) {
                    b.cols <= (1 << 21);   // 128 rows of a stripe stay inside one 32-bit buffer range
   return (want && can) ? PATH_FAST : PATH_F64;
 }
-// Alg. 2 on the MFMA path: the two products that stream G (G R^T and L^T G) run as stripe products when the rows
-// of G are whole 16-byte vectors (both read G itself: stripes of rows, and stripes of columns in chunks of 64 rows)
-bool stripe_ok(const adapm_block_t& b) { return b.cols % 8 == 0; }
 // v of a block on the MFMA path can be finished inside the 128-row stripe of the fused kernel
 bool v_fusable(const adapm_block_t& b) {
   return b.v_mode == ADAPM_V_ROWGROUP && b.v_group_rows <= 128 && 128 % b.v_group_rows == 0;
@@ -333,14 +333,14 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
     constexpr int CUS = 256;
     int longest = 1;
     for (int64_t i : ids)
-      if (stripe_ok(c->table[i]))
+      if (c->lay[i].stripes)
         longest = std::max<int>(longest, (int)((std::max(c->table[i].rows, c->table[i].cols) + 63) / 64));
     int64_t best = -1;
     for (int seg = GRAM_SEG_CHUNKS; seg <= std::max(longest, GRAM_SEG_CHUNKS); ++seg) {
       int64_t wgs = 0;
       int maxlen = 0;
       for (int64_t i : ids) {
-        if (!stripe_ok(c->table[i])) continue;
+        if (!c->lay[i].stripes) continue;
         for (int64_t K : {c->table[i].rows, c->table[i].cols}) {
           const int nch = (int)((K + 63) / 64), nseg = (nch + seg - 1) / seg;
           wgs += nseg;
@@ -400,7 +400,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
     // Where the GD step rides on the stripe products, a workgroup reads and writes only the factor rows behind its own
     // stripe (everything else comes from the images), so the iterations after the first update one working copy in
     // place; the batched GEMM form reads whole rows of the old factor per output tile and alternates two copies.
-    const bool inplace = fast && stripe_ok(b);
+    const bool inplace = L.stripes;
     auto fL = [&](int which) { return mat(SP_WS, 0, (which && !inplace) ? L.wLb : L.wLa, r, 1, idt); };
     auto fR = [&](int which) { return mat(SP_WS, 0, (which && !inplace) ? L.wRb : L.wRa, n, 1, idt); };
     const Mat P = mat(SP_WS, 0, L.wP, r, 1, idt), S = mat(SP_WS, 0, L.wS, n, 1, idt);
@@ -415,7 +415,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       // thin products of Alg. 2 written without forming L R - m_t:
       //   (L R - m_t) R^T = L (R R^T) - (1-b1) G R^T - b1 L' (R' R^T)
       //   L^T (L R - m_t) = (L^T L) R - (1-b1) L^T G - b1 (L^T L') R'
-      if (fast && stripe_ok(b)) {
+      if (L.stripes) {
         // P = G R^T and S = L^T G = (G^T L)^T as stripe products on images of the current factors; the stripes of
         // G^T are 256 columns of G, read with transposing LDS reads
         Mat LcT = T(Lc);
@@ -491,7 +491,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       // optional: both updates of this iteration take eta / max(||R R^T||_F, ||L^T L||_F), a device scalar
       const int64_t off_s = hp.refresh_normalise ? L.wNu : -1;
       if (hp.refresh_normalise) c->gnorm[gnorm0 + e].h.push_back(GnormItem{L.wGrr, L.wGll, L.wNu, r, idt});
-      if (fast && !stripe_ok(b)) {
+      if (fast && !L.stripes) {
         p = problem(m, r);
         p.A1 = Lc; p.B1 = Grr; p.K1 = r; p.a1 = -eta;
         p.A2 = Lp; p.B2 = Gpr; p.K2 = r; p.a2 = eta * b1;
@@ -538,8 +538,8 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       d.l1 = Lp.ref; d.l2 = Lc.ref; d.q1 = Rp.ref; d.q2 = Rc.ref; d.off_img1 = L.wT1; d.off_img2 = L.wT2; d.off_v = L.sv;
       c->rub[grp].h.push_back(d);
       for (int ch = 0; ch < (n + 63) / 64; ++ch) {
-        if (hp.bias_correction && !(stripe_ok(b) && n_eff > 0)) c->qt[grp].h.push_back(ImgItem{Rp, r, n, ch, d.rc, L.wT1});
-        if (!(stripe_ok(b) && n_eff > 0)) c->qt[grp].h.push_back(ImgItem{Rc, r, n, ch, d.rc, L.wT2});   // else: written by the stripes
+        if (hp.bias_correction && !(L.stripes && n_eff > 0)) c->qt[grp].h.push_back(ImgItem{Rp, r, n, ch, d.rc, L.wT1});
+        if (!(L.stripes && n_eff > 0)) c->qt[grp].h.push_back(ImgItem{Rc, r, n, ch, d.rc, L.wT2});   // else: written by the stripes
       }
     } else {
       // m x n low-rank term of m^c (eq. 4): C = L'R' - L R, or L R without the correction
@@ -797,7 +797,7 @@ size_t layout_block_scratch(const adapm_block_t& b, const adapm_hparams_t& hp, L
   Layout& T = dry ? tmp : L;
   auto walloc = [&](size_t bytes) { int64_t o = (int64_t)wo; wo += align_up(bytes); return o; };
   const int64_t m = b.rows, n = b.cols, r = b.rank;
-  const bool fast = L.path == PATH_FAST, stripes = fast && stripe_ok(b);
+  const bool fast = L.path == PATH_FAST, stripes = L.stripes;
   // F64 path: every intermediate of a step stays in fp64, only the state is rounded to fp32
   const size_t es = fast ? 4 : 8;
   T.wLa = walloc(es * m * r); T.wRa = walloc(es * r * n);
@@ -829,6 +829,74 @@ size_t layout_block_scratch(const adapm_block_t& b, const adapm_hparams_t& hp, L
     if (gram_segments(m) > 1) T.wGpm = walloc((size_t)gram_segments(m) * 2 * rc * rc * 4);
   }
   return wo;
+}
+
+// Scratch that a group of low-rank blocks may take: a margin below the state size, at least 32 MiB and the largest block
+size_t scratch_budget(const adapm_ctx* c, size_t persistent) {
+  size_t largest = 0;
+  for (size_t i = 0; i < c->table.size(); ++i) {
+    Layout L = c->lay[i];
+    if (L.path != PATH_NONE) largest = std::max(largest, layout_block_scratch(c->table[i], c->hp, L, 0, true));
+  }
+  const size_t floor_bytes = (size_t)32 << 20;
+  const size_t budget = c->state_bytes > persistent + floor_bytes ? c->state_bytes - persistent : floor_bytes;
+  return std::max(budget - budget / 16, largest);
+}
+
+// The low-rank blocks of a contraction path in table order, cut into groups of about equal scratch: as few as the budget
+// allows, none above it
+std::vector<std::vector<int64_t>> cut_groups(const adapm_ctx* c, int path, size_t budget) {
+  std::vector<std::vector<int64_t>> groups;
+  std::vector<size_t> need(c->table.size(), 0);
+  size_t total = 0;
+  for (size_t i = 0; i < c->table.size(); ++i) {
+    Layout L = c->lay[i];
+    if (L.path == path) total += need[i] = layout_block_scratch(c->table[i], c->hp, L, 0, true);
+  }
+  const size_t n_groups = (total + budget - 1) / budget;
+  const size_t target = n_groups ? (total + n_groups - 1) / n_groups : 0;
+  size_t used = 0;
+  for (size_t i = 0; i < c->table.size(); ++i) {
+    if (c->lay[i].path != path) continue;
+    if (groups.empty() || used + need[i] > budget || used >= target) { groups.emplace_back(); used = 0; }
+    groups.back().push_back((int64_t)i);
+    used += need[i];
+  }
+  return groups;
+}
+
+// Which blocks of the MFMA path run the products of Alg. 2 as stripe products (both read G itself: stripes of rows, and
+// stripes of columns in chunks of 64 rows).  Blocks whose rows are whole 16-byte vectors always do.  The others do where
+// the stripes' scratch (fragment images of the factors, padded to the rank class: 16 rc instead of 12 r bytes per row and
+// column of the block) stays inside the budget that the batched GEMMs have: a tall block of a small rank does not.
+// (1.34 B parameters with 24 blocks of 2048 x 5461 at r = 128: a step that runs Alg. 2 takes 18.2 ms with those blocks on
+// GEMMs, whose 128 x 128 tiles split every operand again in every tile, and 15.0 ms in stripes.)
+// Returns whether the plan on GEMMs fits the library's own scratch array (adapm_step_static); the plan then has to as well.
+// persistent: an upper bound of the part of the workspace that is not a group's scratch.
+bool choose_stripes(adapm_ctx* c, size_t persistent) {
+  bool any = false;
+  for (size_t i = 0; i < c->table.size(); ++i) {
+    Layout& L = c->lay[i];
+    L.stripes = L.path == PATH_FAST && c->table[i].cols % 8 == 0;
+    any = any || (L.path == PATH_FAST && !L.stripes);
+  }
+  if (!any) return false;
+  size_t budget = scratch_budget(c, persistent), scratch = 0;
+  for (int path : {PATH_F64, PATH_FAST})
+    for (const std::vector<int64_t>& ids : cut_groups(c, path, budget)) {
+      size_t used = 0;
+      for (int64_t i : ids) { Layout L = c->lay[i]; used += layout_block_scratch(c->table[i], c->hp, L, 0, true); }
+      scratch = std::max(scratch, used);
+    }
+  const bool fits_static = persistent + scratch <= STATIC_SCRATCH_BYTES;
+  if (fits_static) budget = std::min(budget, STATIC_SCRATCH_BYTES - persistent);
+  for (size_t i = 0; i < c->table.size(); ++i) {
+    Layout L = c->lay[i];
+    if (L.path != PATH_FAST || L.stripes) continue;
+    L.stripes = true;
+    c->lay[i].stripes = layout_block_scratch(c->table[i], c->hp, L, 0, true) <= budget;
+  }
+  return fits_static;
 }
 
 // Lay out state / workspace and build every work list.
@@ -866,6 +934,20 @@ void build_plan(adapm_ctx* c) {
     L.sv = salloc(4 * L.nv);
   }
   c->state_bytes = so;
+  // the part of the workspace that is not a group's scratch, from above (the partial sums of blocks whose v is finished
+  // elsewhere do not exist): which blocks those are depends on the choice made here
+  size_t ws_global = wo, ws_images = 0;
+  bool any_f64 = false;
+  for (int64_t i = 0; i < nb; ++i) {
+    const adapm_block_t& b = c->table[i];
+    const int64_t ge = group_elems(b);
+    if (b.v_mode != ADAPM_V_ELEMENT && ge > VS_CHUNK) ws_global += 8 * (size_t)(c->lay[i].nv * ((ge + VS_CHUNK - 1) / VS_CHUNK));
+    ws_global += 8 * (size_t)((b.rows * b.cols + VS_CHUNK - 1) / VS_CHUNK);       // global gradient norm
+    any_f64 = any_f64 || c->lay[i].path == PATH_F64;
+    if (c->lay[i].path == PATH_FAST && hp.refresh_period_T > 1)
+      ws_images += align_up(proj_qf_bytes(rank_class(b.rank), (int)b.cols)) + align_up(proj_timg_bytes(rank_class(b.rank), (int)b.cols));
+  }
+  const bool fits_static = choose_stripes(c, ws_global + 3 * ALIGN + (any_f64 ? ws_images : 0));
   c->ew.clear();
   c->ew.emplace_back();          // list 0: full / no momentum blocks
 
@@ -901,7 +983,7 @@ void build_plan(adapm_ctx* c) {
       // on the MFMA path with T > 1 the fused kernel finishes fusable groups itself on steps with R held (list 1: only
       // steps that run Alg. 2), and where Alg. 2 streams G in stripes its first GD iteration does so (no list at all)
       const int which = (L.path == PATH_FAST && hp.refresh_period_T > 1 && v_fusable(b)) ? 1 : 0;
-      const bool in_stripes = L.path == PATH_FAST && v_fusable(b) && stripe_ok(b) &&
+      const bool in_stripes = L.path == PATH_FAST && v_fusable(b) && L.stripes &&
                               !effective_step_sizes(hp.refresh_iters_K).empty() && (which == 1 || hp.refresh_period_T == 1);
       const int64_t ge = d.group_elems;
       for (int64_t g = 0; g < (in_stripes ? 0 : L.nv); ++g) {
@@ -968,12 +1050,8 @@ void build_plan(adapm_ctx* c) {
   if (c->n_lowrank == 0) return;
 
   // ---- groups of low-rank blocks: scratch budget, then per group the layout and the launches
-  size_t largest = 0;
-  for (int64_t i = 0; i < nb; ++i)
-    if (c->lay[i].path != PATH_NONE) largest = std::max(largest, layout_block_scratch(c->table[i], hp, c->lay[i], 0, true));
-  const size_t floor_bytes = (size_t)32 << 20;
-  size_t budget = c->state_bytes > persistent + floor_bytes ? c->state_bytes - persistent : floor_bytes;
-  budget = std::max(budget - budget / 16, largest);          // a margin below the state size; at least one block
+  size_t budget = scratch_budget(c, persistent);
+  if (fits_static) budget = std::min(budget, STATIC_SCRATCH_BYTES - persistent);
   size_t scratch_max = 0;
   if (hp.refresh_period_T > 1) {
     c->gemms.emplace_back();
@@ -982,16 +1060,7 @@ void build_plan(adapm_ctx* c) {
     c->rg_chol = (int)c->chol.size() - 1;
   }
   for (int path : {PATH_F64, PATH_FAST}) {
-    // groups of about equal size: as few as the budget allows, none above it
-    size_t total = 0;
-    for (int64_t i = 0; i < nb; ++i)
-      if (c->lay[i].path == path) total += layout_block_scratch(c->table[i], hp, c->lay[i], 0, true);
-    const size_t n_groups = (total + budget - 1) / budget;
-    const size_t target = n_groups ? (total + n_groups - 1) / n_groups : 0;
-    std::vector<int64_t> ids;
-    size_t used = 0;
-    auto flush = [&]() {
-      if (ids.empty()) return;
+    for (const std::vector<int64_t>& ids : cut_groups(c, path, budget)) {
       size_t at = persistent;
       for (int64_t i : ids) {
         at = layout_block_scratch(c->table[i], hp, c->lay[i], at, false);
@@ -1001,17 +1070,7 @@ void build_plan(adapm_ctx* c) {
       const int ew_before = (int)c->ew.size();
       plan_lowrank_refresh(c, path == PATH_FAST, ids);
       if (hp.refresh_period_T > 1 && path == PATH_F64) plan_lowrank_project_f64(c, ids, ew_before);
-      ids.clear();
-      used = 0;
-    };
-    for (int64_t i = 0; i < nb; ++i) {
-      if (c->lay[i].path != path) continue;
-      const size_t need = layout_block_scratch(c->table[i], hp, c->lay[i], 0, true);
-      if (!ids.empty() && (used + need > budget || used >= target)) flush();
-      ids.push_back(i);
-      used += need;
     }
-    flush();
   }
   c->ws_bytes = std::max(images_end, persistent + scratch_max);
   if (hp.refresh_period_T > 1 && !c->rg_apply.h.empty()) {
@@ -1031,7 +1090,6 @@ size_t bytes_of(const std::vector<T>& v) { return align_up(v.size() * sizeof(T))
 // array's NAME is only a stand-in for the symbol, not a device address: host code uses the pointer that
 // hipGetSymbolAddress returned for the device in question, looked up once per device at set-up.
 // ---------------------------------------------------------------------------
-constexpr size_t STATIC_SCRATCH_BYTES = (size_t)64 << 20;
 constexpr int MAX_DEVICES = 64;
 char* g_scratch_ptr[MAX_DEVICES] = {nullptr};
 const adapm_ctx* g_scratch_user[MAX_DEVICES] = {nullptr};     // context whose step used a device's scratch array last

@@ -1,7 +1,7 @@
 // Split-bf16 MFMA version of the strided two-product GEMM (the "BF16X2" contraction mode):
 //   Out = a1 * A1 B1 + a2 * A2 B2 + g * X + d * Y        (fp32 accumulation and output)
-// used for the thin products of Alg. 2 (G R^T, L^T G, Gram matrices, factor updates) and the
-// reconstruction L_{t-1}R_{t-1} - L_t R_t of eq. 3-4 on blocks with bf16 gradients.
+// used for the thin products of Alg. 2 (G R^T, L^T G, Gram matrices, factor updates) on the bf16-gradient blocks that the
+// stripe kernels do not take (rows that are no whole vectors, and images beyond the scratch: choose_stripes in adapm_api.hip).
 // bf16 operands (G) are exact; an fp32 operand x travels as hi = bf16(x), lo = bf16(x - hi), and a
 // product of two operands keeps hi*hi + lo*hi + hi*lo (the lo*lo term, 2^-18 relative, is dropped).
 // One workgroup computes a 128 x 128 output tile; each of its four waves owns 64 x 64 (2 x 2 MFMA tiles).

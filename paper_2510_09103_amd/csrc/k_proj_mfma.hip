@@ -308,10 +308,12 @@ __device__ __forceinline__ void stripe_pass1_x2(unsigned char* smem, const Strip
   float ss[4] = {0.f, 0.f, 0.f, 0.f};   // this streaming thread's sums of squares of rows t512 / 8 + 64 i
   auto fetch_g = [&](int c, uint4 (&dst)[4]) {
     if (TRA) {
-      // the chunk's own range: rows at or beyond K read zeros; 32-bit offsets stay below 64 rows of the matrix
-      const int rows = src.K - c * BK < BK ? src.K - c * BK : BK;
+      // the chunk's own range: rows at or beyond K read zeros; 32-bit offsets stay below 64 rows of the matrix.  A vector
+      // across the end of a row takes the next row's first columns for columns the stripe does not have (their results
+      // are dropped); behind the last row the range ends, with the last whole dword (see stripe_kernel)
+      const int left = src.K - c * BK, rows = left < BK ? left : BK;
       const __amdgpu_buffer_rsrc_t rc = make_rsrc(src.base + (int64_t)c * BK * src.ld,
-                                                  rows > 0 ? (unsigned)(((int64_t)(rows - 1) * src.ld + src.width) * 2) : 0u);
+                                                  rows > 0 ? (unsigned)(((int64_t)(rows - 1) * src.ld + (left > BK ? src.width + 7 : src.width & ~1)) * 2) : 0u);
       const bool ok = tj < src.width;
 #pragma unroll
       for (int i = 0; i < 4; ++i) dst[i] = buf_load16(rc, ok ? (unsigned)((tr + 16 * i) * (int)src.ld + tj) * 2u : OOB);
@@ -1325,7 +1327,10 @@ __global__ __launch_bounds__(NT, 1) void stripe_kernel(const StripeItem* __restr
   // row stride of P in LDS: with the transposed store the lanes of a wave walk down a column of P, which an odd
   // stride spreads over all banks
   constexpr int R = 32 * RT, PS = TRA ? R + 1 : Pass1x2<RT>::PS, ROWS = Pass1x2<RT>::ROWS;
-  constexpr int SMEM = Pass1x2<RT>::BYTES > Pass1x2<RT>::P_BYTES ? Pass1x2<RT>::BYTES : Pass1x2<RT>::P_BYTES;
+  constexpr int TAIL = (ROWS + R) * 8 * 4;            // beside P: the last columns of A and Q where rows are not whole vectors
+  constexpr int P_END = ROWS * PS * 4;
+  constexpr int SMEM = Pass1x2<RT>::BYTES > P_END + TAIL ? Pass1x2<RT>::BYTES : P_END + TAIL;
+  static_assert(P_END % 16 == 0, "the tail is addressed in vectors");
   __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
   const StripeItem item = items[blockIdx.x];
   if (item.prob < 0) return;
@@ -1338,7 +1343,7 @@ __global__ __launch_bounds__(NT, 1) void stripe_kernel(const StripeItem* __restr
     src.base = A + row0; src.ld = M; src.K = K; src.width = (int)rows_valid;
   } else {
     src.rG = make_rsrc(A + (int64_t)row0 * K, rows_valid * (unsigned)K * 2u);
-    src.n = K; src.nv = K;
+    src.n = K; src.nv = K & ~7;
   }
   __shared__ float rsum[ROWS];        // sums of squares of the stripe's rows (second moment)
   const int r = P.r;                  // rows of Q actually present (the image is zero-padded to R)
@@ -1369,6 +1374,51 @@ __global__ __launch_bounds__(NT, 1) void stripe_kernel(const StripeItem* __restr
   }
   stripe_pass1_x2<RT, TRA>(smem, src, bs.ws + P.off_img, (!TRA && P.v_rows > 0) ? rsum : nullptr, tl);
   __syncthreads();
+  // Rows of the gradient that are not whole 16-byte vectors (nt columns beyond the last one; K or, transposed, M is no
+  // multiple of 8).  They may start at any 2-byte alignment, which the loads serve; what the pass leaves out is added here,
+  // outside its loops (inside them the few instructions cost rows that are whole vectors 1 - 2 %), with Q as (hi, lo)
+  // from its image like the matrix instructions take it:
+  //  rows:    the products and squares of the last nt columns, P(row, a) += A(row, n8 + c) Q(a, n8 + c);
+  //  columns: one element.  The range check cuts a vector that reaches past the very end of the matrix in whole dwords;
+  //           where the stripe's last column sits alone in its dword, the last row's element there is left out.
+  const int nt = (TRA ? M : K) & 7;
+  if (nt > 0 && (!TRA || (row0 + ROWS >= M && (rows_valid & 1u)))) {
+    float* const gt = reinterpret_cast<float*>(smem + P_END);   // [ROWS][8]; TRA: the one element
+    float* const qt = gt + ROWS * 8;                            // [R][8]; TRA: [R][1]
+    const int k0 = TRA ? K - 1 : K & ~7, nk = TRA ? 1 : nt;
+    const uint16_t* img = reinterpret_cast<const uint16_t*>(bs.ws + P.off_img);
+    for (int id = tid; id < (ROWS + R) * 8; id += NT) {
+      const int c = id & 7;
+      float x = 0.f;
+      if (id < ROWS * 8) {
+        const int row = id >> 3;
+        const bool ok = TRA ? row == (int)rows_valid - 1 : (unsigned)row < rows_valid;
+        if (c < nk && ok) x = bf16lo((uint32_t)A[TRA ? (int64_t)(K - 1) * M + row0 + row : (int64_t)(row0 + row) * K + k0 + c]);
+      } else if (c < nk) {
+        const int a = (id >> 3) - ROWS, k = k0 + c, kk = (k & (BK - 1)) >> 4, ln = (a & 31) + 32 * ((k >> 3) & 1);
+        const uint16_t* e = img + (int64_t)(k / BK) * (Pass1x2<RT>::QF / 2) + ((kk * RT + a / 32) * 2 * 64 + ln) * 8 + (k & 7);
+        x = bf16lo((uint32_t)e[0]) + bf16lo((uint32_t)e[512]);
+      }
+      gt[id] = x;
+    }
+    __syncthreads();
+    float* Pw = reinterpret_cast<float*>(smem);
+    const float cp = P.upd ? tl.cp : 1.f;
+    for (int id = tid; id < ROWS * R; id += NT) {
+      const int row = id / R, a = id % R;
+      float acc = 0.f;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc = fmaf(gt[row * 8 + c], qt[a * 8 + c], acc);
+      Pw[row * PS + a] += cp * acc;
+    }
+    if (!TRA && P.v_rows > 0 && tid < ROWS) {
+      float q = 0.f;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) q = fmaf(gt[tid * 8 + c], gt[tid * 8 + c], q);
+      rsum[tid] += q;
+    }
+    __syncthreads();
+  }
   if (P.v_rows > 0) {               // groups of v_rows rows inside the stripe (v_rows divides 128)
     const int g = P.v_rows;
     if (tid < ROWS / g && row0 + tid * g < M) {
@@ -1418,7 +1468,7 @@ __global__ __launch_bounds__(NT, 1) void stripe_kernel(const StripeItem* __restr
     // Out[a][row0 + j] = P[j][a], four consecutive j (16 bytes) of one a per access.  A wave covers 4 values of a x 64
     // values of j: 256 contiguous bytes per a in memory, and with the odd row stride of P its 64 lanes fall on 64
     // different LDS banks.  The elements of the old factor are requested together, on clamped (valid) addresses,
-    // before any of them is used.  (M is a multiple of 8 here: the stripes take only such blocks.)
+    // before any of them is used.
     constexpr int NI = (ROWS / 4) * R / NT;
     const int j4 = 64 * ((tid >> 6) & 3) + 4 * (tid & 15), a0 = 4 * (tid >> 8) + ((tid >> 4) & 3);
     const bool jok = row0 + j4 < M;
@@ -1426,21 +1476,58 @@ __global__ __launch_bounds__(NT, 1) void stripe_kernel(const StripeItem* __restr
     float4 xo[NI];
 #pragma unroll
     for (int i = 0; i < NI; ++i) xo[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (Xc) {
+    if ((M & 3) == 0) {
+      if (Xc) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          const int a = a0 + 4 * (NT / 256) * i;
+          xo[i] = *reinterpret_cast<const float4*>(Xc + (int64_t)(a < r ? a : 0) * M + col);
+        }
+      }
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
         const int a = a0 + 4 * (NT / 256) * i;
-        xo[i] = *reinterpret_cast<const float4*>(Xc + (int64_t)(a < r ? a : 0) * M + col);
+        float* ps = Ps + j4 * PS + a;
+        float4 v = make_float4(gs * ps[0] + xo[i].x, gs * ps[PS] + xo[i].y, gs * ps[2 * PS] + xo[i].z, gs * ps[3 * PS] + xo[i].w);
+        if (jok && a < r) *reinterpret_cast<float4*>(Out + (int64_t)a * M + col) = v;
+        else v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (emit) { ps[0] = v.x; ps[PS] = v.y; ps[2 * PS] = v.z; ps[3 * PS] = v.w; }
       }
-    }
+    } else {
+      // the rows of the factor start at 4-byte alignments; the lane at their end, with nj < 4 elements left, reads the
+      // row's last four and stores one by one
+      const int nj = jok ? (M - row0 - j4 < 4 ? M - row0 - j4 : 4) : 0, back = jok ? 4 - nj : 0;
+      if (Xc) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int a = a0 + 4 * (NT / 256) * i;
-      float* ps = Ps + j4 * PS + a;
-      float4 v = make_float4(gs * ps[0] + xo[i].x, gs * ps[PS] + xo[i].y, gs * ps[2 * PS] + xo[i].z, gs * ps[3 * PS] + xo[i].w);
-      if (jok && a < r) *reinterpret_cast<float4*>(Out + (int64_t)a * M + col) = v;
-      else v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (emit) { ps[0] = v.x; ps[PS] = v.y; ps[2 * PS] = v.z; ps[3 * PS] = v.w; }
+        for (int i = 0; i < NI; ++i) {
+          const int a = a0 + 4 * (NT / 256) * i;
+          const f32x4_a4 t = *reinterpret_cast<const f32x4_a4*>(Xc + (int64_t)(a < r ? a : 0) * M + (jok ? col - back : 0));
+          xo[i] = make_float4(t.x, t.y, t.z, t.w);
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          if (back & 2) { xo[i].x = xo[i].z; xo[i].y = xo[i].w; }
+          if (back & 1) { xo[i].x = xo[i].y; xo[i].y = xo[i].z; xo[i].z = xo[i].w; }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int a = a0 + 4 * (NT / 256) * i;
+        float* ps = Ps + j4 * PS + a;
+        float4 v = make_float4(gs * ps[0] + xo[i].x, gs * ps[PS] + xo[i].y, gs * ps[2 * PS] + xo[i].z, gs * ps[3 * PS] + xo[i].w);
+        float* const out = Out + (int64_t)a * M + col;
+        if (nj == 4 && a < r) {
+          *reinterpret_cast<f32x4_a4*>(out) = f32x4_a4{v.x, v.y, v.z, v.w};
+        } else if (nj > 0 && a < r) {
+          out[0] = v.x;
+          if (nj > 1) out[1] = v.y; else v.y = 0.f;
+          if (nj > 2) out[2] = v.z; else v.z = 0.f;
+          v.w = 0.f;
+        } else {
+          v = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        if (emit) { ps[0] = v.x; ps[PS] = v.y; ps[2 * PS] = v.z; ps[3 * PS] = v.w; }
+      }
     }
   }
   if (emit) __syncthreads();

@@ -262,3 +262,16 @@ def test_grad_clip_setter_validates():
     with pytest.raises(B.AdapmError):
         B.adapm_set_grad_clip(ctx, float("nan"))
     B.adapm_destroy(ctx)
+
+
+def test_tables_that_fit_the_static_scratch_still_do():
+    """Blocks whose rows are no whole vectors take the stripe kernels' larger scratch only where the plan without them keeps
+    its bound: 16 rc instead of 12 r bytes per row and column, so a tall block of rank 1 would grow 20-fold."""
+    BF, static = B.ADAPM_BF16, 64 << 20
+    tall = [blk(rows=1 << 17, cols=9, rank=1, param_dtype=BF, grad_dtype=BF)]
+    many = [blk(rows=512, cols=1001, rank=32, param_dtype=BF, grad_dtype=BF, v_mode=B.ADAPM_V_ELEMENT) for _ in range(70)]
+    for table in (tall, many, tall + many[:20]):
+        for T in (1, 10):
+            ctx = B.adapm_init(table, make_hparams(T=T))
+            assert B.adapm_workspace_bytes(ctx) <= static
+            B.adapm_destroy(ctx)

@@ -116,6 +116,19 @@ def test_ragged_shapes_on_the_mfma_path(hp):
     run(ragged_bf16_table(), 6, hp, tol_state=TOL16, tol_param=TOL16, check_every=2)
 
 
+@pytest.mark.parametrize("first", [1, 4])
+@pytest.mark.parametrize("hp", [dict(T=1), dict(T=3)])
+def test_every_row_remainder_in_the_stripe_products(first, hp):
+    """Row lengths of every remainder mod 8 (and so mod 4), below one vector's width past a 64-column chunk and past a
+    256-column stripe: the vector at the end of a row is read at the row's last 8 columns and moved down, and the rows of R
+    are stored at 4-byte alignments.  The per-row second moment takes the rows' sums of squares from the same vectors."""
+    wl = WL.Workload("remainders", tuple(
+        BlockSpec(f"c{c}_r{r}", 70 + c % 7, c, "bf16", "bf16", "lowrank", r, v, 1, 1.0, 0.1)
+        for r, v, base in ((8, "rowgroup", 8), (40, "element", 64), (70, "rowgroup", 256), (32, "whole", 512 + 56))
+        for c in range(base + first, base + first + 4)), steps=4, seed=9, signal_rank=8)
+    run(wl, 4, dict(hp, contraction=B.ADAPM_CONTRACT_BF16X2), tol_state=TOL16, tol_param=TOL16, check_every=2)
+
+
 @pytest.mark.parametrize("hp", [dict(T=1), dict(T=3)])
 def test_both_contraction_paths_in_one_table(hp):
     """Automatic choice of the contraction: the fp32-parameter blocks of the table take the exact path, the bf16 ones
