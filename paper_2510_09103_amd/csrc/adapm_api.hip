@@ -139,7 +139,7 @@ struct adapm_ctx {
   std::vector<DevList<CopyItem>> cp;    // T = 1, MFMA path: the factors Alg. 2 leaves in the workspace -> state
   std::vector<DevList<RuBlockDev>> rub; // fused update after Alg. 2 (MFMA path): blocks, images of R^T, stripes
   std::vector<DevList<ImgItem>> qt;
-  std::vector<DevList<ProjItem>> ru;    //   6 per group: (rank class 32 / 64 / 128) x (fp32 / bf16 parameters)
+  std::vector<DevList<ProjItem>> ru;    //   12 per group: (rank class 32 / 64 / 128) x (fp32 / bf16 parameters) x (blockwise / per-element v)
   int n_groups = 0;
   int rg_gram = -1, rg_chol = -1;       // T > 1, MFMA path: the re-expression of all blocks' factors after the last group
   DevList<RegaugeItem> rg_apply;
@@ -359,8 +359,8 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
   const int grp = c->n_groups++;
   c->cp.emplace_back(); c->rub.emplace_back(); c->qt.emplace_back(); c->chol.emplace_back();
   const int chol_id = (int)c->chol.size() - 1;
-  c->ru.resize(c->ru.size() + 6);
-  const int ru0 = 6 * grp;
+  c->ru.resize(c->ru.size() + 12);
+  const int ru0 = 12 * grp;
   const int img0 = (int)c->img.size(), sit0 = (int)c->sit.size(), gram0 = (int)c->gram.size();
   const int ew_id = fast ? -1 : (int)c->ew.size();
   if (!fast) c->ew.emplace_back();
@@ -634,15 +634,16 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
   const float cG = hp.bias_correction ? 1.f : 0.f;
   const float cC = hp.bias_correction ? (float)(b1 / (1.0 - b1)) : 1.f;
   if (fast) {
-    // stripes of the fused update, per (rank class, parameter type), whole blocks dealt to XCDs
+    // stripes of the fused update, per (rank class, parameter type, kind of v), whole blocks dealt to XCDs
     if (!c->qt[grp].h.empty()) seq.push_back(Op{OP_QTIMG, grp, 0, 0, "update_factor_images"});
-    for (int cls = 0; cls < 6; ++cls) {
-      const int rank = 32 << (cls >> 1);
+    for (int cls = 0; cls < 12; ++cls) {      // (rank 32 / 64 / 128) x (fp32 / bf16 parameters) x (blockwise / per-element v)
+      const int rank = 32 << ((cls >> 1) % 3);
       const int pdt = (cls & 1) ? ADAPM_BF16 : ADAPM_F32;
+      const bool vel = cls >= 6;
       std::vector<size_t> ids;
       const std::vector<RuBlockDev>& rubs = c->rub[grp].h;
       for (size_t k = 0; k < rubs.size(); ++k)
-        if (rubs[k].rc == rank && rubs[k].param_dtype == pdt) ids.push_back(k);
+        if (rubs[k].rc == rank && rubs[k].param_dtype == pdt && (rubs[k].v_kind == 0) == vel) ids.push_back(k);
       if (ids.empty()) continue;
       std::stable_sort(ids.begin(), ids.end(), [&](size_t a, size_t b2) {
         const RuBlockDev &x = rubs[a], &y = rubs[b2];
@@ -663,7 +664,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       for (size_t q = 0; q < longest; ++q)
         for (int x = 0; x < NXCD; ++x) c->ru[ru0 + cls].h.push_back(q < per[x].size() ? per[x][q] : ProjItem{-1, 0});
       static const char* names[3] = {"fused_refresh_update_r32", "fused_refresh_update_r64", "fused_refresh_update_r128"};
-      seq.push_back(Op{OP_REFRESH_UPDATE, ru0 + cls, cG, cC, names[cls >> 1], grp});
+      seq.push_back(Op{OP_REFRESH_UPDATE, ru0 + cls, cG, cC, names[(cls >> 1) % 3], grp});
     }
   } else {
     seq.push_back(Op{gk, l_epi, 0, 0, "reconstruct_f64"});
@@ -1303,7 +1304,7 @@ adapm_status_t run_op(adapm_ctx* c, const Op& op, Bases& bs, const StepScalars& 
     case OP_REFRESH_UPDATE: {
       StepScalars x = sc;
       x.cG = op.cG; x.cC = op.cC;
-      launch_refresh_update(1 << ((op.index % 6) >> 1), (op.index & 1) != 0, c->ru[op.index].d, (int64_t)c->ru[op.index].h.size(),
+      launch_refresh_update(1 << (((op.index % 12) >> 1) % 3), (op.index & 1) != 0, op.index % 12 >= 6, c->ru[op.index].d, (int64_t)c->ru[op.index].h.size(),
                             c->rub[op.aux].d, bs, x, s);
       break;
     }

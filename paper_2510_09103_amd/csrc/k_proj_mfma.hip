@@ -1006,61 +1006,71 @@ __global__ __launch_bounds__(256) void qimage_kernel(const QsItem* __restrict__ 
 // a_p L_p as A-fragments and builds the 32 x 32 tile of product p from the image of Q_p^T (copied
 // global -> LDS without registers, two buffers); the streaming waves add the two partial tiles, apply the
 // update and keep G, W of the next tiles in flight.
-template <bool W16>
+template <bool W16, bool VEL>
 struct RuTail {
-  // one 8-element vector of a row: columns col .. col+7 of the stripe
-  static __device__ __forceinline__ void run(const float (&c)[8], const uint4& gq, const uint4 (&wq)[W16 ? 1 : 2],
-                                             bool ok, unsigned e, __amdgpu_buffer_rsrc_t rW, float* vp, bool v_elem,
-                                             float vinv, const StepScalars& sc, const UpdCoef& cf, float bound, float gs2) {
+  // one 8-element vector of a row (VEL: with its old second moments vq), its low-rank term = the sum of the two products'
+  // partial tiles at ca, cb.  VEL: four elements at a time, all eight at once spill.
+  static __device__ __forceinline__ void run(const float* ca, const float* cb, const uint4& gq, const uint4 (&wq)[W16 ? 1 : 2],
+                                             const uint4 (&vq)[VEL ? 2 : 1], bool ok, unsigned e, __amdgpu_buffer_rsrc_t rW,
+                                             __amdgpu_buffer_rsrc_t rV, float vinv, const StepScalars& sc, const UpdCoef& cf,
+                                             float bound, float gs2) {
     const uint32_t gw[4] = {gq.x, gq.y, gq.z, gq.w};
-    float g[8], mc[8], inv[8];
+    uint32_t o[4];
+    float c[8];
+    auto low_rank = [&](int half) {
+      const float4 a = *reinterpret_cast<const float4*>(ca + 4 * half), b = *reinterpret_cast<const float4*>(cb + 4 * half);
+      c[4 * half] = a.x + b.x; c[4 * half + 1] = a.y + b.y; c[4 * half + 2] = a.z + b.z; c[4 * half + 3] = a.w + b.w;
+    };
+    if (!VEL) { low_rank(0); low_rank(1); }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) { g[2 * k] = bf16lo(gw[k]); g[2 * k + 1] = bf16hi(gw[k]); }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) mc[k] = fmaf(sc.cC, c[k], sc.cG * g[k]);
-    if (v_elem) {                   // per-element second moment
-      float vv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if (ok) {
-        const f32x4_a4 va = reinterpret_cast<const f32x4_a4*>(vp)[0], vb = reinterpret_cast<const f32x4_a4*>(vp)[1];
-        vv[0] = va.x; vv[1] = va.y; vv[2] = va.z; vv[3] = va.w;
-        vv[4] = vb.x; vv[5] = vb.y; vv[6] = vb.z; vv[7] = vb.w;
+    for (int half = 0; half < 2; ++half) {
+      if (VEL) {
+        __builtin_amdgcn_sched_barrier(0);
+        low_rank(half);
       }
-      const float ob2 = (1.f - sc.beta2) * gs2;                    // v sees the clipped gradient
+      float g[4], mc[4], inv[4];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        vv[k] = sc.beta2 * vv[k] + ob2 * g[k] * g[k];
-        inv[k] = inv_denom_fast(vv[k], sc.inv_debias_v, sc.inv_debias_m * cf.neg_lrs, sc.eps);   // -lr folded in
+      for (int k = 0; k < 2; ++k) { g[2 * k] = bf16lo(gw[2 * half + k]); g[2 * k + 1] = bf16hi(gw[2 * half + k]); }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) mc[k] = fmaf(sc.cC, c[4 * half + k], sc.cG * g[k]);
+      if (VEL) {                    // per-element second moment; it sees the clipped gradient
+        const uint4 vo = vq[VEL ? half : 0];
+        const float old[4] = {__uint_as_float(vo.x), __uint_as_float(vo.y), __uint_as_float(vo.z), __uint_as_float(vo.w)};
+        const float ob2 = (1.f - sc.beta2) * gs2;
+        float vv[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          vv[k] = sc.beta2 * old[k] + ob2 * g[k] * g[k];
+          inv[k] = inv_denom_fast(vv[k], sc.inv_debias_v, sc.inv_debias_m * cf.neg_lrs, sc.eps);   // -lr folded in
+        }
+        buf_store16(rV, ok ? e * 4u + 16u * half : OOB,
+                    make_uint4(__float_as_uint(vv[0]), __float_as_uint(vv[1]), __float_as_uint(vv[2]), __float_as_uint(vv[3])));
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) inv[k] = vinv;                  // -lr already folded in
       }
-      if (ok) {
-        reinterpret_cast<f32x4_a4*>(vp)[0] = f32x4_a4{vv[0], vv[1], vv[2], vv[3]};
-        reinterpret_cast<f32x4_a4*>(vp)[1] = f32x4_a4{vv[4], vv[5], vv[6], vv[7]};
+      if (W16) {
+        const uint32_t ww[4] = {wq[0].x, wq[0].y, wq[0].z, wq[0].w};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const uint32_t w = ww[2 * half + k];
+          o[2 * half + k] = pack_bf16x2(apply_update_scaled(bf16lo(w), mc[2 * k], inv[2 * k], bound, cf.decay),
+                                        apply_update_scaled(bf16hi(w), mc[2 * k + 1], inv[2 * k + 1], bound, cf.decay));
+        }
+        if (half) buf_store16(rW, ok ? e * 2u : OOB, make_uint4(o[0], o[1], o[2], o[3]));
+      } else {
+        const uint4 wo = wq[W16 ? 0 : half];
+        const uint32_t ww[4] = {wo.x, wo.y, wo.z, wo.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          o[k] = __float_as_uint(apply_update_scaled(__uint_as_float(ww[k]), mc[k], inv[k], bound, cf.decay));
+        buf_store16(rW, ok ? e * 4u + 16u * half : OOB, make_uint4(o[0], o[1], o[2], o[3]));
       }
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) inv[k] = vinv;                    // -lr already folded in
-    }
-    if (W16) {
-      const uint32_t ww[4] = {wq[0].x, wq[0].y, wq[0].z, wq[0].w};
-      uint32_t o[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        o[k] = pack_bf16x2(apply_update_scaled(bf16lo(ww[k]), mc[2 * k], inv[2 * k], bound, cf.decay),
-                           apply_update_scaled(bf16hi(ww[k]), mc[2 * k + 1], inv[2 * k + 1], bound, cf.decay));
-      buf_store16(rW, ok ? e * 2u : OOB, make_uint4(o[0], o[1], o[2], o[3]));
-    } else {
-      const uint32_t ww[8] = {wq[0].x, wq[0].y, wq[0].z, wq[0].w, wq[W16 ? 0 : 1].x, wq[W16 ? 0 : 1].y, wq[W16 ? 0 : 1].z,
-                              wq[W16 ? 0 : 1].w};
-      uint32_t w[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        w[k] = __float_as_uint(apply_update_scaled(__uint_as_float(ww[k]), mc[k], inv[k], bound, cf.decay));
-      buf_store16(rW, ok ? e * 4u : OOB, make_uint4(w[0], w[1], w[2], w[3]));
-      buf_store16(rW, ok ? e * 4u + 16u : OOB, make_uint4(w[4], w[5], w[6], w[7]));
     }
   }
 };
 
-template <int RT, bool W16>
+template <int RT, bool W16, bool VEL>
 __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* __restrict__ items,
                                                                const RuBlockDev* __restrict__ blocks, Bases bs,
                                                                StepScalars sc) {
@@ -1104,7 +1114,7 @@ __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* _
   float* __restrict__ vst = reinterpret_cast<float*>(bs.state + B.off_v);
   lds_u8* const lds = (lds_u8*)smem;
 
-  if (B.v_kind != 0 && tid < BM && row0 + tid < m)
+  if (!VEL && tid < BM && row0 + tid < m)
     vrow[tid] = inv_denom_exact(vst[(row0 + tid) / B.v_group_rows], sc.inv_debias_v, sc.inv_debias_m, sc.eps);
 
   // ------------------------------------------------------------------ a_p L_p -> bf16 (hi, lo) in LDS -> A-fragments
@@ -1233,9 +1243,14 @@ __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* _
     const __amdgpu_buffer_rsrc_t rW = make_rsrc(W + (int64_t)row0 * n * WE, rows_valid * (unsigned)n * WE);
     const int rowa = t512 >> 3, c8 = (t512 & 7) * 8, hh = (t512 >> 2) & 1;
     const unsigned eoff[2] = {(unsigned)(rowa * n + c8), (unsigned)((rowa + 64) * n + c8)};
-    const bool v_elem = B.v_kind == 0;
+    // VEL (every block of the launch has a per-element second moment): its old values are requested one pair of tiles
+    // ahead (two, as G and W, spill).  Read where they are used instead, every tile waited for them:
+    // 24 layers of 1024 and 4096 wide matrices at r = 64 1.09 -> 0.92 ms (4.6 TB/s), 2048 and 5461 wide ones at r = 128
+    // 4.9 -> 4.5 ms; a copy reaches 5.15 TB/s here
+    constexpr int VV = VEL ? 2 : 1;
+    const __amdgpu_buffer_rsrc_t rV = make_rsrc(vst + (VEL ? (int64_t)row0 * n : 0), VEL ? rows_valid * (unsigned)n * 4u : 0u);
     static_assert(D2 == 4, "two pairs of tiles in flight");
-    uint4 gq[2][2], wq[2][2][WV];
+    uint4 gq[2][2], wq[2][2][WV], vq[2][VV];
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -1243,19 +1258,38 @@ __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* _
         gq[u][h] = make_uint4(0, 0, 0, 0);
 #pragma unroll
         for (int k = 0; k < WV; ++k) wq[u][h][k] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int k = 0; k < VV; ++k) vq[h][k] = make_uint4(0, 0, 0, 0);
       }
+    // element offset of vector h in pair s
+    auto at = [&](int h, int s) { return eoff[h] + (unsigned)(s * 64); };
+    // a vector is opened only in the round that finishes it: both rounds of a pair hold the same code, and what they
+    // compute alike would otherwise be done for every lane ahead of the first and kept, in registers that are not there
+    auto fresh = [](uint4 q) {
+      asm volatile("" : "+v"(q.x), "+v"(q.y), "+v"(q.z), "+v"(q.w));
+      return q;
+    };
     auto fetch = [&](int s, uint4 (&g)[2], uint4 (&w)[2][WV]) {     // pair s = tiles 2 s and 2 s + 1
       const bool ok = s * 64 + c8 < n8;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const unsigned e = eoff[h] + (unsigned)(s * 64);
+        const unsigned e = at(h, s);
         g[h] = buf_load16(rG, ok ? e * 2u : OOB);
 #pragma unroll
         for (int k = 0; k < WV; ++k) w[h][k] = buf_load16(rW, ok ? e * WE + 16u * k : OOB);
       }
     };
+    auto fetch_v = [&](int s) {
+      const bool ok = s * 64 + c8 < n8;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const unsigned e = at(h, s);
+#pragma unroll
+        for (int k = 0; k < VV; ++k) vq[h][k] = buf_load16(rV, ok ? e * 4u + 16u * k : OOB);
+      }
+    };
     __syncthreads();
-    const float vinv[2] = {v_elem ? 0.f : vrow[rowa] * cf.neg_lrs, v_elem ? 0.f : vrow[rowa + 64] * cf.neg_lrs};
+    const float vinv[2] = {VEL ? 0.f : vrow[rowa] * cf.neg_lrs, VEL ? 0.f : vrow[rowa + 64] * cf.neg_lrs};
     fetch(0, gq[0], wq[0]);
     __builtin_amdgcn_sched_barrier(0);
     // round jb + u: tail of tile j = jb + u - 2 (pair j / 2, register set (j / 2) % 2) by the lanes that hold its
@@ -1271,14 +1305,22 @@ __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* _
             const bool ok = j >= 0 && s * 64 + c8 < n8 && row0 + row < m;
             const float* ca = reinterpret_cast<const float*>(Cs + ((j & 1) * 2) * C_TILE) + row * CR + (c8 & 31);
             const float* cb = ca + C_TILE / 4;
-            const float4 a0 = *reinterpret_cast<const float4*>(ca), a1 = *reinterpret_cast<const float4*>(ca + 4);
-            const float4 b0 = *reinterpret_cast<const float4*>(cb), b1 = *reinterpret_cast<const float4*>(cb + 4);
-            const float c[8] = {a0.x + b0.x, a0.y + b0.y, a0.z + b0.z, a0.w + b0.w, a1.x + b1.x, a1.y + b1.y, a1.z + b1.z, a1.w + b1.w};
-            const unsigned e = eoff[h] + (unsigned)(s * 64);
-            RuTail<W16>::run(c, gq[su][h], wq[su][h], ok, e, rW, vst + (int64_t)row0 * n + e, v_elem, vinv[h], sc, cf, bound, gs * gs);
+            const unsigned e = at(h, s);
+            uint4 w[WV], v[VV];
+#pragma unroll
+            for (int k = 0; k < WV; ++k) w[k] = wq[su][h][k];
+#pragma unroll
+            for (int k = 0; k < VV; ++k) v[k] = VEL ? fresh(vq[h][k]) : vq[h][k];
+            RuTail<W16, VEL>::run(ca, cb, VEL ? fresh(gq[su][h]) : gq[su][h], w, v, ok, e, rW, rV, vinv[h], sc, cf, bound, gs * gs);
           }
         }
-        if (u & 1) fetch(s + 2, gq[su], wq[su]);
+        if (u & 1) {
+          if (VEL) {
+            fetch_v(s + 1);                                         // ahead of the newer requests: waited for without them
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          fetch(s + 2, gq[su], wq[su]);
+        }
         wg_barrier();
       }
     }
@@ -1290,7 +1332,7 @@ __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* _
       const float g = bf16lo((uint32_t)G[e]);
       const float mc = fmaf(sc.cC, ctail[tid], sc.cG * g);
       float inv;
-      if (B.v_kind == 0) {
+      if (VEL) {
         const float vv = sc.beta2 * vst[e] + (1.f - sc.beta2) * (gs * gs) * g * g;
         vst[e] = vv;
         inv = inv_denom_fast(vv, sc.inv_debias_v, sc.inv_debias_m * cf.neg_lrs, sc.eps);
@@ -1921,18 +1963,22 @@ void launch_qt_image(const ImgItem* items, int64_t nitems, Bases b, hipStream_t 
 }
 
 template <int RT>
-void launch_ru_rt(bool w16, dim3 grid, const ProjItem* items, const RuBlockDev* blocks, Bases b, StepScalars sc, hipStream_t s) {
-  if (w16) hipLaunchKernelGGL((refresh_update_kernel<RT, true>), grid, dim3(NT), 0, s, items, blocks, b, sc);
-  else hipLaunchKernelGGL((refresh_update_kernel<RT, false>), grid, dim3(NT), 0, s, items, blocks, b, sc);
+void launch_ru_rt(bool w16, bool vel, dim3 grid, const ProjItem* items, const RuBlockDev* blocks, Bases b, StepScalars sc,
+                  hipStream_t s) {
+  if (w16 && vel) hipLaunchKernelGGL((refresh_update_kernel<RT, true, true>), grid, dim3(NT), 0, s, items, blocks, b, sc);
+  else if (w16) hipLaunchKernelGGL((refresh_update_kernel<RT, true, false>), grid, dim3(NT), 0, s, items, blocks, b, sc);
+  else if (vel) hipLaunchKernelGGL((refresh_update_kernel<RT, false, true>), grid, dim3(NT), 0, s, items, blocks, b, sc);
+  else hipLaunchKernelGGL((refresh_update_kernel<RT, false, false>), grid, dim3(NT), 0, s, items, blocks, b, sc);
 }
 
-void launch_refresh_update(int rt, bool w16, const ProjItem* items, int64_t nitems, const RuBlockDev* blocks, Bases b,
+// vel: every block of the list keeps a per-element second moment (v_kind 0); otherwise none does
+void launch_refresh_update(int rt, bool w16, bool vel, const ProjItem* items, int64_t nitems, const RuBlockDev* blocks, Bases b,
                            StepScalars sc, hipStream_t s) {
   if (nitems <= 0) return;
   const dim3 grid((unsigned)nitems);
-  if (rt == 1) launch_ru_rt<1>(w16, grid, items, blocks, b, sc, s);
-  else if (rt == 2) launch_ru_rt<2>(w16, grid, items, blocks, b, sc, s);
-  else launch_ru_rt<4>(w16, grid, items, blocks, b, sc, s);
+  if (rt == 1) launch_ru_rt<1>(w16, vel, grid, items, blocks, b, sc, s);
+  else if (rt == 2) launch_ru_rt<2>(w16, vel, grid, items, blocks, b, sc, s);
+  else launch_ru_rt<4>(w16, vel, grid, items, blocks, b, sc, s);
 }
 
 void launch_qf_image(const ImgItem* items, int64_t nitems, Bases b, hipStream_t s) {
