@@ -206,14 +206,13 @@ def main():
             alg = sum(block_bytes(b, False) for b in full_blocks)
             roof = {"bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s", "achieved": alg / (k["avg_ms"] * 1e-3) / 1e9}
         elif label.startswith("alg2_stripe_step"):
-            # one launch = one of the two streaming products of a GD iteration over every block of a rank class
-            # (G R^T or G^T L: 2 m n r flop) and the thin products of the GD step behind it (2 x 2 d r^2, d = m or n)
+            # one launch = the two streaming products of a GD iteration over every block of a rank class (G R^T and
+            # G^T L: 2 m n r flop each, each reading G) and the thin products of the GD step behind them (2 x 2 d r^2, d = m, n)
             rank = int(label.split("_r")[-1])
-            side_L = "_L_" in label
             blocks = [b for b in lr_blocks if rank_class(b) == rank]
-            alg = sum(2.0 * b.rows * b.cols * b.rank + 4.0 * (b.rows if side_L else b.cols) * b.rank ** 2 for b in blocks)
-            issued = sum(2 * 2.0 * b.rows * b.cols * rank + 3 * 4.0 * (b.rows if side_L else b.cols) * rank ** 2 for b in blocks)
-            alg_bytes = sum(b.rows * b.cols * 2 + 12 * (b.rows if side_L else b.cols) * b.rank for b in blocks)
+            alg = sum(4.0 * b.rows * b.cols * b.rank + 4.0 * (b.rows + b.cols) * b.rank ** 2 for b in blocks)
+            issued = sum(2 * 4.0 * b.rows * b.cols * rank + 3 * 4.0 * (b.rows + b.cols) * rank ** 2 for b in blocks)
+            alg_bytes = sum(b.rows * b.cols * 4 + 12 * (b.rows + b.cols) * b.rank for b in blocks)
             sec = k["avg_ms"] * 1e-3
             # arithmetic intensity (about 110 flop per byte at r = 128, 220 as issued) is below the machine balance
             # (2.5 PFLOP/s / 8 TB/s = 312 flop per byte): HBM is the nearer roof; the matrix-core figures ride along

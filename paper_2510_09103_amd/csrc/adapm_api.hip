@@ -131,7 +131,7 @@ struct adapm_ctx {
   DevList<QsItem> qs;
   DevList<StripeProb> sprob;            //   stripe products G R^T and G^T L ...
   std::vector<DevList<ImgItem>> img;    //   ... per GD iteration: fragment images of R and L^T (only the first iteration has any: the stripes write the later ones)
-  std::vector<DevList<StripeItem>> sit; //   ... per GD iteration x rank class: the stripes
+  std::vector<DevList<StripeItem>> sit; //   ... per GD iteration x rank class: the stripes of both products
   std::vector<DevList<GramFinItem>> gfin; //   ... same index as gram: the sums over the segments of the long ones
   std::vector<DevList<GramItem>> gram;  //   ... per GD iteration: the four r x r Gram-type products, from the images, in pairs that share one
   std::vector<DevList<GnormItem>> gnorm; // optional scale-normalised Alg. 2: per (path, GD iteration) the normalisers
@@ -376,8 +376,8 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
   // MFMA path: per GD iteration the images of (R, L^T) and, per rank class, the stripe problems
   constexpr int NXCD = 8;
   struct StripeWork { int prob; int64_t M, K; };
-  std::vector<std::vector<StripeWork>> swork(fast ? 6 * n_eff : 0);   // per GD iteration: (rank class, G / G^T)
-  if (fast) { c->img.resize(img0 + n_eff); c->sit.resize(sit0 + 6 * n_eff); c->gram.resize(gram0 + n_eff); c->gfin.resize(gram0 + n_eff); }
+  std::vector<std::vector<StripeWork>> swork(fast ? 3 * n_eff : 0);   // per GD iteration: rank class
+  if (fast) { c->img.resize(img0 + n_eff); c->sit.resize(sit0 + 3 * n_eff); c->gram.resize(gram0 + n_eff); c->gfin.resize(gram0 + n_eff); }
   auto IMG = [&](int e) -> DevList<ImgItem>& { return c->img[img0 + e]; };
   auto GRAM = [&](int e) -> DevList<GramItem>& { return c->gram[gram0 + e]; };
   // T > 1: the product-preserving orthonormalisation of R follows Alg. 2.  F64 path: inside the group, from the fp64
@@ -460,7 +460,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
         sp.x_cur = Lc.ref; sp.x_prev = Lp.ref; sp.off_b1 = L.wB[0]; sp.off_b2 = L.wB[1]; sp.off_out = Ln.ref.off;
         sp.off_next = iLn; sp.off_timg = -1; sp.off_timg_prev = -1;
         c->sprob.h.push_back(sp);
-        swork[6 * e + 2 * cls].push_back(StripeWork{(int)c->sprob.h.size() - 1, m, n});
+        swork[3 * e + cls].push_back(StripeWork{(int)c->sprob.h.size() - 1, m, n});
         sp.M = n; sp.K = m; sp.transpose_out = 1; sp.off_img = iL;
         sp.v_rows = 0;
         sp.x_cur = Rc.ref; sp.x_prev = Rp.ref; sp.off_b1 = L.wB[2]; sp.off_b2 = L.wB[3]; sp.off_out = Rn.ref.off;
@@ -468,7 +468,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
         sp.off_timg = e + 1 == n_eff ? L.wT2 : -1;     // the last iteration leaves the image of R_t^T for the fused update
         sp.off_timg_prev = (e == 0 && hp.bias_correction) ? L.wT1 : -1;   // ... the first one that of R_{t-1}^T
         c->sprob.h.push_back(sp);
-        swork[6 * e + 2 * cls + 1].push_back(StripeWork{(int)c->sprob.h.size() - 1, n, m});
+        swork[3 * e + cls].push_back(StripeWork{(int)c->sprob.h.size() - 1, n, m});
       } else if (fast) {
         p = problem(m, r); p.A1 = G; p.B1 = T(Rc); p.K1 = n; p.a1 = 1; p.scale_g = 1; p.Out = P; add_problem(A, p);
         p = problem(r, n); p.A1 = T(Lc); p.B1 = G; p.K1 = m; p.a1 = 1; p.scale_g = 1; p.Out = S; add_problem(A, p);
@@ -586,6 +586,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       }
     }
   }
+  // both products of an iteration share a launch (see stripe_kernel);
   // stripes of one problem go to one XCD (workgroup i runs on XCD i mod 8) so that they share the image
   // through its L2; longest contraction first, problems dealt to the least loaded XCD
   for (size_t w = 0; w < swork.size(); ++w) {
@@ -622,10 +623,9 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
     if (hp.refresh_normalise) seq.push_back(Op{OP_GNORM, gnorm0 + e, 0, 0, "alg2_step_normaliser"});
     if (stripes) {
       // both streaming products of the iteration and, behind each stripe, the GD step on the factor rows it covers
-      static const char* names[6] = {"alg2_stripe_step_L_r32", "alg2_stripe_step_R_r32", "alg2_stripe_step_L_r64",
-                                     "alg2_stripe_step_R_r64", "alg2_stripe_step_L_r128", "alg2_stripe_step_R_r128"};
-      for (int k = 0; k < 6; ++k)
-        if (!c->sit[sit0 + 6 * e + k].h.empty()) seq.push_back(Op{OP_STRIPE, sit0 + 6 * e + k, 0, 0, names[k]});
+      static const char* names[3] = {"alg2_stripe_step_r32", "alg2_stripe_step_r64", "alg2_stripe_step_r128"};
+      for (int k = 0; k < 3; ++k)
+        if (!c->sit[sit0 + 3 * e + k].h.empty()) seq.push_back(Op{OP_STRIPE, sit0 + 3 * e + k, 0, 0, names[k]});
     }
     if (!c->gemms[listB[e]].tiles.empty())
       seq.push_back(Op{gk, listB[e], 0, 0, fast ? "alg2_update_mfma" : "alg2_update_f64"});
@@ -1278,7 +1278,7 @@ adapm_status_t run_op(adapm_ctx* c, const Op& op, Bases& bs, const StepScalars& 
       launch_qf_image(c->img[op.index].d, (int64_t)c->img[op.index].h.size(), bs, s);
       break;
     case OP_STRIPE:
-      launch_stripe(1 << ((op.index % 6) >> 1), (op.index & 1) != 0, c->sit[op.index].d, (int64_t)c->sit[op.index].h.size(), c->sprob.d, bs, s);
+      launch_stripe(1 << (op.index % 3), c->sit[op.index].d, (int64_t)c->sit[op.index].h.size(), c->sprob.d, bs, s);
       break;
     case OP_UPDATE_GROUPED:
       launch_update_grouped(c->blocks.d, c->grp.d, (int64_t)c->grp.h.size(), bs, sc, s);

@@ -294,7 +294,7 @@ void launch_proj_keep(const ProjItem* items, int64_t nitems, const LrBlockDev* l
 int proj_keep_rows();
 int proj_keep_max_cols();
 void launch_qimage(const QsItem* items, int64_t nitems, const LrBlockDev* lrb, Bases b, hipStream_t s);
-void launch_stripe(int rt, bool tra, const StripeItem* items, int64_t nitems, const StripeProb* probs, Bases b, hipStream_t s);
+void launch_stripe(int rt, const StripeItem* items, int64_t nitems, const StripeProb* probs, Bases b, hipStream_t s);
 void launch_qf_image(const ImgItem* items, int64_t nitems, Bases b, hipStream_t s);
 void launch_gram(const GramItem* items, int64_t nitems, Bases b, hipStream_t s);
 void launch_gram_finish(const GramFinItem* items, int64_t nitems, Bases b, hipStream_t s);

@@ -286,7 +286,8 @@ __device__ __forceinline__ void stripe_pass1_x2(unsigned char* smem, const Strip
   constexpr int PS = TRA ? 32 * RT + 1 : Pass1x2<RT>::PS;   // row stride of P (see stripe_kernel)
   static_assert(BK * TS * 2 <= G_TILE, "a transposed-read tile fits the tile buffer");
   constexpr int TPW = RT;                                 // 8 row tiles x RT rank tiles over 8 waves
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool mrole = wave < 8;
   const int mw = wave & 7, t512 = tid & 511, l32 = lane & 31, lh = lane >> 5;
@@ -312,7 +313,7 @@ __device__ __forceinline__ void stripe_pass1_x2(unsigned char* smem, const Strip
       // across the end of a row takes the next row's first columns for columns the stripe does not have (their results
       // are dropped); behind the last row the range ends, with the last whole dword (see stripe_kernel)
       const int left = src.K - c * BK, rows = left < BK ? left : BK;
-      const __amdgpu_buffer_rsrc_t rc = make_rsrc(src.base + (int64_t)c * BK * src.ld,
+      const __amdgpu_buffer_rsrc_t rc = make_rsrc_uniform(src.base + (int64_t)c * BK * src.ld,
                                                   rows > 0 ? (unsigned)(((int64_t)(rows - 1) * src.ld + (left > BK ? src.width + 7 : src.width & ~1)) * 2) : 0u);
       const bool ok = tj < src.width;
 #pragma unroll
@@ -470,11 +471,10 @@ __device__ __forceinline__ void stripe_pass1_x2(unsigned char* smem, const Strip
       // offsets: a slot outside the piece of X reads zeros or a neighbouring element of X, and is masked when staged
       const bool vec = tl.sa == 1 && (tl.r & 3) == 0 && (tl.sj & 3) == 0;
       const unsigned xbytes = (unsigned)(((int64_t)(tl.rows - 1) * tl.sj + (int64_t)(tl.r - 1) * tl.sa + 1) * 4);
-      const __amdgpu_buffer_rsrc_t rXc = make_rsrc(tl.xc, xbytes), rXp = make_rsrc(tl.xp, xbytes);
-      const unsigned sj4 = (unsigned)tl.sj * 4u, sa4 = (unsigned)tl.sa * 4u;
+            const unsigned sj4 = (unsigned)tl.sj * 4u, sa4 = (unsigned)tl.sa * 4u;
       float raw[4][8];
       auto fetch_x = [&](int q) {
-        const __amdgpu_buffer_rsrc_t rX = q < nk2 ? rXc : rXp;
+        const __amdgpu_buffer_rsrc_t rX = make_rsrc_uniform(q < nk2 ? tl.xc : tl.xp, xbytes);
         const unsigned k0 = (unsigned)((q < nk2 ? q : q - nk2) * BK + c8);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1364,30 +1364,32 @@ __global__ __launch_bounds__(256) void qt_image_kernel(const ImgItem* __restrict
 // TRA: the stripes of a transposed_out problem are 256 columns of its matrix A^T (K x M, row-major: the gradient
 // itself where A = G^T), read with transposing LDS reads instead of from a transposed copy.
 template <int RT, bool TRA>
-__global__ __launch_bounds__(NT, 1) void stripe_kernel(const StripeItem* __restrict__ items,
-                                                       const StripeProb* __restrict__ probs, Bases bs) {
+struct StripeLds {
   // row stride of P in LDS: with the transposed store the lanes of a wave walk down a column of P, which an odd
   // stride spreads over all banks
-  constexpr int R = 32 * RT, PS = TRA ? R + 1 : Pass1x2<RT>::PS, ROWS = Pass1x2<RT>::ROWS;
-  constexpr int TAIL = (ROWS + R) * 8 * 4;            // beside P: the last columns of A and Q where rows are not whole vectors
-  constexpr int P_END = ROWS * PS * 4;
-  constexpr int SMEM = Pass1x2<RT>::BYTES > P_END + TAIL ? Pass1x2<RT>::BYTES : P_END + TAIL;
+  static constexpr int R = 32 * RT, PS = TRA ? R + 1 : Pass1x2<RT>::PS, ROWS = Pass1x2<RT>::ROWS;
+  static constexpr int TAIL = (ROWS + R) * 8 * 4;     // beside P: the last columns of A and Q where rows are not whole vectors
+  static constexpr int P_END = ROWS * PS * 4;
+  static constexpr int BYTES = Pass1x2<RT>::BYTES > P_END + TAIL ? Pass1x2<RT>::BYTES : P_END + TAIL;
   static_assert(P_END % 16 == 0, "the tail is addressed in vectors");
-  __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
-  const StripeItem item = items[blockIdx.x];
-  if (item.prob < 0) return;
-  const StripeProb P = probs[item.prob];
-  const int M = P.M, K = P.K, row0 = item.row0, tid = threadIdx.x;
+};
+
+// smem: StripeLds<RT, TRA>::BYTES of LDS; rsum: LDS, the sums of squares of the stripe's rows (second moment)
+template <int RT, bool TRA>
+__device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, const StripeItem& item, const StripeProb& P,
+                                            const Bases& bs) {
+  constexpr int R = 32 * RT, PS = StripeLds<RT, TRA>::PS, ROWS = StripeLds<RT, TRA>::ROWS, P_END = StripeLds<RT, TRA>::P_END;
+  const int M = P.M, K = P.K, row0 = item.row0;
+  const int tid = threadIdx.x;
   const uint16_t* __restrict__ A = reinterpret_cast<const uint16_t*>(resolve(P.a, bs));
   const unsigned rows_valid = (unsigned)(M - row0 < ROWS ? M - row0 : ROWS);
   StripeSrc src = {};
   if (TRA) {
     src.base = A + row0; src.ld = M; src.K = K; src.width = (int)rows_valid;
   } else {
-    src.rG = make_rsrc(A + (int64_t)row0 * K, rows_valid * (unsigned)K * 2u);
+    src.rG = make_rsrc_uniform(A + (int64_t)row0 * K, rows_valid * (unsigned)K * 2u);
     src.n = K; src.nv = K & ~7;
   }
-  __shared__ float rsum[ROWS];        // sums of squares of the stripe's rows (second moment)
   const int r = P.r;                  // rows of Q actually present (the image is zero-padded to R)
   float gs = grad_scale(bs);          // global gradient clipping: A is the gradient (or its transpose)
   const float gs2 = gs * gs;
@@ -1608,6 +1610,27 @@ __global__ __launch_bounds__(NT, 1) void stripe_kernel(const StripeItem* __restr
       *reinterpret_cast<uint4*>(dst + 1024) = make_uint4(l[0], l[1], l[2], l[3]);
     }
   }
+}
+
+// Both products of a GD iteration in one launch.  They are independent (the stripes of an iteration read one set of images
+// and write the next, and of the factors only the rows behind themselves).  A workgroup owns a CU and a launch ends with
+// its slowest CU, so half as many launches waste half as many tails, and the two products read G at about the same time.
+// Measured per literal step, two launches -> one: 24 layers of 1024 / 4096 at r = 64 3.11 -> 2.91 ms, 2048 / 5461 at
+// r = 128 14.6 -> 14.1 ms, 48 layers of 1600 / 6400 at r = 128 (launches long enough already) 15.4 -> 15.3 ms.  One wave of
+// each role per SIMD instead of two (256 registers, 4 x 2 tiles per matrix-core wave, fragments requested one k-step
+// ahead: two thirds of the LDS reads) changed nothing: the launch moves 4.3 TB/s of mixed reads and writes, of the 5.0 that a
+// plain read-modify-write stream of this access pattern reaches.
+template <int RT>
+__global__ __launch_bounds__(NT, 1) void stripe_kernel(const StripeItem* __restrict__ items,
+                                                       const StripeProb* __restrict__ probs, Bases bs) {
+  constexpr int L0 = StripeLds<RT, false>::BYTES, L1 = StripeLds<RT, true>::BYTES;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[L0 > L1 ? L0 : L1];
+  __shared__ float rsum[Pass1x2<RT>::ROWS];
+  const StripeItem item = items[blockIdx.x];
+  if (item.prob < 0) return;
+  const StripeProb P = probs[item.prob];
+  if (P.transpose_out) stripe_body<RT, true>(smem, rsum, item, P, bs);
+  else stripe_body<RT, false>(smem, rsum, item, P, bs);
 }
 
 // Fragment image of Q(a, k) = q[a * s0 + k * s1] (fp32, r x K): per 64-column chunk
@@ -1933,18 +1956,12 @@ void launch_proj(int rt, bool w16, bool vel, const ProjItem* items, int64_t nite
   else launch_proj_rt<4>(w16, vel, grid, items, lrb, b, sc, s);
 }
 
-void launch_stripe(int rt, bool tra, const StripeItem* items, int64_t nitems, const StripeProb* probs, Bases b, hipStream_t s) {
+void launch_stripe(int rt, const StripeItem* items, int64_t nitems, const StripeProb* probs, Bases b, hipStream_t s) {
   if (nitems <= 0) return;
   const dim3 grid((unsigned)nitems);
-  if (tra) {
-    if (rt == 1) hipLaunchKernelGGL((stripe_kernel<1, true>), grid, dim3(NT), 0, s, items, probs, b);
-    else if (rt == 2) hipLaunchKernelGGL((stripe_kernel<2, true>), grid, dim3(NT), 0, s, items, probs, b);
-    else hipLaunchKernelGGL((stripe_kernel<4, true>), grid, dim3(NT), 0, s, items, probs, b);
-  } else {
-    if (rt == 1) hipLaunchKernelGGL((stripe_kernel<1, false>), grid, dim3(NT), 0, s, items, probs, b);
-    else if (rt == 2) hipLaunchKernelGGL((stripe_kernel<2, false>), grid, dim3(NT), 0, s, items, probs, b);
-    else hipLaunchKernelGGL((stripe_kernel<4, false>), grid, dim3(NT), 0, s, items, probs, b);
-  }
+  if (rt == 1) hipLaunchKernelGGL((stripe_kernel<1>), grid, dim3(NT), 0, s, items, probs, b);
+  else if (rt == 2) hipLaunchKernelGGL((stripe_kernel<2>), grid, dim3(NT), 0, s, items, probs, b);
+  else hipLaunchKernelGGL((stripe_kernel<4>), grid, dim3(NT), 0, s, items, probs, b);
 }
 
 void launch_gram(const GramItem* items, int64_t nitems, Bases b, hipStream_t s) {

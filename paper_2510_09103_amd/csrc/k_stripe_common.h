@@ -24,6 +24,14 @@ constexpr unsigned OOB = 0x80000000u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
+// The same for a base and a size that are uniform over the wave without the compiler seeing it (values that went through a
+// kernel of two large bodies): kept in scalar registers, or every access becomes a loop over the distinct descriptors.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_uniform(const void* base, unsigned bytes) {
+  const uint64_t a = (uint64_t)base;
+  const uint64_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a);
+  const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32));
+  return make_rsrc((const void*)(hi << 32 | lo), (unsigned)__builtin_amdgcn_readfirstlane((int)bytes));
+}
 __device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, unsigned off) {
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
   return make_uint4(v.x, v.y, v.z, v.w);
