@@ -226,12 +226,16 @@ def main():
                             "flops of the mathematical products; mfma.issued = matrix-core work with every fp32 "
                             "operand as a (hi, lo) bf16 pair (2 instructions per product of G, 3 per thin product) "
                             "at the padded rank class"}
-        elif label in ("project_f64", "reconstruct_f64", "alg2_gram_f64", "alg2_update_f64"):
-            # exact path: batched fp64 products on the matrix cores.  project: G Q^T; reconstruct: the m x n term of
-            # the update from the thin factors; Alg. 2, per GD iteration: the r x r Gram matrices, and G R^T, L^T G with the
+        elif label == "update_lowrank_f64":
+            # exact path: the m x n term from the thin factors inside the update; G, W, v and the factors it reads
+            size = {"bf16": 2, "f32": 4}
+            alg = sum(b.rows * b.cols * (size[b.grad_dtype] + 2 * size[b.param_dtype] + (8 if b.v_mode == "element" else 0)) +
+                      4 * (b.rows + b.cols) * b.rank * (2 if refresh_step else 1) for b in lr_blocks)
+            roof = {"bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s", "achieved": alg / (k["avg_ms"] * 1e-3) / 1e9}
+        elif label in ("project_f64", "alg2_gram_f64", "alg2_update_f64"):
+            # exact path: batched fp64 products on the matrix cores.  project: G Q^T; Alg. 2, per GD iteration: the r x r Gram matrices, and G R^T, L^T G with the
             # thin products of the factor updates behind them
             per_block = {"project_f64": lambda b: 2.0 * b.rows * b.cols * b.rank,
-                         "reconstruct_f64": lambda b: 2.0 * b.rows * b.cols * b.rank,
                          "alg2_gram_f64": lambda b: 4.0 * (b.rows + b.cols) * b.rank ** 2,
                          "alg2_update_f64": lambda b: 4.0 * b.rows * b.cols * b.rank + 4.0 * (b.rows + b.cols) * b.rank ** 2}[label]
             alg = sum(per_block(b) for b in lr_blocks)

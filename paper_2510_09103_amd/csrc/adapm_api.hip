@@ -55,7 +55,7 @@ struct Layout {                      // byte offsets, -1 = absent
   int64_t sL = -1, sR = -1, sm = -1, sv = -1;               // state
   int64_t wLa = -1, wRa = -1, wLb = -1, wRb = -1;           // ws: ping-pong factors of Alg. 2
   int64_t wP = -1, wS = -1, wGrr = -1, wGpr = -1, wGll = -1, wGlp = -1;
-  int64_t wG64 = -1, wCinv = -1, wC = -1;
+  int64_t wG64 = -1, wCinv = -1;
   int64_t wQf = -1, wTimg = -1;                             // ws: bf16 (hi, lo) images of Q and Q^T
   int64_t wIr = -1, wIl = -1;                               // ws: the fragment images of R, L^T during Alg. 2 ...
   int64_t wIr2 = -1, wIl2 = -1;                             // ws: ... written by the stripes of one GD iteration for the next, hence two sets
@@ -69,7 +69,7 @@ struct Layout {                      // byte offsets, -1 = absent
   bool stripes = false;                                     // MFMA path: the products of Alg. 2 run as stripes (choose_stripes)
 };
 
-enum OpKind { OP_GEMM, OP_GEMM_MFMA, OP_CHOL, OP_VSTAT, OP_VFINAL, OP_UPDATE, OP_QSPLIT, OP_PROJ, OP_QFIMG, OP_STRIPE, OP_QTIMG, OP_REFRESH_UPDATE, OP_GRADNORM, OP_GRAM, OP_GNORM, OP_UPDATE_GROUPED, OP_COPY, OP_PROJ_KEEP, OP_GRAM_FIN, OP_REGAUGE_APPLY };
+enum OpKind { OP_GEMM, OP_GEMM_MFMA, OP_CHOL, OP_VSTAT, OP_VFINAL, OP_UPDATE, OP_QSPLIT, OP_PROJ, OP_QFIMG, OP_STRIPE, OP_QTIMG, OP_REFRESH_UPDATE, OP_GRADNORM, OP_GRAM, OP_GNORM, OP_UPDATE_GROUPED, OP_COPY, OP_PROJ_KEEP, OP_GRAM_FIN, OP_REGAUGE_APPLY, OP_UPDATE64 };
 
 struct GemmList {
   std::vector<GemmProblem> probs;
@@ -82,7 +82,7 @@ struct GemmList {
 struct Op {
   OpKind kind;
   int index;          // GEMM*: gemm list; UPDATE / VSTAT / VFINAL / PROJ / QFIMG / STRIPE / ...: which item list
-  float cG, cC;       // UPDATE of low-rank blocks, PROJ
+  float cG, cC;       // updates of low-rank blocks
   const char* label;  // profiling name
   int aux = 0;        // REFRESH_UPDATE: which list of block descriptors the items index
 };
@@ -118,7 +118,7 @@ struct adapm_ctx {
   float grad_clip = 0.f;                           // threshold of the global gradient-norm clipping; <= 0: off
 
   DevList<BlockDev> blocks;
-  std::vector<DevList<EwItem>> ew;   // 0: full / no momentum; then one per group of low-rank blocks on the F64 path (the MFMA path updates in its fused kernels)
+  DevList<EwItem> ew;           // full / no momentum (low-rank blocks are updated where their m x n term is built)
   DevList<VsItem> vs[2];        // 0: every step; 1: only on steps that run Alg. 2 (fused elsewhere)
   DevList<VfItem> vf[2];
   DevList<GrpItem> grp;         // full / no momentum blocks whose v groups fit a wavefront: statistic + update fused
@@ -293,7 +293,16 @@ GemmProblem problem(int M, int N) {
   p.M = M; p.N = N;
   p.layout = G64_KK; p.tm = p.tn = 2;
   p.off_s = -1;
+  p.s0 = 1.0;
+  p.Out2 = none_mat();
   return p;
+}
+
+// The update of one block on the exact path: the problem's products are the m x n term, its result is the block itself
+void add_update64(GemmList& gl, GemmProblem p, int32_t block) {
+  p.Out = mat(SP_PARAM, block, 0, p.N, 1, DT_F32);
+  p.tm = p.tn = UPD64_TILE / 16;
+  add_problem(gl, p);
 }
 
 // most segments a Gram-type product over K columns is cut into (sizes the partial sums; a group may use fewer, longer ones)
@@ -362,8 +371,6 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
   c->ru.resize(c->ru.size() + 12);
   const int ru0 = 12 * grp;
   const int img0 = (int)c->img.size(), sit0 = (int)c->sit.size(), gram0 = (int)c->gram.size();
-  const int ew_id = fast ? -1 : (int)c->ew.size();
-  if (!fast) c->ew.emplace_back();
   auto new_list = [&](bool mfma) {
     c->gemms.emplace_back();
     c->gemms.back().mfma = mfma;
@@ -542,8 +549,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
         if (!(L.stripes && n_eff > 0)) c->qt[grp].h.push_back(ImgItem{Rc, r, n, ch, d.rc, L.wT2});   // else: written by the stripes
       }
     } else {
-      // m x n low-rank term of m^c (eq. 4): C = L'R' - L R, or L R without the correction
-      const Mat C = mat(SP_WS, 0, L.wC, n, 1, DT_F32);
+      // m x n low-rank term of m^c (eq. 4), L'R' - L R, or L R without the correction: built inside the update
       p = problem(m, n);
       if (hp.bias_correction) {
         p.A1 = Lp; p.B1 = Rp; p.K1 = r; p.a1 = 1.0;
@@ -551,10 +557,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       } else {
         p.A1 = Lc; p.B1 = Rc; p.K1 = r; p.a1 = 1.0;
       }
-      p.Out = C;
-      add_problem(c->gemms[l_epi], shape64(p, G64_KJ));
-      for (int64_t s0 = 0; s0 < (int64_t)m * n; s0 += EW_CHUNK)
-        c->ew[ew_id].h.push_back(EwItem{s0, (int32_t)i, (int32_t)std::min<int64_t>(EW_CHUNK, (int64_t)m * n - s0)});
+      add_update64(c->gemms[l_epi], p, (int32_t)i);
     }
     if (fast && hp.refresh_period_T > 1) {
       // the pass over all blocks that follows the last group: Gram matrix of the stored R in fp64, Cholesky, in place
@@ -667,8 +670,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       seq.push_back(Op{OP_REFRESH_UPDATE, ru0 + cls, cG, cC, names[(cls >> 1) % 3], grp});
     }
   } else {
-    seq.push_back(Op{gk, l_epi, 0, 0, "reconstruct_f64"});
-    seq.push_back(Op{OP_UPDATE, ew_id, cG, cC, "update_lowrank"});
+    seq.push_back(Op{OP_UPDATE64, l_epi, cG, cC, "update_lowrank_f64"});
   }
   if (l_gram >= 0) {
     seq.push_back(Op{OP_GEMM, l_gram, 0, 0, "regauge_gram_f64"});
@@ -681,14 +683,14 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
   if (fast && !c->cp[grp].h.empty()) seq.push_back(Op{OP_COPY, grp, 0, 0, "store_factors"});
 }
 
-// step with R held, F64 path: four batched GEMM launches and the update kernel
-// `ids`: one group of blocks (the scratch of a group is reused by the next); ew_id: the group's element-wise list
-void plan_lowrank_project_f64(adapm_ctx* c, const std::vector<int64_t>& ids, int ew_id) {
+// step with R held, F64 path: the projection with both factors that follow from it, then the update
+// `ids`: one group of blocks (the scratch of a group is reused by the next)
+void plan_lowrank_project_f64(adapm_ctx* c, const std::vector<int64_t>& ids) {
   const adapm_hparams_t& hp = c->hp;
   const double b1 = hp.beta1;
   if (ids.empty()) return;
   auto new_list = [&]() { c->gemms.emplace_back(); return (int)c->gemms.size() - 1; };
-  const int l_p = new_list(), l_d = new_list(), l_l = new_list(), l_c = new_list();
+  const int l_p = new_list(), l_c = new_list();
   for (int64_t i : ids) {
     const adapm_block_t& b = c->table[i];
     const Layout& L = c->lay[i];
@@ -697,23 +699,18 @@ void plan_lowrank_project_f64(adapm_ctx* c, const std::vector<int64_t>& ids, int
     const Mat G = mat(SP_GRAD, (int32_t)i, 0, n, 1, gdt);
     const Mat Ls = mat(SP_STATE, 0, L.sL, r, 1, DT_F32), Q = mat(SP_STATE, 0, L.sR, n, 1, DT_F32);
     Mat Qt = Q; Qt.s0 = Q.s1; Qt.s1 = Q.s0;
-    const Mat P = mat(SP_WS, 0, L.wP, r, 1, DT_F64), D = mat(SP_WS, 0, L.wLa, r, 1, DT_F64);
-    const Mat C = mat(SP_WS, 0, L.wC, n, 1, DT_F32);
+    const Mat D = mat(SP_WS, 0, L.wLa, r, 1, DT_F64);
     GemmProblem p;
-    p = problem(m, r); p.A1 = G; p.B1 = Qt; p.K1 = n; p.a1 = 1.0; p.scale_g = 1; p.Out = P; add_problem(c->gemms[l_p], shape64(p, G64_KK));
     // L_t = b1 L' + (1-b1) G Q^T;  m^c = G + b1 (L' - G Q^T) Q   (or L_t Q without the correction)
-    p = problem(m, r); p.X = Ls; p.Y = P; p.Out = D;
-    if (hp.bias_correction) { p.g = b1; p.d = -b1; } else { p.g = b1; p.d = 1.0 - b1; }
-    add_problem(c->gemms[l_d], p);
-    p = problem(m, r); p.X = Ls; p.g = b1; p.Y = P; p.d = 1.0 - b1; p.Out = Ls; add_problem(c->gemms[l_l], p);
-    p = problem(m, n); p.A1 = D; p.B1 = Q; p.K1 = r; p.a1 = 1.0; p.Out = C; add_problem(c->gemms[l_c], shape64(p, G64_KJ));
+    p = problem(m, r); p.A1 = G; p.B1 = Qt; p.K1 = n; p.a1 = 1.0; p.scale_g = 1; p.X = Ls;
+    p.Out = D; p.g = b1; p.s0 = hp.bias_correction ? -b1 : 1.0 - b1;
+    p.Out2 = Ls; p.g2 = b1; p.s2 = 1.0 - b1;
+    add_problem(c->gemms[l_p], shape64(p, G64_KK));
+    p = problem(m, n); p.A1 = D; p.B1 = Q; p.K1 = r; p.a1 = 1.0; add_update64(c->gemms[l_c], p, (int32_t)i);
   }
   std::vector<Op>& seq = c->seq_project;
   seq.push_back(Op{OP_GEMM, l_p, 0, 0, "project_f64"});
-  seq.push_back(Op{OP_GEMM, l_d, 0, 0, "project_residual_f64"});
-  seq.push_back(Op{OP_GEMM, l_l, 0, 0, "project_store_L_f64"});
-  seq.push_back(Op{OP_GEMM, l_c, 0, 0, "reconstruct_f64"});
-  seq.push_back(Op{OP_UPDATE, ew_id, hp.bias_correction ? 1.f : 0.f, 1.f, "update_lowrank"});
+  seq.push_back(Op{OP_UPDATE64, l_c, hp.bias_correction ? 1.f : 0.f, 1.f, "update_lowrank_f64"});
 }
 
 // step with R held, MFMA path: Q^T split once, then one fused launch per rank class.  Stripes of one
@@ -805,8 +802,8 @@ size_t layout_block_scratch(const adapm_block_t& b, const adapm_hparams_t& hp, L
   // the second working copy of the factors: only where the GD step runs as batched GEMMs (see plan_lowrank_refresh)
   if (!stripes) { T.wLb = walloc(es * m * r); T.wRb = walloc(es * r * n); }
   // G R^T and L^T G: blocks whose GD step rides on the stripe products never store them
-  if (!stripes) T.wP = walloc(es * m * r);
-  if (fast && !stripes) T.wS = walloc(es * r * n);       // the exact path adds L^T G to the factor in place
+  if (fast && !stripes) T.wP = walloc(es * m * r);          // the exact path adds both to the factors in place
+  if (fast && !stripes) T.wS = walloc(es * r * n);
   T.wGrr = walloc(es * r * r); T.wGpr = walloc(es * r * r);
   T.wGll = walloc(es * r * r); T.wGlp = walloc(es * r * r);
   if (hp.refresh_period_T > 1 && !fast) { T.wG64 = walloc(8 * r * r); T.wCinv = walloc(8 * r * r); }
@@ -814,8 +811,6 @@ size_t layout_block_scratch(const adapm_block_t& b, const adapm_hparams_t& hp, L
   if (fast) {
     T.wT1 = walloc(proj_timg_bytes(rank_class((int)r), (int)n));
     T.wT2 = walloc(proj_timg_bytes(rank_class((int)r), (int)n));
-  } else {
-    T.wC = walloc(4 * m * n);
   }
   if (stripes) {
     T.wIr = walloc(proj_qf_bytes(rank_class((int)r), (int)n));
@@ -949,8 +944,6 @@ void build_plan(adapm_ctx* c) {
       ws_images += align_up(proj_qf_bytes(rank_class(b.rank), (int)b.cols)) + align_up(proj_timg_bytes(rank_class(b.rank), (int)b.cols));
   }
   const bool fits_static = choose_stripes(c, ws_global + 3 * ALIGN + (any_f64 ? ws_images : 0));
-  c->ew.clear();
-  c->ew.emplace_back();          // list 0: full / no momentum blocks
 
   // device block table, element-wise chunks, v statistics
   int64_t npart = 0;
@@ -960,7 +953,7 @@ void build_plan(adapm_ctx* c) {
     BlockDev d;
     d.numel = b.rows * b.cols;
     d.group_elems = group_elems(b);
-    d.off_m = L.sm; d.off_v = L.sv; d.off_C = -1;      // off_C: set when the block's group is laid out
+    d.off_m = L.sm; d.off_v = L.sv;
     d.param_dtype = b.param_dtype; d.grad_dtype = b.grad_dtype;
     d.mom_mode = b.mom_mode; d.v_mode = b.v_mode;
     d.lr_scale = b.lr_scale; d.wd = b.weight_decay;
@@ -978,7 +971,7 @@ void build_plan(adapm_ctx* c) {
     // the MFMA path)
     if (L.path == PATH_NONE) {
       for (int64_t s = 0; s < d.numel; s += EW_CHUNK)
-        c->ew[0].h.push_back(EwItem{s, (int32_t)i, (int32_t)std::min<int64_t>(EW_CHUNK, d.numel - s)});
+        c->ew.h.push_back(EwItem{s, (int32_t)i, (int32_t)std::min<int64_t>(EW_CHUNK, d.numel - s)});
     }
     if (b.v_mode != ADAPM_V_ELEMENT) {
       // on the MFMA path with T > 1 the fused kernel finishes fusable groups itself on steps with R held (list 1: only
@@ -1044,7 +1037,7 @@ void build_plan(adapm_ctx* c) {
       if (!c->vs[1].h.empty()) seq.push_back(Op{OP_VSTAT, 1, 0, 0, "v_statistics"});
       if (!c->vf[1].h.empty()) seq.push_back(Op{OP_VFINAL, 1, 0, 0, "v_statistics_fold"});
     }
-    if (!c->ew[0].h.empty()) seq.push_back(Op{OP_UPDATE, 0, 0, 0, "update_full"});
+    if (!c->ew.h.empty()) seq.push_back(Op{OP_UPDATE, 0, 0, 0, "update_full"});
     if (!c->grp.h.empty()) seq.push_back(Op{OP_UPDATE_GROUPED, 0, 0, 0, "update_full_grouped"});
   }
   c->ws_bytes = images_end;
@@ -1065,12 +1058,10 @@ void build_plan(adapm_ctx* c) {
       size_t at = persistent;
       for (int64_t i : ids) {
         at = layout_block_scratch(c->table[i], hp, c->lay[i], at, false);
-        c->blocks.h[i].off_C = c->lay[i].wC;
       }
       scratch_max = std::max(scratch_max, at - persistent);
-      const int ew_before = (int)c->ew.size();
       plan_lowrank_refresh(c, path == PATH_FAST, ids);
-      if (hp.refresh_period_T > 1 && path == PATH_F64) plan_lowrank_project_f64(c, ids, ew_before);
+      if (hp.refresh_period_T > 1 && path == PATH_F64) plan_lowrank_project_f64(c, ids);
     }
   }
   c->ws_bytes = std::max(images_end, persistent + scratch_max);
@@ -1118,14 +1109,13 @@ adapm_status_t ensure_uploaded(adapm_ctx* c) {
   HIP_TRY(hipGetDevice(&dev));
   const size_t nb = c->table.size();
   size_t total = bytes_of(c->blocks.h) + bytes_of(c->sk.h) + bytes_of(c->lrb.h) + bytes_of(c->qs.h) + bytes_of(c->proj_keep.h) +
-                 bytes_of(c->sprob.h) + bytes_of(c->gn.h) + bytes_of(c->grp.h) + bytes_of(c->rg_apply.h) +
+                 bytes_of(c->sprob.h) + bytes_of(c->gn.h) + bytes_of(c->grp.h) + bytes_of(c->rg_apply.h) + bytes_of(c->ew.h) +
                  adapm_ctx::NSLOT * align_up(2 * nb * sizeof(void*));
   for (auto& l : c->cp) total += bytes_of(l.h);
   for (auto& l : c->rub) total += bytes_of(l.h);
   for (auto& l : c->qt) total += bytes_of(l.h);
   for (auto& l : c->ru) total += bytes_of(l.h);
   for (auto& l : c->chol) total += bytes_of(l.h);
-  for (auto& l : c->ew) total += bytes_of(l.h);
   for (auto& l : c->img) total += bytes_of(l.h);
   for (auto& l : c->sit) total += bytes_of(l.h);
   for (auto& l : c->gram) total += bytes_of(l.h);
@@ -1144,13 +1134,12 @@ adapm_status_t ensure_uploaded(adapm_ctx* c) {
     return dst;
   };
 #define PUT_LIST(L) (L).d = (decltype((L).d))put((L).h.data(), (L).h.size() * sizeof((L).h[0]))
-  PUT_LIST(c->blocks); PUT_LIST(c->sk); PUT_LIST(c->lrb); PUT_LIST(c->qs); PUT_LIST(c->proj_keep); PUT_LIST(c->sprob); PUT_LIST(c->gn); PUT_LIST(c->grp); PUT_LIST(c->rg_apply);
+  PUT_LIST(c->blocks); PUT_LIST(c->sk); PUT_LIST(c->lrb); PUT_LIST(c->qs); PUT_LIST(c->proj_keep); PUT_LIST(c->sprob); PUT_LIST(c->gn); PUT_LIST(c->grp); PUT_LIST(c->rg_apply); PUT_LIST(c->ew);
   for (auto& l : c->cp) PUT_LIST(l);
   for (auto& l : c->rub) PUT_LIST(l);
   for (auto& l : c->qt) PUT_LIST(l);
   for (auto& l : c->ru) PUT_LIST(l);
   for (auto& l : c->chol) PUT_LIST(l);
-  for (auto& l : c->ew) PUT_LIST(l);
   for (auto& l : c->img) PUT_LIST(l);
   for (auto& l : c->sit) PUT_LIST(l);
   for (auto& l : c->gram) PUT_LIST(l);
@@ -1248,15 +1237,19 @@ adapm_status_t run_op(adapm_ctx* c, const Op& op, Bases& bs, const StepScalars& 
     case OP_VFINAL:
       launch_vfinal(c->blocks.d, c->vf[op.index].d, (int64_t)c->vf[op.index].h.size(), partials, bs, sc.beta2, s);
       break;
-    case OP_UPDATE: {
-      StepScalars x = sc;
-      x.cG = op.cG; x.cC = op.cC;
-      launch_update(c->blocks.d, c->ew[op.index].d, (int64_t)c->ew[op.index].h.size(), bs, x, s);
+    case OP_UPDATE:
+      launch_update(c->blocks.d, c->ew.d, (int64_t)c->ew.h.size(), bs, sc, s);
       break;
-    }
     case OP_GEMM: {
       const GemmList& g = c->gemms[op.index];
       launch_gemm64(g.d_probs, g.d_tiles, (int64_t)g.tiles.size(), bs, s);
+      break;
+    }
+    case OP_UPDATE64: {
+      StepScalars x = sc;
+      x.cG = op.cG; x.cC = op.cC;
+      const GemmList& g = c->gemms[op.index];
+      launch_update64(g.d_probs, g.d_tiles, (int64_t)g.tiles.size(), c->blocks.d, bs, x, s);
       break;
     }
     case OP_GEMM_MFMA: {

@@ -73,7 +73,11 @@ struct GemmProblem {
   double a1, a2, a3, g, d;
   int32_t scale_g;   // 1: the first product has the gradient as an operand and takes the clipping factor
   int32_t tri;       // fp64 kernel: 1 = A1 is lower triangular, 2 = B1 is lower triangular (zero part of the contraction skipped)
-  int64_t off_s;     // >= 0: workspace offset of the device scalar s (double); -1: s = 1
+  int64_t off_s;     // >= 0: workspace offset of the device scalar s (double); -1: s = s0
+  double s0;
+  // fp64 kernel, optional second result of the same sums: Out2 = g2 X + s2 (...); may be X itself
+  Mat Out2;
+  double g2, s2;
 };
 
 struct GemmTile {
@@ -89,7 +93,6 @@ struct BlockDev {
   int64_t group_elems;   // elements sharing one v (1 for per-element v)
   int64_t off_m;         // state byte offset of m (full momentum) or -1
   int64_t off_v;         // state byte offset of v
-  int64_t off_C;         // workspace byte offset of the m x n low-rank term, or -1
   int32_t param_dtype, grad_dtype, mom_mode, v_mode;
   float lr_scale, wd;
 };
@@ -278,6 +281,10 @@ void launch_gram_norm(const GnormItem* items, int64_t nitems, Bases b, hipStream
 void launch_update_grouped(const BlockDev* blocks, const GrpItem* items, int64_t nitems, Bases b, StepScalars sc,
                            hipStream_t s);
 void launch_gradnorm_final(const double* partials, int64_t nparts, float max_norm, float* out, hipStream_t s);
+// update of the low-rank blocks of the exact path (k_update64.hip): 64 x 64 tiles of problems whose sums are the m x n term
+constexpr int UPD64_TILE = 64;
+void launch_update64(const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, const BlockDev* blocks, Bases b,
+                     StepScalars sc, hipStream_t s);
 void launch_update(const BlockDev* blocks, const EwItem* items, int64_t nitems, Bases b, StepScalars sc,
                    hipStream_t s);
 void launch_fill_zero(void* p, size_t bytes, hipStream_t s);

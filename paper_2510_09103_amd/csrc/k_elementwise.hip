@@ -5,9 +5,9 @@
 //    blockwise mean of Sec. 5.1.3).  A group is a contiguous run of elements (whole rows),
 //    reduced by one wavefront with DPP-style shuffles; long groups go through fixed-order
 //    partial sums (deterministic, no float atomics).
-//  - update: m <- (1-beta1) G + beta1 m (eq. 5) or m^c = cG G + cC C for low-rank blocks
-//    (eq. 4 rewritten as m^c = G + beta1/(1-beta1) (L_{t-1}R_{t-1} - L_t R_t)), per-element v,
-//    then W <- W - lr (clip(m^c / (sqrt(v) + eps)) + lambda W)  (Alg. 1 last line).
+//  - update of full / no momentum blocks: m <- (1-beta1) G + beta1 m (eq. 5) or m^c = G, per-element v,
+//    then W <- W - lr (clip(m^c / (sqrt(v) + eps)) + lambda W)  (Alg. 1 last line).  Low-rank blocks are updated where
+//    their m x n term is built (k_update64.hip, k_proj_mfma.hip).
 #include "adapm_plan.h"
 #include "ew_math.h"
 
@@ -256,7 +256,6 @@ __global__ __launch_bounds__(256) void update_kernel(const BlockDev* __restrict_
   char* W = (char*)b.params[item.block];
   float* m = blk.off_m >= 0 ? reinterpret_cast<float*>(b.state + blk.off_m) : nullptr;
   float* v = reinterpret_cast<float*>(b.state + blk.off_v);
-  const float* C = blk.off_C >= 0 ? reinterpret_cast<const float*>(b.ws + blk.off_C) : nullptr;
   const UpdCoef cf = make_coef(sc.lr, blk.lr_scale, blk.wd, sc.clip);
   const float ob1 = 1.f - sc.beta1, ob2 = 1.f - sc.beta2;
   const float gs = grad_scale(b);                 // global clipping: the method sees gs * G
@@ -306,10 +305,6 @@ __global__ __launch_bounds__(256) void update_kernel(const BlockDev* __restrict_
 #pragma unroll
         for (int k = 0; k < 8; ++k) mc[k] = ob1 * g[k] + sc.beta1 * mc[k];
         store8((char*)m, DT_F32, e, mc);
-      } else if (blk.mom_mode == MM_LOWRANK) {  // low-rank: m^c = cG G + cC C
-        load8((const char*)C, DT_F32, e, mc);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) mc[k] = sc.cG * g[k] + sc.cC * mc[k];
       } else {
 #pragma unroll
         for (int k = 0; k < 8; ++k) mc[k] = g[k];
@@ -332,7 +327,6 @@ __global__ __launch_bounds__(256) void update_kernel(const BlockDev* __restrict_
         }
         float mc;
         if (blk.mom_mode == MM_FULL) { mc = ob1 * g + sc.beta1 * m[i]; m[i] = mc; }
-        else if (blk.mom_mode == MM_LOWRANK) mc = sc.cG * g + sc.cC * C[i];
         else mc = g;
         store1(W, blk.param_dtype, i,
                apply_update(w, mc, inv_denom_fast(vv, sc.inv_debias_v, sc.inv_debias_m, sc.eps), cf));

@@ -1,5 +1,5 @@
 // fp64 batched GEMM on the fp64 matrix cores (the "F64" contraction mode and the re-expression of the factors):
-//   Out = g X + s (a1 A1 B1 + a2 A2 B2 + a3 A3 B3 + d Y)
+//   Out = g X + s (a1 A1 B1 + a2 A2 B2 + a3 A3 B3 + d Y),   optionally a second combination of X and the same sums
 // One launch covers a list of output tiles drawn from many independent problems, so every thin product of Alg. 2 of every
 // low-rank block runs in two launches per iteration (the r x r Gram matrices, then both factor updates with their
 // products with G).  Operands (bf16 / fp32 / fp64) convert exactly to fp64; all sums run in fp64 in a fixed order.
@@ -127,7 +127,8 @@ __device__ __forceinline__ void tile_body(const GemmProblem& P, const GemmTile& 
   const char* Yb = P.Y.ref.space != SP_NONE ? resolve(P.Y.ref, bs) : nullptr;
   char* Ob = resolve(P.Out.ref, bs);
   // optional device scalar on everything but X (normalised step of Alg. 2)
-  const double step_scale = P.off_s >= 0 ? *reinterpret_cast<const double*>(bs.ws + P.off_s) : 1.0;
+  const double step_scale = P.off_s >= 0 ? *reinterpret_cast<const double*>(bs.ws + P.off_s) : P.s0;
+  char* Ob2 = P.Out2.ref.space != SP_NONE ? resolve(P.Out2.ref, bs) : nullptr;
 #pragma unroll
   for (int e = 0; e < NR / NW; ++e) {
     const int reg = e * NW + wave, q = reg & 3, b = (reg >> 2) % TN, a = (reg >> 2) / TN;
@@ -139,11 +140,22 @@ __device__ __forceinline__ void tile_body(const GemmProblem& P, const GemmTile& 
     const int j = LAY == G64_KK ? j0 + 16 * b + l16 : j0 + TN * l16 + b;
     if (i >= P.M || j >= P.N) continue;
     if (Yb) val = fma(P.d, load_el(Yb, P.Y.dtype, (int64_t)i * P.Y.s0 + (int64_t)j * P.Y.s1), val);
+    // the step with R held takes both D = b1 (L' - P) and L_t from one P = G R^T (three launches 62 + 19 + 13 -> 66 us)
+    double val2 = P.s2 * val;
     val *= step_scale;
-    if (Xb) val = fma(P.g, load_el(Xb, P.X.dtype, (int64_t)i * P.X.s0 + (int64_t)j * P.X.s1), val);
+    if (Xb) {
+      const double x = load_el(Xb, P.X.dtype, (int64_t)i * P.X.s0 + (int64_t)j * P.X.s1);
+      val = fma(P.g, x, val);
+      val2 = fma(P.g2, x, val2);
+    }
     const int64_t o = (int64_t)i * P.Out.s0 + (int64_t)j * P.Out.s1;
     if (P.Out.dtype == DT_F64) reinterpret_cast<double*>(Ob)[o] = val;
     else reinterpret_cast<float*>(Ob)[o] = (float)val;
+    if (Ob2) {
+      const int64_t o2 = (int64_t)i * P.Out2.s0 + (int64_t)j * P.Out2.s1;
+      if (P.Out2.dtype == DT_F64) reinterpret_cast<double*>(Ob2)[o2] = val2;
+      else reinterpret_cast<float*>(Ob2)[o2] = (float)val2;
+    }
   }
 }
 

@@ -158,6 +158,18 @@ def test_exact_path_at_the_edges_of_its_tiles(gd, many, T):
     run(exact_edges_table(gd, many), 4, dict(T=T), tol_state=TOL32, tol_param=TOL32)
 
 
+@pytest.mark.parametrize("pd,gd,vm,clip", [("f32", "bf16", "element", None), ("bf16", "f32", "rowgroup", 0.5), ("bf16", "bf16", "element", None),
+                                           ("f32", "f32", "whole", None)])
+@pytest.mark.parametrize("hp", [dict(T=1), dict(T=3), dict(T=2, bias_correction=0), dict(T=2, K=1)])
+def test_update_of_the_exact_path_at_the_edges_of_its_tiles(pd, gd, vm, clip, hp):
+    """Tiles of 64 x 64 with four columns per lane and steps of 16 along the rank: rows of 2 and 3 columns, one column beside
+    a multiple of 4 and 64, rows beside a multiple of 16 and 64, ranks beside a multiple of 4 and 16; both types of G and W."""
+    sizes = [(2, 2, 2), (5, 3, 3), (15, 4, 4), (16, 5, 1), (17, 63, 15), (63, 64, 16), (64, 65, 17), (65, 66, 5), (130, 131, 33)]
+    wl = WL.Workload("update64_edges", tuple(BlockSpec(f"b{m}x{n}_r{r}", m, n, pd, gd, "lowrank", r, vm, 1, 1.0, 0.1)
+                                             for m, n, r in sizes), steps=4, seed=41, signal_rank=24)
+    run(wl, 4, dict(hp, contraction=B.ADAPM_CONTRACT_F64), tol_state=TOL32, tol_param=TOL32, grad_clip=clip)
+
+
 def odd_rank_table():
     """bf16 blocks whose rank is not 32, 64 or 128 (the paper takes r = 5 % of the smaller dimension): the
     MFMA kernels run them in the next rank class with zero-padded images of the factors.  Ranks that are
