@@ -442,17 +442,17 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
         // row a, column k = B[k][a] with B = R' R^T, R R^T for L and B = (L^T L')^T, L^T L for R^T
         // a contraction longer than the group's segment length is cut into segments (one workgroup each, partial sums added
         // in segment order by a second small launch): the longest workgroup of a launch then stays short
-        auto add_gram = [&](int64_t off_x, int64_t off_s, int64_t o_xs, int64_t o_ss, int64_t i_xs, int64_t i_ss, int K, int tx,
-                            int64_t off_part) {
+        auto add_gram = [&](int64_t off_x, int64_t off_s, int64_t o_ss, int64_t i_xs, int64_t i_ss, int K, int64_t off_part) {
           const int nch = (K + 63) / 64, nseg = (nch + gram_seg - 1) / gram_seg, per = (nch + nseg - 1) / nseg;
+          if (!hp.refresh_normalise) o_ss = -1;          // the GD step multiplies by the images; only the normaliser reads fp32
           for (int sg = 0; sg < nseg; ++sg)
-            GRAM(e).h.push_back(GramItem{off_x, off_s, o_xs, o_ss, i_xs, i_ss, K, r, rc, tx, sg * per, std::min(nch, (sg + 1) * per),
+            GRAM(e).h.push_back(GramItem{off_x, off_s, o_ss, i_xs, i_ss, K, r, rc, sg * per, std::min(nch, (sg + 1) * per),
                                          sg, nseg, off_part});
           if (nseg > 1)
-            c->gfin[gram0 + e].h.push_back(GramFinItem{off_part, o_xs, o_ss, i_xs, i_ss, r, rc, tx, nseg, off_x == off_s ? 1 : 0, 0});
+            c->gfin[gram0 + e].h.push_back(GramFinItem{off_part, o_ss, i_xs, i_ss, r, rc, nseg, off_x == off_s ? 1 : 0});
         };
-        add_gram(L.wIr0, iR, L.wGpr, L.wGrr, L.wB[1], L.wB[0], n, 0, L.wGpn);   // R' R^T and R R^T
-        add_gram(L.wIl0, iL, L.wGlp, L.wGll, L.wB[3], L.wB[2], m, 1, L.wGpm);   // (L'^T L)^T = L^T L' and L^T L
+        add_gram(L.wIr0, iR, L.wGrr, L.wB[1], L.wB[0], n, L.wGpn);   // R' R^T and R R^T
+        add_gram(L.wIl0, iL, L.wGll, L.wB[3], L.wB[2], m, L.wGpm);   // L'^T L = (L^T L')^T and L^T L
         // the GD step rides on the stripes: L_new = L + s (-eta L (R R^T) + eta b1 L' (R' R^T) + eta (1-b1) G R^T) on the
         // rows of a stripe of G, R_new likewise on the columns of R behind a stripe of G^T.  The r x r matrices enter
         // as images with row a, column k = B[k][a]: (R R^T)^T and (R' R^T)^T for L; L^T L and L^T L' for R^T.
@@ -804,8 +804,8 @@ size_t layout_block_scratch(const adapm_block_t& b, const adapm_hparams_t& hp, L
   // G R^T and L^T G: blocks whose GD step rides on the stripe products never store them
   if (fast && !stripes) T.wP = walloc(es * m * r);          // the exact path adds both to the factors in place
   if (fast && !stripes) T.wS = walloc(es * r * n);
-  T.wGrr = walloc(es * r * r); T.wGpr = walloc(es * r * r);
-  T.wGll = walloc(es * r * r); T.wGlp = walloc(es * r * r);
+  if (!stripes || hp.refresh_normalise) { T.wGrr = walloc(es * r * r); T.wGll = walloc(es * r * r); }
+  if (!stripes) { T.wGpr = walloc(es * r * r); T.wGlp = walloc(es * r * r); }
   if (hp.refresh_period_T > 1 && !fast) { T.wG64 = walloc(8 * r * r); T.wCinv = walloc(8 * r * r); }
   T.wNu = walloc(8);
   if (fast) {

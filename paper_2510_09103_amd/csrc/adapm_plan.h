@@ -191,12 +191,12 @@ struct ImgItem {           // one workgroup: one 64-column chunk of the fragment
   int32_t r, K, c, rc;     // rows of Q, columns, chunk, rank class of the image (rows r .. rc-1 are zero)
   int64_t off_img;
 };
-struct GramItem {          // one workgroup: Out_xs = X S^T (stored transposed if transpose_xs) and Out_ss = S S^T, both r x r
-  int64_t off_x, off_s;    // with row stride r, from the fragment images of X, S (r x K); workspace: images (rank class rc)
-  int64_t off_out_xs, off_out_ss;   // workspace: fp32
+struct GramItem {          // one workgroup: X S^T and S S^T, both r x r, from the fragment images of X, S (r x K);
+  int64_t off_x, off_s;    // workspace: images (rank class rc)
+  int64_t off_out_ss;      // workspace: S S^T as fp32 with row stride r; < 0: not wanted
   int64_t off_img_xs, off_img_ss;   // workspace: fragment images of the two results as the GD step on the stripes reads them
-                                    // (image row a, column k = result[k][a]; S S^T is symmetric up to rounding); < 0: none
-  int32_t K, r, rc, transpose_xs;
+                                    // (image row a, column k = result[k][a]; S S^T is symmetric up to rounding); X = S: only the second
+  int32_t K, r, rc;
   // A long contraction is cut into segments of 64-column chunks, one workgroup each: segment [c0, c1) of nseg; with
   // nseg > 1 the workgroup only leaves its partial sums (two R x R fp32 matrices, S S^T then X S^T) at workspace
   // offset off_part + seg * 2 R^2 floats, and gram_finish_kernel adds them in segment order and writes the results.
@@ -205,9 +205,9 @@ struct GramItem {          // one workgroup: Out_xs = X S^T (stored transposed i
 };
 struct GramFinItem {       // one workgroup: the sum of the nseg partial results of one pair of products -> results and images
   int64_t off_part;
-  int64_t off_out_xs, off_out_ss;
+  int64_t off_out_ss;
   int64_t off_img_xs, off_img_ss;
-  int32_t r, rc, transpose_xs, nseg, same, pad;   // same: X = S (first GD iteration), one product serves both outputs
+  int32_t r, rc, nseg, same;   // same: X = S (first GD iteration), one product serves both
 };
 struct CopyItem {          // one workgroup: count floats from src + first to dst + first (first is a multiple of 4)
   Ref src, dst;

@@ -1683,8 +1683,7 @@ __global__ __launch_bounds__(256) void qf_image_kernel(const ImgItem* __restrict
 // (chunks c0 .. c1 - 1): a segment leaves its partial sums for gram_finish_kernel.
 template <int RT>
 __device__ __forceinline__ void gram_emit(const float* Mss, const float* Mxs, const Bases& bs, int64_t off_out_ss,
-                                          int64_t off_out_xs, int64_t off_img_ss, int64_t off_img_xs, int r,
-                                          int transpose_xs, int nthreads);
+                                          int64_t off_img_ss, int64_t off_img_xs, int r, bool same, int nthreads);
 
 template <int RT>
 __device__ __forceinline__ void gram_body(const GramItem& it, const Bases& bs, unsigned char* smem) {
@@ -1833,28 +1832,23 @@ __device__ __forceinline__ void gram_body(const GramItem& it, const Bases& bs, u
         }
   }
   __syncthreads();
-  gram_emit<RT>(Mss, Mxs, bs, it.off_out_ss, it.off_out_xs, it.off_img_ss, it.off_img_xs, it.r, it.transpose_xs, 512);
+  gram_emit<RT>(Mss, Mxs, bs, it.off_out_ss, it.off_img_ss, it.off_img_xs, it.r, same, 512);
 }
 
-// Results of a pair of Gram-type products, complete in LDS as [R][R] fp32 each: the r x r matrices themselves and
-// their fragment images for the GD step on the stripes (the layout qf_image_kernel writes), 64-wide chunks of the
+// Results of a pair of Gram-type products, complete in LDS as [R][R] fp32 each: S S^T itself where somebody reads it (the
+// normaliser of the step; nobody reads X S^T) and the fragment images of both for the GD step on the stripes (the layout qf_image_kernel writes), 64-wide chunks of the
 // contraction index k: lane l of a piece holds result[64 c + 16 kk + 8 (l / 32) .. + 7][32 tile + l % 32].
 template <int RT>
 __device__ __forceinline__ void gram_emit(const float* Mss, const float* Mxs, const Bases& bs, int64_t off_out_ss,
-                                          int64_t off_out_xs, int64_t off_img_ss, int64_t off_img_xs, int r,
-                                          int transpose_xs, int nthreads) {
+                                          int64_t off_img_ss, int64_t off_img_xs, int r, bool same, int nthreads) {
   constexpr int R = 32 * RT;
   constexpr int QF = qf_chunk_bytes(R);
-  float* __restrict__ Oss = reinterpret_cast<float*>(bs.ws + off_out_ss);
-  float* __restrict__ Oxs = reinterpret_cast<float*>(bs.ws + off_out_xs);
-  for (int id = threadIdx.x; id < r * r; id += nthreads) {
-    const int row = id / r, col = id % r;
-    Oss[id] = Mss[row * R + col];
-    Oxs[id] = transpose_xs ? Mxs[col * R + row] : Mxs[row * R + col];      // the transposition is an LDS read: stores stay contiguous
+  if (off_out_ss >= 0) {
+    float* __restrict__ Oss = reinterpret_cast<float*>(bs.ws + off_out_ss);
+    for (int id = threadIdx.x; id < r * r; id += nthreads) Oss[id] = Mss[(id / r) * R + id % r];
   }
-  if (off_img_ss < 0) return;
   const int nk2 = (r + BK - 1) / BK;
-  for (int p = threadIdx.x; p < 2 * nk2 * (BK / 16) * RT * 64; p += nthreads) {
+  for (int p = threadIdx.x; p < (same ? 1 : 2) * nk2 * (BK / 16) * RT * 64; p += nthreads) {   // same: one image serves both
     const int ln = p & 63, rest = p >> 6, tile = rest % RT, kk = (rest / RT) % (BK / 16), kc = (rest / (RT * (BK / 16))) % nk2;
     const int which = rest / (RT * (BK / 16) * nk2);
     const float* M = (which ? Mxs : Mss) + 32 * tile + (ln & 31);
@@ -1921,7 +1915,7 @@ __device__ __forceinline__ void gram_finish_body(const GramFinItem& it, const Ba
     }
   }
   __syncthreads();
-  gram_emit<RT>(Mss, Mxs, bs, it.off_out_ss, it.off_out_xs, it.off_img_ss, it.off_img_xs, it.r, it.transpose_xs, 512);
+  gram_emit<RT>(Mss, Mxs, bs, it.off_out_ss, it.off_img_ss, it.off_img_xs, it.r, it.same != 0, 512);
 }
 
 __global__ __launch_bounds__(512) void gram_finish_kernel(const GramFinItem* __restrict__ items, Bases bs) {
