@@ -7,7 +7,7 @@
 // A Gram matrix that is not positive definite in fp64 (a pivot that is zero, negative or not finite: R has lost
 // rank, e.g. factors that are exactly zero) has no such factorisation; the kernel then writes C = C^-1 = I, so that
 // the block's (L, R) pass through the re-expression unchanged instead of turning into NaN.
-#include "adapm_plan.h"
+#include "k_f64_common.h"
 
 namespace adapm {
 
@@ -106,96 +106,121 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(const CholItem* __restric
   }
 }
 
-// R <- C^-1 R on 64 whole columns, or L <- L C on 64 whole rows, in place (fp64 products, fp32 stores): the r x 64
-// result Out[a][j] = sum_k M[k][a] T[k][j] with T the tile of the factor (contraction index k = row of R / column of
-// L) and M[k][a] = C^-1[a][k] (for R) or C[k][a] (for L).  The whole tile goes to LDS first (fp32, as stored), so the
-// workgroup may overwrite its columns / rows afterwards; M is staged 32 values of k at a time (fp64).  A thread owns
-// two 4 x 4 pieces of the result: per k one 16-byte read of T and two of M feed 16 multiply-adds.  Entries of the
-// triangular matrices outside the triangle are exact zeros; a thread skips the slabs of k that lie wholly outside
-// its piece's part of the triangle.
-constexpr int RG_W = 64;                 // columns of R / rows of L per workgroup
-constexpr int RG_K = 32;                 // values of the contraction index per staged slab of M
-constexpr int RG_MS = 128 + 2;           // LDS row stride of M (doubles): rows stay 16-byte aligned
-__global__ __launch_bounds__(256) void regauge_apply_kernel(const RegaugeItem* __restrict__ items, Bases b) {
-  __shared__ __attribute__((aligned(16))) float T[128 * RG_W];        // T[k][j]
-  __shared__ __attribute__((aligned(16))) double Ms[RG_K * RG_MS];    // Ms[kk][a] = M[k0 + kk][a], zero for a >= r
-  const RegaugeItem it = items[blockIdx.x];
-  const int r = it.r, tid = threadIdx.x;
+// R <- C^-1 R on 64 whole columns, or L <- L C on 64 whole rows, in place (fp64 products on the matrix cores, fp32 stores).
+// A wave owns 16 columns of R (rows of L) with all r results of each, so it overwrites nothing that another wave reads: it
+// requests its whole share of the factor first, then walks the contraction in steps of 16 and takes the triangular matrix
+// straight from the caches (k_f64_common.h for the lane layouts), whose 16 x 16 (L: 16 x 32) tiles outside the triangle are skipped.
+// Bound by those cache reads, 66 KB per wave at r = 128, and by the fp64 rate (25 GFLOP, 0.35 ms of the table below).  Against
+// 4 x 4 pieces per thread on the vector units with the matrix staged through LDS: 288 matrices of 1600 / 6400 at r = 128
+// 2.38 -> 1.05 ms.
+// One body per number of 16-wide steps, RG_T = ceil(r / 16), without branches from the first matrix instruction to the last:
+// a result must not be read until 19 wait states after the instruction that writes it, which the compiler fills in along
+// straight code but not, here, along every path of branches that skip steps (such a form left the last rows of a tile stale).
+template <int RG_T>
+__device__ __forceinline__ void regauge_body(const RegaugeItem& it, const Bases& b) {
+  const int r = it.r, len = it.len;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int u0 = it.first + 16 * wave;
+  if (u0 >= len) return;
   float* X = reinterpret_cast<float*>(b.state + it.off_x);
   const double* __restrict__ Cm = reinterpret_cast<const double*>(b.ws + it.off_c);
-  const int width = it.len - it.first < RG_W ? it.len - it.first : RG_W;
-  const bool isL = it.is_L != 0;
-  if (!isL) {
-    for (int e = tid; e < r * RG_W; e += 256) {
-      const int k = e / RG_W, j = e % RG_W;
-      T[e] = j < width ? X[(int64_t)k * it.len + it.first + j] : 0.f;
+  const int u = u0 + l16, uc = u < len ? u : len - 1;     // lanes past the end repeat the last column / row and store nothing
+  // x[s][v] = element k = 16 s + 4 kq + v of this lane's column of R / row of L, zero past the rank
+  float x[RG_T][4];
+#pragma unroll
+  for (int s = 0; s < RG_T; ++s) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[s][v] = 0.f;
+    const int k = 16 * s + 4 * kq;
+    if (it.is_L && s + 1 < RG_T) {
+      const f32x4_a4 q = *reinterpret_cast<const f32x4_a4*>(X + (int64_t)uc * r + k);
+      x[s][0] = q.x; x[s][1] = q.y; x[s][2] = q.z; x[s][3] = q.w;
+    } else {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (s + 1 < RG_T || k + v < r) x[s][v] = X[it.is_L ? (int64_t)uc * r + k + v : (int64_t)(k + v) * len + uc];
+    }
+  }
+  f64x4 acc[RG_T + 1];
+#pragma unroll
+  for (int t = 0; t <= RG_T; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+  if (!it.is_L) {
+    // result row a = sum over k <= a of C^-1[a][k] R[k][u]
+#pragma unroll
+    for (int s = 0; s < RG_T; ++s) {
+      const int k = 16 * s + 4 * kq;
+#pragma unroll
+      for (int t = s; t < RG_T; ++t) {
+        const double* row = Cm + (int64_t)(16 * t + l16 < r ? 16 * t + l16 : r - 1) * r;
+        RawVec<DT_F64, 4> m;
+        if (s + 1 < RG_T) m.load((const char*)(row + k));
+        else {                               // x is zero past the rank: any finite element will do
+#pragma unroll
+          for (int v = 0; v < 4; ++v) m.r[v] = row[k + v < r ? k + v : r - 1];
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[t] = mfma_f64(m.r[v], (double)x[s][v], acc[t]);
+      }
+    }
+    if (u < len) {
+#pragma unroll
+      for (int t = 0; t < RG_T; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int a = 16 * t + 4 * q + kq;
+          if (a < r) X[(int64_t)a * len + u] = (float)acc[t][q];
+        }
     }
   } else {
-    for (int e = tid; e < r * RG_W; e += 256) {
-      const int j = e / r, k = e % r;                 // row j of the 64, column k of L: contiguous in memory along k
-      T[k * RG_W + j] = j < width ? X[(int64_t)(it.first + j) * r + k] : 0.f;
-    }
-  }
-  // this thread's two pieces: values a0 .. a0+3 of the free index, positions j0 .. j0+3.  R: consecutive lanes walk
-  // along j (their stores are contiguous along a row of R); L: along a (contiguous along a row of L).
-  int a0[2], j0[2];
+    // result column a = sum over k >= a of L[u][k] C[k][a]; tiles 2 p, 2 p + 1 interleave the columns 32 p .. + 31
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int q = tid + 256 * u;
-    a0[u] = 4 * (isL ? q % 32 : q / 16);
-    j0[u] = 4 * (isL ? q / 32 : q % 16);
-  }
-  double acc[2][4][4];
+    for (int s = 0; s < RG_T; ++s) {
+      const int k = 16 * s + 4 * kq;
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
+      for (int p = 0; p <= s / 2; ++p) {
+        const int a = 32 * p + 2 * l16;
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-      for (int y = 0; y < 4; ++y) acc[u][x][y] = 0.0;
-  for (int k0 = 0; k0 < r; k0 += RG_K) {
-    __syncthreads();                                  // the tile is in LDS / the previous slab has been used
-    for (int e = tid; e < RG_K * 128; e += 256) {
-      int kk, a;
-      if (isL) { kk = e / 128; a = e % 128; } else { a = e / RG_K; kk = e % RG_K; }   // contiguous in memory either way
-      const int k = k0 + kk;
-      double v = 0.0;
-      if (k < r && a < r) v = isL ? Cm[(int64_t)k * r + a] : Cm[(int64_t)a * r + k];
-      Ms[kk * RG_MS + a] = v;
-    }
-    __syncthreads();
-    const int kn = r - k0 < RG_K ? r - k0 : RG_K;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      // R: M[k][a] != 0 only for k <= a; L: only for k >= a
-      const bool live = a0[u] < r && (isL ? k0 + RG_K > a0[u] : k0 <= a0[u] + 3);
-      if (!live) continue;
-      for (int kk = 0; kk < kn; ++kk) {
-        const float4 t4 = *reinterpret_cast<const float4*>(&T[(k0 + kk) * RG_W + j0[u]]);
-        const double2 m01 = *reinterpret_cast<const double2*>(&Ms[kk * RG_MS + a0[u]]);
-        const double2 m23 = *reinterpret_cast<const double2*>(&Ms[kk * RG_MS + a0[u] + 2]);
-        const double tv[4] = {(double)t4.x, (double)t4.y, (double)t4.z, (double)t4.w};
-        const double mv[4] = {m01.x, m01.y, m23.x, m23.y};
-#pragma unroll
-        for (int x = 0; x < 4; ++x)
-#pragma unroll
-          for (int y = 0; y < 4; ++y) acc[u][x][y] = fma(mv[x], tv[y], acc[u][x][y]);
+        for (int v = 0; v < 4; ++v) {
+          const double* row = Cm + (int64_t)(k + v < r ? k + v : r - 1) * r;
+          double c0, c1;
+          if (2 * p + 2 < RG_T) {
+            const f64x2_a8 q = *reinterpret_cast<const f64x2_a8*>(row + a);
+            c0 = q.x; c1 = q.y;
+          } else {
+            c0 = row[a < r ? a : r - 1];     // columns past the rank are computed and dropped
+            c1 = row[a + 1 < r ? a + 1 : r - 1];
+          }
+          const double xv = (double)x[s][v];
+          acc[2 * p] = mfma_f64(xv, c0, acc[2 * p]);
+          acc[2 * p + 1] = mfma_f64(xv, c1, acc[2 * p + 1]);
+        }
       }
     }
-  }
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
+    for (int p = 0; p < (RG_T + 1) / 2; ++p)
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const int a = a0[u] + x;
-      if (a >= r) continue;
-#pragma unroll
-      for (int y = 0; y < 4; ++y) {
-        const int j = j0[u] + y;
-        if (j >= width) continue;
-        if (isL) X[(int64_t)(it.first + j) * r + a] = (float)acc[u][x][y];
-        else X[(int64_t)a * it.len + it.first + j] = (float)acc[u][x][y];
+      for (int q = 0; q < 4; ++q) {
+        const int j = u0 + 4 * q + kq, a = 32 * p + 2 * l16;
+        if (j >= len || a >= r) continue;
+        float* o = X + (int64_t)j * r + a;
+        if (a + 1 < r) *reinterpret_cast<f32x2_a4*>(o) = f32x2_a4{(float)acc[2 * p][q], (float)acc[2 * p + 1][q]};
+        else *o = (float)acc[2 * p][q];
       }
-    }
+  }
+}
+
+__global__ __launch_bounds__(256) void regauge_apply_kernel(const RegaugeItem* __restrict__ items, Bases b) {
+  const RegaugeItem it = items[blockIdx.x];
+  switch ((it.r + 15) / 16) {
+    case 1: regauge_body<1>(it, b); break;
+    case 2: regauge_body<2>(it, b); break;
+    case 3: regauge_body<3>(it, b); break;
+    case 4: regauge_body<4>(it, b); break;
+    case 5: regauge_body<5>(it, b); break;
+    case 6: regauge_body<6>(it, b); break;
+    case 7: regauge_body<7>(it, b); break;
+    default: regauge_body<8>(it, b); break;     // r <= 128
   }
 }
 

@@ -1,5 +1,5 @@
-// Building blocks shared by the fp64 kernels of the exact contraction path (k_gemm64.hip, k_step64.hip): the fp64 matrix
-// instruction, and operands that go from memory straight into its registers.
+// Building blocks shared by the fp64 kernels of the exact contraction path (k_gemm64.hip, k_update64.hip) and of the
+// re-expression of R (k_chol.hip): the fp64 matrix instruction, and operands that go from memory straight into its registers.
 //
 // v_mfma_f64_16x16x4_f64: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16]; result register q of lane l is
 // D[4 q + l / 16][l % 16].  One instruction is 64 cycles of a SIMD whatever the dependence on the previous one (measured:

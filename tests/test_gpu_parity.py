@@ -191,6 +191,27 @@ def test_ranks_between_the_classes_on_the_mfma_path(hp):
     run(odd_rank_table(), 6, hp, tol_state=TOL16, tol_param=TOL16, check_every=2)
 
 
+@pytest.mark.parametrize("ranks", [(1, 15, 16, 17, 31, 33), (47, 49, 64, 65, 80), (81, 93, 96, 97, 112), (113, 127, 128)])
+def test_orthonormalisation_for_every_number_of_rank_steps(ranks):
+    """R <- C^-1 R and L <- L C run in one body per number of 16-wide steps of the rank: first, last and middle ranks of each,
+    columns and rows beside a multiple of 16 and 64.  Rows of R orthonormal to fp32 rounding (the sum of n products of values
+    rounded to 2^-24, n |R_ik R_jk| <= 1 by Cauchy-Schwarz, on either side: 2 * 2^-24, times 4), and the product L R that of
+    the same step without it (each factor rounded once more, r-term sums: 1e-6 in the 2-norm)."""
+    blocks = [BlockSpec(f"r{r}", 145 + i, 208 + 13 * i, "bf16", "bf16", "lowrank", r, "rowgroup", 1, 1.0, 0.1) for i, r in enumerate(ranks)]
+    got = {}
+    for T in (1, 3):
+        pair = Pair(WL.Workload("regauge", tuple(blocks), steps=1, seed=51, signal_rank=24),
+                    dict(T=T, contraction=B.ADAPM_CONTRACT_BF16X2))
+        pair.step()
+        torch.cuda.synchronize()
+        got[T] = [{k: v.double().cpu() for k, v in pair.opt.state_view(i).items()} for i in range(len(blocks))]
+    for b, plain, ortho in zip(blocks, got[1], got[3]):
+        eye = torch.eye(b.rank, dtype=torch.float64)
+        assert float((ortho["R"] @ ortho["R"].T - eye).abs().max()) <= 8 * 2.0 ** -24, b.name
+        want = plain["L"] @ plain["R"]
+        assert float((ortho["L"] @ ortho["R"] - want).norm()) <= 1e-6 * float(want.norm()), b.name
+
+
 def random_table(rng, case):
     """A few low-rank bf16-gradient blocks with random sizes (mostly multiples of 8, which Alg. 2 takes as stripe
     products with the GD step riding on them; otherwise any size), ranks on and between the class and vector
