@@ -170,6 +170,7 @@ struct adapm_ctx {
   bool gauge_ok = false;                // T > 1: the state's R has orthonormal rows (a step that ran Alg. 2, or adapm_state_loaded)
   int64_t last_launches = 0;
   int n_lowrank = 0;
+  int n_eff = 0;                        // iterations of Alg. 2 whose step size is not zero
   const void* split_ws = nullptr;       // workspace that holds valid bf16 copies of Q (T > 1, MFMA path) ...
   const void* split_state = nullptr;    // ... made from the R of this state buffer
   std::vector<std::pair<std::string, std::pair<double, int64_t>>> prof_agg;   // folded timings (adapm_profile_read)
@@ -786,7 +787,6 @@ void plan_lowrank_project_fast(adapm_ctx* c) {
   }
 }
 
-// Lay out state / workspace and build every work list.
 // Scratch of one low-rank block while its group runs Alg. 2 (and, on the F64 path, a step with R held): laid out
 // from `base` on; returns the end.  dry = true only measures.
 size_t layout_block_scratch(const adapm_block_t& b, const adapm_hparams_t& hp, Layout& L, size_t base, bool dry) {
@@ -827,28 +827,74 @@ size_t layout_block_scratch(const adapm_block_t& b, const adapm_hparams_t& hp, L
   return wo;
 }
 
-// Scratch that a group of low-rank blocks may take: a margin below the state size, at least 32 MiB and the largest block
-size_t scratch_budget(const adapm_ctx* c, size_t persistent) {
-  size_t largest = 0;
+// Scratch of block i in a plan.  stored: with every intermediate of Alg. 2 in memory (both products with G, all four r x r
+// matrices, the m x n term of the exact path), whether or not the kernels of today keep it on chip.
+size_t block_scratch(const adapm_ctx* c, size_t i, bool stored) {
+  const adapm_block_t& b = c->table[i];
+  Layout L = c->lay[i];
+  if (L.path == PATH_NONE) return 0;
+  size_t need = layout_block_scratch(b, c->hp, L, 0, true);
+  if (!stored) return need;
+  const size_t m = b.rows, n = b.cols, r = b.rank;
+  if (L.path == PATH_F64) need += align_up(8 * m * r) + align_up(8 * r * n) + align_up(4 * m * n);
+  if (L.stripes) need += (c->hp.refresh_normalise ? 2 : 4) * align_up(4 * r * r);
+  return need;
+}
+
+// The first GD iteration of Alg. 2 finishes block i's blockwise second moment: no statistic of its own on such steps
+bool v_in_stripes(const adapm_ctx* c, size_t i) {
+  const adapm_block_t& b = c->table[i];
+  return c->lay[i].stripes && v_fusable(b) && c->n_eff > 0;
+}
+// Partial sums of block i's blockwise second moment (groups longer than a wavefront's piece)
+int64_t v_partials(const adapm_ctx* c, size_t i) {
+  const adapm_block_t& b = c->table[i];
+  const int64_t ge = group_elems(b);
+  if (b.v_mode == ADAPM_V_ELEMENT || ge <= VS_CHUNK || v_in_stripes(c, i)) return 0;
+  return c->lay[i].nv * ((ge + VS_CHUNK - 1) / VS_CHUNK);
+}
+static_assert(GRP_MAX_ELEMS <= VS_CHUNK, "groups whose update takes the statistic along have no partial sums");
+
+// The part of the workspace that is not a group's scratch: [matrices of the re-gauge, partial sums | images of the held R]
+struct FixedPart {
+  size_t images_at, images_end;
+  size_t scratch_at;             // where the groups' scratch starts
+};
+FixedPart fixed_part(const adapm_ctx* c) {
+  size_t at = 0, images = 0;
+  int64_t npart = 0, ngn = 0;
+  bool any_f64 = false;
   for (size_t i = 0; i < c->table.size(); ++i) {
-    Layout L = c->lay[i];
-    if (L.path != PATH_NONE) largest = std::max(largest, layout_block_scratch(c->table[i], c->hp, L, 0, true));
+    const adapm_block_t& b = c->table[i];
+    npart += v_partials(c, i);
+    ngn += (b.rows * b.cols + VS_CHUNK - 1) / VS_CHUNK;
+    if (c->lay[i].path == PATH_F64) any_f64 = true;
+    if (c->lay[i].path != PATH_FAST || c->hp.refresh_period_T <= 1) continue;
+    at += 2 * align_up((size_t)8 * b.rank * b.rank);
+    images += align_up(proj_qf_bytes(rank_class(b.rank), (int)b.cols)) + align_up(proj_timg_bytes(rank_class(b.rank), (int)b.cols));
   }
+  if (npart > 0) at += align_up(8 * (size_t)npart);
+  at += align_up(8 * (size_t)ngn) + align_up(8);
+  return FixedPart{at, at + images, any_f64 ? at + images : at};
+}
+
+// Scratch that a group of low-rank blocks may take: a margin below the state size, at least 32 MiB and the largest block
+size_t scratch_budget(const adapm_ctx* c, size_t persistent, bool stored) {
+  size_t largest = 0;
+  for (size_t i = 0; i < c->table.size(); ++i) largest = std::max(largest, block_scratch(c, i, stored));
   const size_t floor_bytes = (size_t)32 << 20;
   const size_t budget = c->state_bytes > persistent + floor_bytes ? c->state_bytes - persistent : floor_bytes;
   return std::max(budget - budget / 16, largest);
 }
 
 // The low-rank blocks of a contraction path in table order, cut into groups of about equal scratch: as few as the budget
-// allows, none above it
-std::vector<std::vector<int64_t>> cut_groups(const adapm_ctx* c, int path, size_t budget) {
+// allows, none above it.  largest: the scratch of the largest group so far.
+std::vector<std::vector<int64_t>> cut_groups(const adapm_ctx* c, int path, size_t budget, bool stored, size_t& largest) {
   std::vector<std::vector<int64_t>> groups;
   std::vector<size_t> need(c->table.size(), 0);
   size_t total = 0;
-  for (size_t i = 0; i < c->table.size(); ++i) {
-    Layout L = c->lay[i];
-    if (L.path == path) total += need[i] = layout_block_scratch(c->table[i], c->hp, L, 0, true);
-  }
+  for (size_t i = 0; i < c->table.size(); ++i)
+    if (c->lay[i].path == path) total += need[i] = block_scratch(c, i, stored);
   const size_t n_groups = (total + budget - 1) / budget;
   const size_t target = n_groups ? (total + n_groups - 1) / n_groups : 0;
   size_t used = 0;
@@ -857,8 +903,18 @@ std::vector<std::vector<int64_t>> cut_groups(const adapm_ctx* c, int path, size_
     if (groups.empty() || used + need[i] > budget || used >= target) { groups.emplace_back(); used = 0; }
     groups.back().push_back((int64_t)i);
     used += need[i];
+    largest = std::max(largest, used);
   }
   return groups;
+}
+
+// Whether the whole workspace of a plan fits the library's own scratch array (adapm_step_static)
+bool fits_static(const adapm_ctx* c, bool stored) {
+  const FixedPart f = fixed_part(c);
+  const size_t budget = scratch_budget(c, f.scratch_at, stored);
+  size_t scratch = 0;
+  for (int path : {PATH_F64, PATH_FAST}) cut_groups(c, path, budget, stored, scratch);
+  return std::max(f.images_end, f.scratch_at + scratch) <= STATIC_SCRATCH_BYTES;
 }
 
 // Which blocks of the MFMA path run the products of Alg. 2 as stripe products (both read G itself: stripes of rows, and
@@ -867,32 +923,25 @@ std::vector<std::vector<int64_t>> cut_groups(const adapm_ctx* c, int path, size_
 // column of the block) stays inside the budget that the batched GEMMs have: a tall block of a small rank does not.
 // (1.34 B parameters with 24 blocks of 2048 x 5461 at r = 128: a step that runs Alg. 2 takes 18.2 ms with those blocks on
 // GEMMs, whose 128 x 128 tiles split every operand again in every tile, and 15.0 ms in stripes.)
-// Returns whether the plan on GEMMs fits the library's own scratch array (adapm_step_static); the plan then has to as well.
-// persistent: an upper bound of the part of the workspace that is not a group's scratch.
-bool choose_stripes(adapm_ctx* c, size_t persistent) {
-  bool any = false;
+// Returns the budget of a group's scratch.  adapm_step_static takes a table whose workspace fits the library's own array.
+// Which tables those are must not shrink with what the kernels learn to keep on chip: less scratch per block puts more
+// blocks into a group, and the groups may grow up to the budget, which follows the state size.  So a table that fits with
+// every intermediate stored, or with the blocks of ragged rows on GEMMs, is planned inside the array.
+size_t choose_stripes(adapm_ctx* c) {
+  for (size_t i = 0; i < c->table.size(); ++i)
+    c->lay[i].stripes = c->lay[i].path == PATH_FAST && c->table[i].cols % 8 == 0;
+  const bool in_static = fits_static(c, true) || fits_static(c, false);
+  const size_t gemm_at = fixed_part(c).scratch_at;       // stripes only take partial sums of v away from it
+  size_t limit = scratch_budget(c, gemm_at, false);
+  if (in_static) limit = std::min(limit, STATIC_SCRATCH_BYTES - gemm_at);
   for (size_t i = 0; i < c->table.size(); ++i) {
     Layout& L = c->lay[i];
-    L.stripes = L.path == PATH_FAST && c->table[i].cols % 8 == 0;
-    any = any || (L.path == PATH_FAST && !L.stripes);
-  }
-  if (!any) return false;
-  size_t budget = scratch_budget(c, persistent), scratch = 0;
-  for (int path : {PATH_F64, PATH_FAST})
-    for (const std::vector<int64_t>& ids : cut_groups(c, path, budget)) {
-      size_t used = 0;
-      for (int64_t i : ids) { Layout L = c->lay[i]; used += layout_block_scratch(c->table[i], c->hp, L, 0, true); }
-      scratch = std::max(scratch, used);
-    }
-  const bool fits_static = persistent + scratch <= STATIC_SCRATCH_BYTES;
-  if (fits_static) budget = std::min(budget, STATIC_SCRATCH_BYTES - persistent);
-  for (size_t i = 0; i < c->table.size(); ++i) {
-    Layout L = c->lay[i];
     if (L.path != PATH_FAST || L.stripes) continue;
     L.stripes = true;
-    c->lay[i].stripes = layout_block_scratch(c->table[i], c->hp, L, 0, true) <= budget;
+    L.stripes = block_scratch(c, i, false) <= limit;
   }
-  return fits_static;
+  const size_t at = fixed_part(c).scratch_at, budget = scratch_budget(c, at, false);
+  return in_static ? std::min(budget, STATIC_SCRATCH_BYTES - at) : budget;
 }
 
 // Lay out state / workspace and build every work list.
@@ -906,6 +955,7 @@ void build_plan(adapm_ctx* c) {
   const int64_t nb = (int64_t)c->table.size();
   const adapm_hparams_t& hp = c->hp;
   c->lay.assign(nb, Layout());
+  c->n_eff = (int)effective_step_sizes(hp.refresh_iters_K).size();
   size_t so = 0, wo = 0;
 
   for (int64_t i = 0; i < nb; ++i) {
@@ -930,20 +980,7 @@ void build_plan(adapm_ctx* c) {
     L.sv = salloc(4 * L.nv);
   }
   c->state_bytes = so;
-  // the part of the workspace that is not a group's scratch, from above (the partial sums of blocks whose v is finished
-  // elsewhere do not exist): which blocks those are depends on the choice made here
-  size_t ws_global = wo, ws_images = 0;
-  bool any_f64 = false;
-  for (int64_t i = 0; i < nb; ++i) {
-    const adapm_block_t& b = c->table[i];
-    const int64_t ge = group_elems(b);
-    if (b.v_mode != ADAPM_V_ELEMENT && ge > VS_CHUNK) ws_global += 8 * (size_t)(c->lay[i].nv * ((ge + VS_CHUNK - 1) / VS_CHUNK));
-    ws_global += 8 * (size_t)((b.rows * b.cols + VS_CHUNK - 1) / VS_CHUNK);       // global gradient norm
-    any_f64 = any_f64 || c->lay[i].path == PATH_F64;
-    if (c->lay[i].path == PATH_FAST && hp.refresh_period_T > 1)
-      ws_images += align_up(proj_qf_bytes(rank_class(b.rank), (int)b.cols)) + align_up(proj_timg_bytes(rank_class(b.rank), (int)b.cols));
-  }
-  const bool fits_static = choose_stripes(c, ws_global + 3 * ALIGN + (any_f64 ? ws_images : 0));
+  const size_t budget = choose_stripes(c);
 
   // device block table, element-wise chunks, v statistics
   int64_t npart = 0;
@@ -977,8 +1014,7 @@ void build_plan(adapm_ctx* c) {
       // on the MFMA path with T > 1 the fused kernel finishes fusable groups itself on steps with R held (list 1: only
       // steps that run Alg. 2), and where Alg. 2 streams G in stripes its first GD iteration does so (no list at all)
       const int which = (L.path == PATH_FAST && hp.refresh_period_T > 1 && v_fusable(b)) ? 1 : 0;
-      const bool in_stripes = L.path == PATH_FAST && v_fusable(b) && L.stripes &&
-                              !effective_step_sizes(hp.refresh_iters_K).empty() && (which == 1 || hp.refresh_period_T == 1);
+      const bool in_stripes = v_in_stripes(c, (size_t)i);
       const int64_t ge = d.group_elems;
       for (int64_t g = 0; g < (in_stripes ? 0 : L.nv); ++g) {
         if (ge <= VS_CHUNK) {
@@ -1044,8 +1080,6 @@ void build_plan(adapm_ctx* c) {
   if (c->n_lowrank == 0) return;
 
   // ---- groups of low-rank blocks: scratch budget, then per group the layout and the launches
-  size_t budget = scratch_budget(c, persistent);
-  if (fits_static) budget = std::min(budget, STATIC_SCRATCH_BYTES - persistent);
   size_t scratch_max = 0;
   if (hp.refresh_period_T > 1) {
     c->gemms.emplace_back();
@@ -1054,12 +1088,11 @@ void build_plan(adapm_ctx* c) {
     c->rg_chol = (int)c->chol.size() - 1;
   }
   for (int path : {PATH_F64, PATH_FAST}) {
-    for (const std::vector<int64_t>& ids : cut_groups(c, path, budget)) {
+    for (const std::vector<int64_t>& ids : cut_groups(c, path, budget, false, scratch_max)) {
       size_t at = persistent;
       for (int64_t i : ids) {
         at = layout_block_scratch(c->table[i], hp, c->lay[i], at, false);
       }
-      scratch_max = std::max(scratch_max, at - persistent);
       plan_lowrank_refresh(c, path == PATH_FAST, ids);
       if (hp.refresh_period_T > 1 && path == PATH_F64) plan_lowrank_project_f64(c, ids);
     }

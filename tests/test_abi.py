@@ -275,3 +275,23 @@ def test_tables_that_fit_the_static_scratch_still_do():
             ctx = B.adapm_init(table, make_hparams(T=T))
             assert B.adapm_workspace_bytes(ctx) <= static
             B.adapm_destroy(ctx)
+
+
+@pytest.mark.parametrize("blocks,hp", [
+    ([(120, 256, 440, 64, "bf16", "bf16")], dict(T=10)),
+    ([(40, 512, 928, 64, "bf16", "bf16")], dict(T=10)),
+    ([(60, 1351, 1043, 128, "f32", "bf16", B.ADAPM_V_WHOLE)], dict(T=10)),
+    ([(16, 191, 236, 51, "bf16", "bf16"), (12, 677, 2139, 128, "f32", "bf16")], dict(T=10)),
+    ([(73, 456, 536, 64, "f32", "bf16")], dict(T=1, K=1)),
+    ([(91, 711, 136, 128, "f32", "bf16")], dict(T=1)),
+])
+def test_less_scratch_per_block_does_not_outgrow_the_static_array(blocks, hp):
+    """Rows that are whole vectors and fp32 parameters too: with every intermediate of Alg. 2 in memory these tables need
+    43 - 64 MiB in two or more groups.  A plan that stores less may not answer by packing more blocks into fewer groups until
+    the whole no longer fits the array that adapm_step_static runs in."""
+    dt = {"f32": B.ADAPM_F32, "bf16": B.ADAPM_BF16}
+    table = [blk(rows=m, cols=n, rank=r, param_dtype=dt[pd], grad_dtype=dt[gd], v_mode=v[0] if v else B.ADAPM_V_ELEMENT)
+             for k, m, n, r, pd, gd, *v in blocks for _ in range(k)]
+    ctx = B.adapm_init(table, make_hparams(**hp))
+    assert B.adapm_workspace_bytes(ctx) <= B.adapm_static_scratch_bytes()
+    B.adapm_destroy(ctx)
