@@ -113,9 +113,8 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(const CholItem* __restric
 // Bound by those cache reads, 66 KB per wave at r = 128, and by the fp64 rate (25 GFLOP, 0.35 ms of the table below).  Against
 // 4 x 4 pieces per thread on the vector units with the matrix staged through LDS: 288 matrices of 1600 / 6400 at r = 128
 // 2.38 -> 1.05 ms.
-// One body per number of 16-wide steps, RG_T = ceil(r / 16), without branches from the first matrix instruction to the last:
-// a result must not be read until 19 wait states after the instruction that writes it, which the compiler fills in along
-// straight code but not, here, along every path of branches that skip steps (such a form left the last rows of a tile stale).
+// One body per number of 16-wide steps, RG_T = ceil(r / 16), without branches between the matrix instructions: the tiles that
+// are skipped are known at compile time, and no accumulator is copied on the way (see mfma_f64_results).
 template <int RG_T>
 __device__ __forceinline__ void regauge_body(const RegaugeItem& it, const Bases& b) {
   const int r = it.r, len = it.len;
@@ -163,6 +162,7 @@ __device__ __forceinline__ void regauge_body(const RegaugeItem& it, const Bases&
         for (int v = 0; v < 4; ++v) acc[t] = mfma_f64(m.r[v], (double)x[s][v], acc[t]);
       }
     }
+    mfma_f64_results(acc);
     if (u < len) {
 #pragma unroll
       for (int t = 0; t < RG_T; ++t)
@@ -197,6 +197,7 @@ __device__ __forceinline__ void regauge_body(const RegaugeItem& it, const Bases&
         }
       }
     }
+    mfma_f64_results(acc);
 #pragma unroll
     for (int p = 0; p < (RG_T + 1) / 2; ++p)
 #pragma unroll
@@ -210,7 +211,7 @@ __device__ __forceinline__ void regauge_body(const RegaugeItem& it, const Bases&
   }
 }
 
-__global__ __launch_bounds__(256) void regauge_apply_kernel(const RegaugeItem* __restrict__ items, Bases b) {
+__global__ __launch_bounds__(256, 2) void regauge_apply_kernel(const RegaugeItem* __restrict__ items, Bases b) {
   const RegaugeItem it = items[blockIdx.x];
   switch ((it.r + 15) / 16) {
     case 1: regauge_body<1>(it, b); break;

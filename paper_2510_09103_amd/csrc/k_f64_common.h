@@ -27,6 +27,32 @@ __device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// Between the matrix instructions of a product and the first other use of its results.  The hardware does not interlock
+// that read: it returns the registers' old contents until 19 wait states after the instruction.  The compiler is to fill them
+// in, but has left 4 - 9 along branches from one matrix instruction to the next (rows 92 - 95 of a 96-row tile stale), so the
+// source waits itself: 20 states, held in place by the two rows of ties.  What may still come before it are copies from
+// register to register; tests/test_fp64_listings.py checks the distance of those in the listings of every build.
+//
+// The kernels ask for two workgroups of four waves per CU, that is at most 256 registers, because the compiler then lets the
+// instruction work on ordinary registers.  With more it keeps the accumulators in the second half of the file and copies
+// them there and back in every step of a loop, and every copy is such a read.
+template <int N>
+__device__ __forceinline__ void mfma_f64_tie(f64x4 (&acc)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(acc[i]));
+}
+template <int M, int N>
+__device__ __forceinline__ void mfma_f64_tie(f64x4 (&acc)[M][N]) {
+#pragma unroll
+  for (int i = 0; i < M; ++i) mfma_f64_tie(acc[i]);
+}
+template <class Acc>
+__device__ __forceinline__ void mfma_f64_results(Acc& acc) {
+  mfma_f64_tie(acc);
+  asm volatile("; fp64 results\n\ts_nop 15\n\ts_nop 3");
+  mfma_f64_tie(acc);
+}
+
 __host__ __device__ constexpr int elem_bytes(int dtype) { return dtype == DT_F64 ? 8 : (dtype == DT_F32 ? 4 : 2); }
 
 // N consecutive elements as they lie in memory (raw: converted only where they are used, so that a load stays in flight)

@@ -66,11 +66,13 @@ __device__ __forceinline__ void product(const Mat& A, const Mat& B, double alpha
       a0 = a1;
       b0 = b1;
     }
+    mfma_f64_results(acc);
   }
   if (kb + nfull * KS < ke && (nfull & (NW - 1)) == wave) {
     a0.load_edge(wa, k1 + nfull * KS, ke);
     b0.load_edge(wb, k1 + nfull * KS, ke);
     mma(a0, b0);
+    mfma_f64_results(acc);
   }
 }
 
@@ -159,7 +161,7 @@ __device__ __forceinline__ void tile_body(const GemmProblem& P, const GemmTile& 
   }
 }
 
-__global__ __launch_bounds__(64 * NW) void gemm64_kernel(const GemmProblem* __restrict__ probs,
+__global__ __launch_bounds__(64 * NW, 2) void gemm64_kernel(const GemmProblem* __restrict__ probs,
                                                          const GemmTile* __restrict__ tiles, Bases bs) {
   __shared__ double red[NW * 16 * 64];
   const GemmTile t = tiles[blockIdx.x];

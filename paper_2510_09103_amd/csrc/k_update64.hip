@@ -82,6 +82,7 @@ __device__ __forceinline__ void accumulate(const Mat& A, const Mat& B, double al
       for (int t = 0; t < 4; ++t) acc[t] = mfma_f64(av, in ? b[v].get(t) : 0.0, acc[t]);
     }
   }
+  mfma_f64_results(acc);
 }
 
 // the operand types that occur (the planner makes no others)
@@ -92,7 +93,7 @@ __device__ __forceinline__ void accumulate_any(const Mat& A, const Mat& B, doubl
   else accumulate<DT_F64, DT_F64>(A, B, alpha, K, M, N, i0, col, bs, acc);
 }
 
-__global__ __launch_bounds__(256) void update64_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
+__global__ __launch_bounds__(256, 2) void update64_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
                                                        const BlockDev* __restrict__ blocks, Bases bs, StepScalars sc) {
   const GemmTile tile = tiles[blockIdx.x];
   const GemmProblem& P = probs[tile.prob];
