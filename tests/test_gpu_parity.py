@@ -130,11 +130,60 @@ def test_every_row_remainder_in_the_stripe_products(first, hp):
 
 
 @pytest.mark.parametrize("hp", [dict(T=1), dict(T=3)])
+def test_rows_a_multiple_of_the_chunks_with_ragged_columns(hp):
+    """The other end of a gradient whose rows are no whole vectors: rows that fill the last chunk of the transposed product
+    exactly (64), or all but one of it, with odd columns, so that its very last element sits alone in its dword."""
+    wl = WL.Workload("whole_chunks", tuple(
+        BlockSpec(f"{m}x{n}_r{r}", m, n, "bf16", "bf16", "lowrank", r, v, 1, 1.0, 0.1)
+        for m, n, r, v in ((64, 73, 8, "element"), (128, 331, 40, "rowgroup"), (192, 515, 70, "element"), (256, 257, 128, "whole"),
+                           (63, 513, 32, "rowgroup"), (320, 9, 4, "element"))), steps=4, seed=19, signal_rank=8)
+    pair, _ = run(wl, 4, dict(hp, contraction=B.ADAPM_CONTRACT_BF16X2), tol_state=TOL16, tol_param=TOL16, check_every=2)
+    labels = labels_of_a_step(pair.opt, pair.params, pair.stream.next(), 1, pair.wl.lr)
+    assert "alg2_stripe_step_r128" in labels and "alg2_products_mfma" not in labels, labels
+
+
+@pytest.mark.parametrize("hp", [dict(T=1), dict(T=3)])
 def test_both_contraction_paths_in_one_table(hp):
     """Automatic choice of the contraction: the fp32-parameter blocks of the table take the exact path, the bf16 ones
     the MFMA path.  With T > 1 the exact path's step with R held needs scratch in every step while the MFMA path's
     bf16 copies of R have to survive beside it (the layout that may not put the one over the other)."""
     run(ragged_bf16_table(), 6, dict(hp), tol_state=TOL16, tol_param=TOL16, check_every=2)
+
+
+def labels_of_a_step(opt, params, grads, t, lr):
+    """kernel classes that one step of this optimizer launches"""
+    torch.cuda.synchronize()
+    B.adapm_profile_read(opt.ctx)
+    B.adapm_profile_enable(opt.ctx, True)
+    opt.step(params, grads, t, lr)
+    torch.cuda.synchronize()
+    labels = set(B.adapm_profile_read(opt.ctx))
+    B.adapm_profile_enable(opt.ctx, False)
+    return labels
+
+
+def long_ragged_table():
+    """Long blocks whose rows are no whole vectors and whose rank is small for their size: the fragment images that stripe
+    products need would outgrow the scratch (30 MiB here, the state is smaller than that), so Alg. 2 runs as split-bf16 GEMMs.
+    Tall and wide, every rank class, every kind of v, both types of parameters; the contractions over the long side walk
+    up to 4096 chunks, with a remainder."""
+    mk = BlockSpec
+    return WL.Workload("long_ragged", (
+        mk("tall_r1", 131072, 9, "bf16", "bf16", "lowrank", 1, "element", 1, 1.0, 0.1),
+        mk("wide_r5", 9, 70001, "bf16", "bf16", "lowrank", 5, "rowgroup", 3, 1.0, 0.1),
+        mk("tall_r40_f32params", 40001, 75, "f32", "bf16", "lowrank", 40, "whole", 1, 1.0, 0.0),
+        mk("tall_r100", 20003, 130, "bf16", "bf16", "lowrank", 100, "rowgroup", 1, 1.0, 0.1),
+    ), steps=4, seed=15, signal_rank=8)
+
+
+@pytest.mark.parametrize("hp,clip", [(dict(T=1), None), (dict(T=3), None), (dict(T=1, normalise=1), None), (dict(T=2, bias_correction=0), 0.5)])
+def test_long_ragged_blocks_on_the_split_gemms(hp, clip):
+    pair, _ = run(long_ragged_table(), 3, dict(hp, contraction=B.ADAPM_CONTRACT_BF16X2), tol_state=TOL16, tol_param=TOL16,
+                  grad_clip=clip)
+    labels = labels_of_a_step(pair.opt, pair.params, pair.stream.next(), 1, pair.wl.lr)
+    assert {"alg2_products_mfma", "alg2_update_mfma"} <= labels, labels
+    assert not any(l.startswith("alg2_stripe") for l in labels), labels
+    assert ("alg2_step_normaliser" in labels) == bool(hp.get("normalise"))
 
 
 def exact_edges_table(gd, many):
@@ -173,8 +222,7 @@ def test_update_of_the_exact_path_at_the_edges_of_its_tiles(pd, gd, vm, clip, hp
 def odd_rank_table():
     """bf16 blocks whose rank is not 32, 64 or 128 (the paper takes r = 5 % of the smaller dimension): the
     MFMA kernels run them in the next rank class with zero-padded images of the factors.  Ranks that are
-    and are not multiples of 4 (vector / scalar access to the rows of L), rows that are and are not
-    multiples of 8 (stripe products / batched GEMM in Alg. 2)."""
+    and are not multiples of 4 (vector / scalar access to the rows of L)."""
     mk = BlockSpec
     return WL.Workload("odd_ranks", (
         mk("r8", 136, 200, "bf16", "bf16", "lowrank", 8, "rowgroup", 1, 1.0, 0.1),
@@ -213,9 +261,9 @@ def test_orthonormalisation_for_every_number_of_rank_steps(ranks):
 
 
 def random_table(rng, case):
-    """A few low-rank bf16-gradient blocks with random sizes (mostly multiples of 8, which Alg. 2 takes as stripe
-    products with the GD step riding on them; otherwise any size), ranks on and between the class and vector
-    boundaries, every kind of second moment."""
+    """A few low-rank bf16-gradient blocks with random sizes (mostly multiples of 8, rows of whole vectors; otherwise any
+    size, which the stripe products finish behind their loops), ranks on and between the class and vector boundaries, every
+    kind of second moment."""
     blocks = []
     for b in range(rng.randint(2, 4)):
         if rng.random() < 0.7:
@@ -599,11 +647,22 @@ def test_degenerate_inputs_zero_gradients_and_zero_step_size(hp):
 @pytest.mark.parametrize("rows,cols", [(136, 1 << 21), (1 << 21, 136)])
 def test_largest_blocks_of_the_mfma_path_agree_with_the_exact_path(rows, cols):
     """Maximum sizes: 2^21 columns is the widest block the MFMA kernels take (32-bit offsets inside a stripe),
-    2^21 rows the tallest one whose transposed copy still runs as stripe products.  The oracle needs minutes at
-    these sizes, so the property checked is that the two contraction paths of the library, which share no kernel
-    for low-rank blocks, agree on the same inputs."""
+    2^21 rows a tall one whose transposed product still runs in stripes.  The oracle needs minutes at these sizes, so the
+    property checked is that the two contraction paths of the library, which share no kernel for low-rank blocks, agree on
+    the same inputs."""
+    paths_agree(rows, cols, "rowgroup")
+
+
+@pytest.mark.parametrize("rows,cols", [(200, (1 << 21) - 1), (1 << 21, 137)])
+def test_largest_ragged_blocks_agree_with_the_exact_path(rows, cols):
+    """The same for rows that are no whole vectors, with a per-element second moment (whose state is what leaves room for
+    the stripes' images): the largest offsets of the loads at 2-byte alignment and of the 16-byte second moments."""
+    assert "alg2_stripe_step_r32" in paths_agree(rows, cols, "element")
+
+
+def paths_agree(rows, cols, v_mode):
     from paper_2510_09103_amd.optimizer import AdaPM, make_hparams
-    wl = WL.Workload("largest", (BlockSpec("big", rows, cols, "bf16", "bf16", "lowrank", 32, "rowgroup", 1, 1.0, 0.1),),
+    wl = WL.Workload("largest", (BlockSpec("big", rows, cols, "bf16", "bf16", "lowrank", 32, v_mode, 1, 1.0, 0.1),),
                      steps=3, seed=11, signal_rank=8)
     stream = WL.GradientStream(wl, device="cuda:0")
     grads = [[g.clone() for g in stream.next()] for _ in range(3)]
@@ -618,6 +677,8 @@ def test_largest_blocks_of_the_mfma_path_agree_with_the_exact_path(rows, cols):
         torch.cuda.synchronize()
         sv = opt.state_view(0)
         out.append((params[0].float().clone(), (sv["L"].double()[:4096] @ sv["R"].double()[:, :4096]).clone(), sv["v"].clone()))
+        if mode == B.ADAPM_CONTRACT_BF16X2:
+            labels = labels_of_a_step(opt, params, grads[0], 1, wl.lr)
         opt.close()
         del opt
     (w_a, lr_a, v_a), (w_b, lr_b, v_b) = out
@@ -627,6 +688,7 @@ def test_largest_blocks_of_the_mfma_path_agree_with_the_exact_path(rows, cols):
     rms = float(lr_b.pow(2).mean().sqrt())
     assert float((lr_a - lr_b).abs().max()) <= TOL16 * max(float(lr_b.abs().max()), rms)
     assert torch.allclose(v_a, v_b, rtol=1e-5, atol=0.0)
+    return labels
 
 
 def test_one_context_serving_two_state_buffers():
