@@ -50,7 +50,8 @@ __device__ __forceinline__ char* resolve(const Ref& r, const Bases& b) {
 
 // ---------------------------------------------------------------------------
 // batched GEMMs over strided operands
-//   Out[i,j] = g * X[i,j] + s * (sum_p a_p * sum_k A_p[i,k] B_p[k,j] + d * Y[i,j])      (up to three products)
+//   Out[i,j] = g * X[i,j] + s * (sum_p a_p * sum_k A_p[i,k] B_p[k,j] + d * Y[i,j])
+// up to three products in the fp64 kernel, which takes no Y, two in the split-bf16 one
 // element (i,j) of a matrix lives at base + (i*s0 + j*s1) * sizeof(dtype)
 // ---------------------------------------------------------------------------
 struct Mat {

@@ -1,5 +1,5 @@
 // fp64 batched GEMM on the fp64 matrix cores (the "F64" contraction mode and the re-expression of the factors):
-//   Out = g X + s (a1 A1 B1 + a2 A2 B2 + a3 A3 B3 + d Y),   optionally a second combination of X and the same sums
+//   Out = g X + s (a1 A1 B1 + a2 A2 B2 + a3 A3 B3),   optionally a second combination of X and the same sums
 // One launch covers a list of output tiles drawn from many independent problems, so every thin product of Alg. 2 of every
 // low-rank block runs in two launches per iteration (the r x r Gram matrices, then both factor updates with their
 // products with G).  Operands (bf16 / fp32 / fp64) convert exactly to fp64; all sums run in fp64 in a fixed order.
@@ -126,7 +126,6 @@ __device__ __forceinline__ void tile_body(const GemmProblem& P, const GemmTile& 
       for (int q = 0; q < 4; ++q) red[(wave * NR + (a * TN + b) * 4 + q) * 64 + lane] = acc[a][b][q];
   __syncthreads();
   const char* Xb = P.X.ref.space != SP_NONE ? resolve(P.X.ref, bs) : nullptr;
-  const char* Yb = P.Y.ref.space != SP_NONE ? resolve(P.Y.ref, bs) : nullptr;
   char* Ob = resolve(P.Out.ref, bs);
   // optional device scalar on everything but X (normalised step of Alg. 2)
   const double step_scale = P.off_s >= 0 ? *reinterpret_cast<const double*>(bs.ws + P.off_s) : P.s0;
@@ -141,7 +140,6 @@ __device__ __forceinline__ void tile_body(const GemmProblem& P, const GemmTile& 
     const int i = LAY == G64_IJ ? i0 + TM * row + a : i0 + 16 * a + row;
     const int j = LAY == G64_KK ? j0 + 16 * b + l16 : j0 + TN * l16 + b;
     if (i >= P.M || j >= P.N) continue;
-    if (Yb) val = fma(P.d, load_el(Yb, P.Y.dtype, (int64_t)i * P.Y.s0 + (int64_t)j * P.Y.s1), val);
     // the step with R held takes both D = b1 (L' - P) and L_t from one P = G R^T (three launches 62 + 19 + 13 -> 66 us)
     double val2 = P.s2 * val;
     val *= step_scale;
