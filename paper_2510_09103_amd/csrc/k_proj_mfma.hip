@@ -418,6 +418,10 @@ __device__ __forceinline__ void stripe_pass1_x2(unsigned char* smem, const Strip
     }
   }
   if (tl.xc) {
+    // what follows from the thread's number is computed again: kept from above it would not fit beside the accumulators
+    int id = threadIdx.x;
+    asm volatile("" : "+v"(id));
+    const int lane = id & 63, t512 = id & 511, l32 = lane & 31, lh = lane >> 5, c8 = (t512 & 7) * 8;
     // Every round above ended with a barrier behind its reads, so both tile buffers and both image buffers are free.
     // Chunk q = (matrix, 64 columns of X): barrier A = tiles staged and image landed, barrier B = both read.  The
     // tail moves about as many bytes per stripe as a short stripe product does and runs at that rate; deeper
@@ -540,6 +544,9 @@ __device__ __forceinline__ void stripe_pass1_x2(unsigned char* smem, const Strip
   }
   __syncthreads();
   if (mrole) {
+    int id = threadIdx.x;
+    asm volatile("" : "+v"(id));
+    const int l32 = id & 31, lh = (id >> 5) & 1;
     float* Ps = reinterpret_cast<float*>(smem);
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
@@ -1374,14 +1381,24 @@ struct StripeLds {
   static_assert(P_END % 16 == 0, "the tail is addressed in vectors");
 };
 
+// Values that are uniform over the wave without the compiler seeing it, kept in scalar registers (see make_rsrc_uniform)
+__device__ __forceinline__ char* resolve_uniform(const Ref& r, const Bases& b) {
+  const uint64_t a = (uint64_t)resolve(r, b);
+  const uint64_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a);
+  const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32));
+  return (char*)(hi << 32 | lo);
+}
+
+__device__ __forceinline__ float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
+
 // smem: StripeLds<RT, TRA>::BYTES of LDS; rsum: LDS, the sums of squares of the stripe's rows (second moment)
 template <int RT, bool TRA>
 __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, const StripeItem& item, const StripeProb& P,
                                             const Bases& bs) {
   constexpr int R = 32 * RT, PS = StripeLds<RT, TRA>::PS, ROWS = StripeLds<RT, TRA>::ROWS, P_END = StripeLds<RT, TRA>::P_END;
   const int M = P.M, K = P.K, row0 = item.row0;
-  const int tid = threadIdx.x;
-  const uint16_t* __restrict__ A = reinterpret_cast<const uint16_t*>(resolve(P.a, bs));
+  int tid = threadIdx.x;
+  const uint16_t* __restrict__ A = reinterpret_cast<const uint16_t*>(resolve_uniform(P.a, bs));
   const unsigned rows_valid = (unsigned)(M - row0 < ROWS ? M - row0 : ROWS);
   StripeSrc src = {};
   if (TRA) {
@@ -1391,32 +1408,33 @@ __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, co
     src.n = K; src.nv = K & ~7;
   }
   const int r = P.r;                  // rows of Q actually present (the image is zero-padded to R)
-  float gs = grad_scale(bs);          // global gradient clipping: A is the gradient (or its transpose)
+  float gs = uniform(grad_scale(bs));   // global gradient clipping: A is the gradient (or its transpose)
   const float gs2 = gs * gs;
   // fused GD step of Alg. 2: the factor X in the layout of Out; its coefficients take the step normaliser, the one of
   // the stripe product also the gradient scale (the store below then adds X instead of scaling)
   StripeTail tl = {};
   const float* Xc = nullptr;        // may be the very buffer Out points at (iterations after the first update in place)
   if (P.upd) {
-    const float s = P.off_s >= 0 ? (float)*reinterpret_cast<const double*>(bs.ws + P.off_s) : 1.f;
-    Xc = reinterpret_cast<const float*>(resolve(P.x_cur, bs));
-    const float* Xp = reinterpret_cast<const float*>(resolve(P.x_prev, bs));
-    tl.sj = P.transpose_out ? 1 : r;
-    tl.sa = P.transpose_out ? M : 1;
+    const float s = uniform(P.off_s >= 0 ? (float)*reinterpret_cast<const double*>(bs.ws + P.off_s) : 1.f);
+    Xc = reinterpret_cast<const float*>(resolve_uniform(P.x_cur, bs));
+    const float* Xp = reinterpret_cast<const float*>(resolve_uniform(P.x_prev, bs));
+    tl.sj = TRA ? 1 : r;
+    tl.sa = TRA ? M : 1;
     tl.xc = Xc + (int64_t)row0 * tl.sj;
     tl.xp = Xp + (int64_t)row0 * tl.sj;
     tl.rows = (int)rows_valid; tl.r = r;
     tl.img1 = bs.ws + P.off_b1; tl.img2 = bs.ws + P.off_b2;
-    tl.c1 = s * P.c1; tl.c2 = s * P.c2; tl.cp = s * gs * P.cp;
+    tl.c1 = uniform(s * P.c1); tl.c2 = uniform(s * P.c2); tl.cp = uniform(s * gs * P.cp);
     tl.nmat = 2;
     // first GD iteration: the factor is still the one of the previous step and the two r x r matrices are one and the
     // same product (the Gram kernel writes it to both places), so the two thin products fold into one
-    if (P.x_cur.space == P.x_prev.space && P.x_cur.off == P.x_prev.off) { tl.c1 += tl.c2; tl.nmat = 1; }
+    if (P.x_cur.space == P.x_prev.space && P.x_cur.off == P.x_prev.off) { tl.c1 = uniform(tl.c1 + tl.c2); tl.nmat = 1; }
     if (TRA && tl.nmat == 1 && P.off_timg_prev >= 0)
       tl.timg = bs.ws + P.off_timg_prev + (int64_t)(row0 / BK) * timg_chunk_bytes(R);
     gs = 1.f;
   }
   stripe_pass1_x2<RT, TRA>(smem, src, bs.ws + P.off_img, (!TRA && P.v_rows > 0) ? rsum : nullptr, tl);
+  asm volatile("" : "+v"(tid));        // nothing computed from it is kept across the pass
   __syncthreads();
   // Rows of the gradient that are not whole 16-byte vectors (nt columns beyond the last one; K or, transposed, M is no
   // multiple of 8).  They may start at any 2-byte alignment, which the loads serve; what the pass leaves out is added here,
@@ -1476,7 +1494,7 @@ __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, co
   float* Out = reinterpret_cast<float*>(bs.ws + P.off_out);
   // with the GD step, the new factor values (zeros outside the factor) go back into P for the image below
   const bool emit_f = P.upd && P.off_next >= 0, emit_t = P.upd && P.off_timg >= 0, emit = emit_f || emit_t;
-  if (!P.transpose_out) {
+  if (!TRA) {
     const bool vec4 = (r & 3) == 0;
 #pragma unroll
     for (int i = 0; i < (ROWS * R / 4) / NT; ++i) {
@@ -1614,12 +1632,17 @@ __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, co
 
 // Both products of a GD iteration in one launch.  They are independent (the stripes of an iteration read one set of images
 // and write the next, and of the factors only the rows behind themselves).  A workgroup owns a CU and a launch ends with
-// its slowest CU, so half as many launches waste half as many tails, and the two products read G at about the same time.
+// its slowest CU, so half as many launches waste half as many tails.  (They do not share reads of G: the longest contractions
+// are dealt first, so the two products of a rectangular block run far apart.)
 // Measured per literal step, two launches -> one: 24 layers of 1024 / 4096 at r = 64 3.11 -> 2.91 ms, 2048 / 5461 at
 // r = 128 14.6 -> 14.1 ms, 48 layers of 1600 / 6400 at r = 128 (launches long enough already) 15.4 -> 15.3 ms.  One wave of
 // each role per SIMD instead of two (256 registers, 4 x 2 tiles per matrix-core wave, fragments requested one k-step
 // ahead: two thirds of the LDS reads) changed nothing: the launch moves 4.3 TB/s of mixed reads and writes, of the 5.0 that a
 // plain read-modify-write stream of this access pattern reaches.
+// Registers: at r = 128 the two bodies want more than the 128 there are.  Uniform pointers and factors are therefore forced
+// into scalar registers and what follows from the thread's number is computed again behind the pass over G; with both kept
+// in vector registers 60 bytes per lane went to scratch, 2 % of the launch's traffic (now 12 bytes, read in the loop of the
+// thin products: 15.31 -> 15.17 ms per literal step of the 1600 / 6400 table, 14.13 -> 14.00 of the 2048 / 5461 one).
 template <int RT>
 __global__ __launch_bounds__(NT, 1) void stripe_kernel(const StripeItem* __restrict__ items,
                                                        const StripeProb* __restrict__ probs, Bases bs) {
