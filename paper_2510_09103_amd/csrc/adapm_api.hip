@@ -322,9 +322,10 @@ std::vector<double> effective_step_sizes(int K) {
   return out;
 }
 
-// Alg. 2 + eq. 3-4 for the low-rank blocks of one contraction path, as batched GEMM launches.
-//   fast = false: fp64 vector-ALU GEMM, every intermediate kept in fp64;
-//   fast = true : split-bf16 MFMA GEMM, fp32 intermediates.
+// Alg. 2 + eq. 3-4 for the low-rank blocks of one contraction path.
+//   fast = false: batched GEMMs on the fp64 matrix cores, every intermediate kept in fp64;
+//   fast = true : split-bf16 matrix instructions, fp32 intermediates: stripe products, or batched GEMMs for the blocks
+//                 that the stripes do not take.
 // `ids`: the blocks of ONE group, all on the same contraction path; the group's scratch offsets are in c->lay.
 void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& ids) {
   const adapm_hparams_t& hp = c->hp;

@@ -70,7 +70,7 @@ struct GemmProblem {
   Mat A1, B1, A2, B2, A3, B3, X, Y, Out;
   int32_t M, N, K1, K2, K3;
   int32_t layout;    // fp64 kernel: Gemm64Layout
-  int32_t tm, tn;    // fp64 kernel: output tile of a workgroup in units of 16 (see gemm64_tile_shape)
+  int32_t tm, tn;    // fp64 kernel: output tile of a workgroup in units of 16 (chosen in shape64, adapm_api.hip)
   double a1, a2, a3, g, d;
   int32_t scale_g;   // 1: the first product has the gradient as an operand and takes the clipping factor
   int32_t tri;       // fp64 kernel: 1 = A1 is lower triangular, 2 = B1 is lower triangular (zero part of the contraction skipped)

@@ -475,7 +475,7 @@ __device__ __forceinline__ void stripe_pass1_x2(unsigned char* smem, const Strip
       // offsets: a slot outside the piece of X reads zeros or a neighbouring element of X, and is masked when staged
       const bool vec = tl.sa == 1 && (tl.r & 3) == 0 && (tl.sj & 3) == 0;
       const unsigned xbytes = (unsigned)(((int64_t)(tl.rows - 1) * tl.sj + (int64_t)(tl.r - 1) * tl.sa + 1) * 4);
-            const unsigned sj4 = (unsigned)tl.sj * 4u, sa4 = (unsigned)tl.sa * 4u;
+      const unsigned sj4 = (unsigned)tl.sj * 4u, sa4 = (unsigned)tl.sa * 4u;
       float raw[4][8];
       auto fetch_x = [&](int q) {
         const __amdgpu_buffer_rsrc_t rX = make_rsrc_uniform(q < nk2 ? tl.xc : tl.xp, xbytes);
@@ -1427,7 +1427,7 @@ __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, co
     tl.c1 = uniform(s * P.c1); tl.c2 = uniform(s * P.c2); tl.cp = uniform(s * gs * P.cp);
     tl.nmat = 2;
     // first GD iteration: the factor is still the one of the previous step and the two r x r matrices are one and the
-    // same product (the Gram kernel writes it to both places), so the two thin products fold into one
+    // same product (one image, which the Gram kernel writes once), so the two thin products fold into one
     if (P.x_cur.space == P.x_prev.space && P.x_cur.off == P.x_prev.off) { tl.c1 = uniform(tl.c1 + tl.c2); tl.nmat = 1; }
     if (TRA && tl.nmat == 1 && P.off_timg_prev >= 0)
       tl.timg = bs.ws + P.off_timg_prev + (int64_t)(row0 / BK) * timg_chunk_bytes(R);
@@ -1859,8 +1859,8 @@ __device__ __forceinline__ void gram_body(const GramItem& it, const Bases& bs, u
 }
 
 // Results of a pair of Gram-type products, complete in LDS as [R][R] fp32 each: S S^T itself where somebody reads it (the
-// normaliser of the step; nobody reads X S^T) and the fragment images of both for the GD step on the stripes (the layout qf_image_kernel writes), 64-wide chunks of the
-// contraction index k: lane l of a piece holds result[64 c + 16 kk + 8 (l / 32) .. + 7][32 tile + l % 32].
+// normaliser of the step; nobody reads X S^T) and the fragment images of both for the GD step on the stripes (the layout
+// qf_image_kernel writes), 64-wide chunks of the contraction index k: lane l of a piece holds result[64 c + 16 kk + 8 (l / 32) .. + 7][32 tile + l % 32].
 template <int RT>
 __device__ __forceinline__ void gram_emit(const float* Mss, const float* Mxs, const Bases& bs, int64_t off_out_ss,
                                           int64_t off_img_ss, int64_t off_img_xs, int r, bool same, int nthreads) {

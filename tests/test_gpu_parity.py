@@ -89,8 +89,8 @@ def test_mixed_table_all_modes(hp):
 
 
 def ragged_bf16_table():
-    """bf16 blocks on the MFMA path whose sizes are not multiples of the 64-row stripes, the
-    64-column chunks, the 128 x 128 GEMM tiles or the 8-element vectors; every rank class; every kind of v."""
+    """bf16 blocks on the MFMA path whose sizes are not multiples of the 128- and 256-row stripes, the 64-column chunks
+    or the 8-element vectors; every rank class; every kind of v."""
     mk = BlockSpec
     return WL.Workload("ragged_bf16", (
         mk("r32_cols1000", 200, 1000, "bf16", "bf16", "lowrank", 32, "rowgroup", 1, 1.0, 0.1),
@@ -120,8 +120,8 @@ def test_ragged_shapes_on_the_mfma_path(hp):
 @pytest.mark.parametrize("hp", [dict(T=1), dict(T=3)])
 def test_every_row_remainder_in_the_stripe_products(first, hp):
     """Row lengths of every remainder mod 8 (and so mod 4), below one vector's width past a 64-column chunk and past a
-    256-column stripe: the vector at the end of a row is read at the row's last 8 columns and moved down, and the rows of R
-    are stored at 4-byte alignments.  The per-row second moment takes the rows' sums of squares from the same vectors."""
+    256-column stripe: the columns behind a row's last whole vector join the products, and the sums of squares of the
+    per-row second moment, behind the loops, and the rows of R are stored at 4-byte alignments."""
     wl = WL.Workload("remainders", tuple(
         BlockSpec(f"c{c}_r{r}", 70 + c % 7, c, "bf16", "bf16", "lowrank", r, v, 1, 1.0, 0.1)
         for r, v, base in ((8, "rowgroup", 8), (40, "element", 64), (70, "rowgroup", 256), (32, "whole", 512 + 56))
