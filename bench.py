@@ -222,7 +222,7 @@ def main():
                              "frac": alg / sec / 1e12 / MFMA_BF16_PEAK_TFLOPS,
                              "issued_TFLOPs": issued / sec / 1e12,
                              "issued_frac": issued / sec / 1e12 / MFMA_BF16_PEAK_TFLOPS},
-                    "note": "bytes: G once plus the factor it updates (current and previous read, new written: fp32); mfma.achieved = "
+                    "note": "bytes: G once per product and the factors they update (current and previous read, new written: fp32); mfma.achieved = "
                             "flops of the mathematical products; mfma.issued = matrix-core work with every fp32 "
                             "operand as a (hi, lo) bf16 pair (2 instructions per product of G, 3 per thin product) "
                             "at the padded rank class"}
@@ -233,11 +233,13 @@ def main():
                       4 * (b.rows + b.cols) * b.rank * (2 if refresh_step else 1) for b in lr_blocks)
             roof = {"bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s", "achieved": alg / (k["avg_ms"] * 1e-3) / 1e9}
         elif label in ("project_f64", "alg2_gram_f64", "alg2_update_f64"):
-            # exact path: batched fp64 products on the matrix cores.  project: G Q^T; Alg. 2, per GD iteration: the r x r Gram matrices, and G R^T, L^T G with the
-            # thin products of the factor updates behind them
+            # exact path: batched fp64 products on the matrix cores.  project: G Q^T; Alg. 2, per GD iteration: the r x r Gram
+            # matrices, and G R^T, L^T G with the thin products of the factor updates behind them.  The first iteration has
+            # half as many Gram matrices and thin products (its factors are still the previous step's): averaged over the K - 1
+            thin = lambda b: 4.0 * (b.rows + b.cols) * b.rank ** 2 * (1 - 0.5 / max(wl.K - 1, 1))
             per_block = {"project_f64": lambda b: 2.0 * b.rows * b.cols * b.rank,
-                         "alg2_gram_f64": lambda b: 4.0 * (b.rows + b.cols) * b.rank ** 2,
-                         "alg2_update_f64": lambda b: 4.0 * b.rows * b.cols * b.rank + 4.0 * (b.rows + b.cols) * b.rank ** 2}[label]
+                         "alg2_gram_f64": thin,
+                         "alg2_update_f64": lambda b: 4.0 * b.rows * b.cols * b.rank + thin(b)}[label]
             alg = sum(per_block(b) for b in lr_blocks)
             roof = {"bound": "alu", "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "achieved": alg / (k["avg_ms"] * 1e-3) / 1e12,

@@ -112,7 +112,8 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(const CholItem* __restric
 // straight from the caches (k_f64_common.h for the lane layouts), whose 16 x 16 (L: 16 x 32) tiles outside the triangle are skipped.
 // Bound by those cache reads, 66 KB per wave at r = 128, and by the fp64 rate (25 GFLOP, 0.35 ms of the table below).  Against
 // 4 x 4 pieces per thread on the vector units with the matrix staged through LDS: 288 matrices of 1600 / 6400 at r = 128
-// 2.38 -> 1.05 ms.
+// 2.38 -> 0.87 ms (1.05 with 264 registers and the accumulators in the second half of
+// the file, see mfma_f64_results).
 // One body per number of 16-wide steps, RG_T = ceil(r / 16), without branches between the matrix instructions: the tiles that
 // are skipped are known at compile time, and no accumulator is copied on the way (see mfma_f64_results).
 template <int RG_T>

@@ -1637,12 +1637,13 @@ __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, co
 // Measured per literal step, two launches -> one: 24 layers of 1024 / 4096 at r = 64 3.11 -> 2.91 ms, 2048 / 5461 at
 // r = 128 14.6 -> 14.1 ms, 48 layers of 1600 / 6400 at r = 128 (launches long enough already) 15.4 -> 15.3 ms.  One wave of
 // each role per SIMD instead of two (256 registers, 4 x 2 tiles per matrix-core wave, fragments requested one k-step
-// ahead: two thirds of the LDS reads) changed nothing: the launch moves 4.3 TB/s of mixed reads and writes, of the 5.0 that a
+// ahead: two thirds of the LDS reads) changed nothing: the launch moves 4.4 TB/s of mixed reads and writes, of the 5.0 that a
 // plain read-modify-write stream of this access pattern reaches.
 // Registers: at r = 128 the two bodies want more than the 128 there are.  Uniform pointers and factors are therefore forced
 // into scalar registers and what follows from the thread's number is computed again behind the pass over G; with both kept
-// in vector registers 60 bytes per lane went to scratch, 2 % of the launch's traffic (now 12 bytes, read in the loop of the
-// thin products: 15.31 -> 15.17 ms per literal step of the 1600 / 6400 table, 14.13 -> 14.00 of the 2048 / 5461 one).
+// in vector registers 60 bytes per lane went to scratch, 5 % of the launch's traffic (now 12 bytes, read in the loop of the
+// thin products: 3.65 -> 3.47 GB for a third of the 1600 / 6400 table, whose literal step went from 15.31 to 15.17 ms, that of
+// the 2048 / 5461 table from 14.13 to 14.00).
 template <int RT>
 __global__ __launch_bounds__(NT, 1) void stripe_kernel(const StripeItem* __restrict__ items,
                                                        const StripeProb* __restrict__ probs, Bases bs) {
