@@ -38,14 +38,28 @@ __device__ __forceinline__ float grad_scale(const Bases& b) { return b.gscale ? 
 struct __attribute__((packed, aligned(2))) u32x4_a2 { uint32_t x, y, z, w; };
 struct __attribute__((packed, aligned(4))) f32x4_a4 { float x, y, z, w; };
 
+// Every buffer the kernels are handed is device memory.  A pointer that comes out of a table or a switch is a generic one to the
+// compiler, whose flat loads count as LDS reads as well: they return in no known order, so every wait is for all of them, and
+// they are split at alignments that global loads serve whole.
+// p is the same in every lane of the wave.
+template <class T>
+__device__ __forceinline__ T* global_ptr(T* p) {
+  const uint64_t a = (uint64_t)p;
+  const uint64_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a);
+  const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32));
+  return (T*)(__attribute__((address_space(1))) T*)(hi << 32 | lo);
+}
+
 __device__ __forceinline__ char* resolve(const Ref& r, const Bases& b) {
+  char* p;
   switch (r.space) {
-    case SP_STATE: return b.state + r.off;
-    case SP_WS: return b.ws + r.off;
-    case SP_GRAD: return (char*)b.grads[r.block] + r.off;
-    case SP_PARAM: return (char*)b.params[r.block] + r.off;
+    case SP_STATE: p = b.state + r.off; break;
+    case SP_WS: p = b.ws + r.off; break;
+    case SP_GRAD: p = (char*)b.grads[r.block] + r.off; break;
+    case SP_PARAM: p = (char*)b.params[r.block] + r.off; break;
     default: return nullptr;
   }
+  return global_ptr(p);
 }
 
 // ---------------------------------------------------------------------------

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void vstat_kernel(const BlockDev* __restrict__
   if (it >= nitems) return;
   const VsItem item = items[it];
   const BlockDev blk = blocks[item.block];
-  const char* G = (const char*)b.grads[item.block];
+  const char* G = global_ptr((const char*)b.grads[item.block]);
   const int64_t s = item.start, e = item.start + item.count;
   const int64_t a0 = min((s + 7) & ~(int64_t)7, e), a1 = max(e & ~(int64_t)7, a0);
   float acc = 0.f;
@@ -152,8 +152,8 @@ __global__ __launch_bounds__(256) void update_grouped_kernel(const BlockDev* __r
   const GrpItem item = items[blockIdx.x];
   const BlockDev blk = blocks[item.block];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const char* G = (const char*)b.grads[item.block];
-  char* W = (char*)b.params[item.block];
+  const char* G = global_ptr((const char*)b.grads[item.block]);
+  char* W = global_ptr((char*)b.params[item.block]);
   float* m = blk.off_m >= 0 ? reinterpret_cast<float*>(b.state + blk.off_m) : nullptr;
   float* v = reinterpret_cast<float*>(b.state + blk.off_v);
   const UpdCoef cf = make_coef(sc.lr, blk.lr_scale, blk.wd, sc.clip);
@@ -252,8 +252,8 @@ __global__ __launch_bounds__(256) void update_kernel(const BlockDev* __restrict_
                                                      const EwItem* __restrict__ items, Bases b, StepScalars sc) {
   const EwItem item = items[blockIdx.x];
   const BlockDev blk = blocks[item.block];
-  const char* G = (const char*)b.grads[item.block];
-  char* W = (char*)b.params[item.block];
+  const char* G = global_ptr((const char*)b.grads[item.block]);
+  char* W = global_ptr((char*)b.params[item.block]);
   float* m = blk.off_m >= 0 ? reinterpret_cast<float*>(b.state + blk.off_m) : nullptr;
   float* v = reinterpret_cast<float*>(b.state + blk.off_v);
   const UpdCoef cf = make_coef(sc.lr, blk.lr_scale, blk.wd, sc.clip);

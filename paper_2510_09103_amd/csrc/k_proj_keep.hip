@@ -109,8 +109,8 @@ __global__ __launch_bounds__(KT, 1) void proj_keep_kernel(const ProjItem* __rest
   const int l32 = lane & 31, lh = lane >> 5;
   const int m = B.m, n = B.n, r = B.r, row0 = item.row0;
   const int nc = (n + BK - 1) / BK;                  // n is a multiple of 8 and nc <= KMAXC (the planner sees to both)
-  const uint16_t* __restrict__ G = reinterpret_cast<const uint16_t*>(bs.grads[B.block]);
-  char* __restrict__ W = reinterpret_cast<char*>(bs.params[B.block]);
+  const uint16_t* __restrict__ G = reinterpret_cast<const uint16_t*>(global_ptr(bs.grads[B.block]));
+  char* __restrict__ W = reinterpret_cast<char*>(global_ptr(bs.params[B.block]));
   float* __restrict__ Lst = reinterpret_cast<float*>(bs.state + B.off_L);
   float* __restrict__ vst = reinterpret_cast<float*>(bs.state + B.off_v);
   const char* __restrict__ Qf = bs.ws + B.off_Qf;

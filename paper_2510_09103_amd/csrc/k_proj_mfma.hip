@@ -599,8 +599,8 @@ __global__ __launch_bounds__(NT, 1) void proj_kernel(const ProjItem* __restrict_
   // their share of D Q, their update).
   const int n8 = n & ~7, nt = n - n8;
   const int nc = (n8 + BK - 1) / BK;
-  const uint16_t* __restrict__ G = reinterpret_cast<const uint16_t*>(bs.grads[B.block]);
-  char* __restrict__ W = reinterpret_cast<char*>(bs.params[B.block]);
+  const uint16_t* __restrict__ G = reinterpret_cast<const uint16_t*>(global_ptr(bs.grads[B.block]));
+  char* __restrict__ W = reinterpret_cast<char*>(global_ptr(bs.params[B.block]));
   float* __restrict__ Lst = reinterpret_cast<float*>(bs.state + B.off_L);
   float* __restrict__ vst = reinterpret_cast<float*>(bs.state + B.off_v);
   const char* __restrict__ Qf = bs.ws + B.off_Qf;
@@ -1116,8 +1116,8 @@ __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* _
   const int n8 = n & ~7, nt = n - n8;
   const int nr = (n8 + BR - 1) / BR;              // 32-column tiles
   const int NR = (nr + 1 + D2) / D2 * D2;         // rounds: nr + 2, rounded up to the prefetch depth
-  const uint16_t* __restrict__ G = reinterpret_cast<const uint16_t*>(bs.grads[B.block]);
-  char* __restrict__ W = reinterpret_cast<char*>(bs.params[B.block]);
+  const uint16_t* __restrict__ G = reinterpret_cast<const uint16_t*>(global_ptr(bs.grads[B.block]));
+  char* __restrict__ W = reinterpret_cast<char*>(global_ptr(bs.params[B.block]));
   float* __restrict__ vst = reinterpret_cast<float*>(bs.state + B.off_v);
   lds_u8* const lds = (lds_u8*)smem;
 
@@ -1381,14 +1381,7 @@ struct StripeLds {
   static_assert(P_END % 16 == 0, "the tail is addressed in vectors");
 };
 
-// Values that are uniform over the wave without the compiler seeing it, kept in scalar registers (see make_rsrc_uniform)
-__device__ __forceinline__ char* resolve_uniform(const Ref& r, const Bases& b) {
-  const uint64_t a = (uint64_t)resolve(r, b);
-  const uint64_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a);
-  const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32));
-  return (char*)(hi << 32 | lo);
-}
-
+// A value that is uniform over the wave without the compiler seeing it, kept in a scalar register (see make_rsrc_uniform)
 __device__ __forceinline__ float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
 
 // smem: StripeLds<RT, TRA>::BYTES of LDS; rsum: LDS, the sums of squares of the stripe's rows (second moment)
@@ -1398,7 +1391,7 @@ __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, co
   constexpr int R = 32 * RT, PS = StripeLds<RT, TRA>::PS, ROWS = StripeLds<RT, TRA>::ROWS, P_END = StripeLds<RT, TRA>::P_END;
   const int M = P.M, K = P.K, row0 = item.row0;
   int tid = threadIdx.x;
-  const uint16_t* __restrict__ A = reinterpret_cast<const uint16_t*>(resolve_uniform(P.a, bs));
+  const uint16_t* __restrict__ A = reinterpret_cast<const uint16_t*>(resolve(P.a, bs));
   const unsigned rows_valid = (unsigned)(M - row0 < ROWS ? M - row0 : ROWS);
   StripeSrc src = {};
   if (TRA) {
@@ -1416,8 +1409,8 @@ __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, co
   const float* Xc = nullptr;        // may be the very buffer Out points at (iterations after the first update in place)
   if (P.upd) {
     const float s = uniform(P.off_s >= 0 ? (float)*reinterpret_cast<const double*>(bs.ws + P.off_s) : 1.f);
-    Xc = reinterpret_cast<const float*>(resolve_uniform(P.x_cur, bs));
-    const float* Xp = reinterpret_cast<const float*>(resolve_uniform(P.x_prev, bs));
+    Xc = reinterpret_cast<const float*>(resolve(P.x_cur, bs));
+    const float* Xp = reinterpret_cast<const float*>(resolve(P.x_prev, bs));
     tl.sj = TRA ? 1 : r;
     tl.sa = TRA ? M : 1;
     tl.xc = Xc + (int64_t)row0 * tl.sj;
