@@ -66,6 +66,8 @@ struct Layout {                      // byte offsets, -1 = absent
   int64_t wT1 = -1, wT2 = -1;                               // ws: images of R_{t-1}^T and R_t^T for the fused update after Alg. 2
   int64_t nv = 0;
   int path = PATH_NONE;
+  int64_t wLp = -1, wRp = -1;                               // ws: exact path: the previous step's factors, where Alg. 2 writes the state itself
+  bool direct = false;                                      // exact path: the last GD iteration writes the state (stores_direct)
   bool stripes = false;                                     // MFMA path: the products of Alg. 2 run as stripes (choose_stripes)
 };
 
@@ -77,6 +79,9 @@ struct GemmList {
   GemmProblem* d_probs = nullptr;
   GemmTile* d_tiles = nullptr;
   bool mfma = false;  // split-bf16 kernel (else fp64)
+  int waves = 4;      // fp64 kernel: waves of a workgroup (waves64)
+  int steps = 0;      // update of the exact path: most steps of 16 in the contractions of a block
+  int cls = 0;        // ... and the class of its blocks (update64_class)
 };
 
 struct Op {
@@ -274,7 +279,7 @@ void add_problem(GemmList& gl, const GemmProblem& p, bool lower_only = false) {
   const int TM = gl.mfma ? 128 : 16 * p.tm, TN = gl.mfma ? 128 : 16 * p.tn;
   for (int ti = 0; ti < (p.M + TM - 1) / TM; ++ti)
     for (int tj = 0; tj < (p.N + TN - 1) / TN; ++tj)
-      if (!lower_only || tj <= ti) gl.tiles.push_back(GemmTile{id, ti, tj});
+      if (!lower_only || tj <= ti) gl.tiles.push_back(GemmTile{id, ti, tj, 1});
 }
 
 // The fp64 kernel: operand layout and output tile.  32 x 32 tiles load half as much per multiply-add as 16 x 16 ones; a
@@ -285,6 +290,50 @@ GemmProblem& shape64(GemmProblem& p, int layout, bool small = false) {
   p.tm = (small || (p.M <= 16 && layout != G64_KJ)) ? 1 : 2;
   p.tn = (small || p.N <= 16) ? 1 : 2;
   return p;
+}
+
+// Waves that share the contraction of one output tile in a launch of the fp64 kernel whose results are `tiles16` tiles of 16 x 16
+// (measured: k_gemm64.hip).  One workgroup of 16 waves or two of 8 fill a compute unit's 128-register slots; above two rounds
+// of those, four waves on 32 x 32 tiles load half as much per multiply-add: the updates of 56 blocks at r = 32, 9760 tiles, take
+// 98 us that way and 146 us with 8 waves.
+int waves64(int64_t tiles16) { return tiles16 <= 256 ? 16 : (tiles16 <= 1024 ? 8 : 4); }
+int64_t tiles_of(int64_t x) { return (x + 15) / 16; }
+
+// Order of the tiles of a launch of the exact path: whole blocks to one XCD (workgroup i runs on XCD i mod 8), whose L2 then
+// fetches a factor or gradient once for all tiles that read it; largest blocks first, to the least loaded XCD.  The list
+// holds the problems of its blocks one after the other, `nblocks` times the same number of them.  Gram matrices of 56 blocks at
+// r = 32 30 -> 22 us, G R^T 63 -> 56 us.  Launches of fewer tiles than three per compute unit keep their order: whole blocks
+// leave some XCDs idle (update of 7 small blocks 10.9 -> 13.8 us).
+void deal_to_xcds(GemmList& gl, size_t nblocks) {
+  constexpr int NXCD = 8;
+  if (nblocks < 2 || gl.probs.size() % nblocks != 0 || gl.tiles.size() < 768) return;
+  const size_t each = gl.probs.size() / nblocks;
+  std::vector<std::vector<GemmTile>> of(nblocks);
+  std::vector<double> cost(nblocks, 0.0);
+  for (const GemmTile& t : gl.tiles) {
+    const GemmProblem& p = gl.probs[t.prob];
+    of[t.prob / each].push_back(t);
+    cost[t.prob / each] += (double)p.K1 + p.K2 + p.K3;
+  }
+  std::vector<size_t> order(nblocks);
+  for (size_t i = 0; i < nblocks; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
+  std::vector<GemmTile> per[NXCD];
+  double load[NXCD] = {0};
+  for (size_t i : order) {
+    int x = 0;
+    for (int k = 1; k < NXCD; ++k) if (load[k] < load[x]) x = k;
+    per[x].insert(per[x].end(), of[i].begin(), of[i].end());
+    load[x] += cost[i];
+  }
+  size_t longest = 0;
+  for (auto& v : per) {
+    std::stable_sort(v.begin(), v.end(), [&](const GemmTile& a, const GemmTile& b) { return gl.probs[a.prob].K1 > gl.probs[b.prob].K1; });
+    longest = std::max(longest, v.size());
+  }
+  gl.tiles.clear();
+  for (size_t q = 0; q < longest; ++q)
+    for (int x = 0; x < NXCD; ++x) gl.tiles.push_back(q < per[x].size() ? per[x][q] : GemmTile{GEMM_TILE_NONE, 0, 0, 0});
 }
 
 GemmProblem problem(int M, int N) {
@@ -303,9 +352,45 @@ GemmProblem problem(int M, int N) {
 void add_update64(GemmList& gl, GemmProblem p, int32_t block) {
   p.Out = mat(SP_PARAM, block, 0, p.N, 1, DT_F32);
   p.tm = p.tn = UPD64_TILE / 16;
+  gl.steps = std::max(gl.steps, (p.K1 + 15) / 16 + (p.K2 + 15) / 16);
   add_problem(gl, p);
 }
+// ... and how many tiles along a row one workgroup walks: a longer walk costs the look-up of its problem and the staging of its
+// factor rows once, as long as the launch still holds three rounds of the four workgroups per compute unit.
+void walk_update64(GemmList& gl) {
+  const int nj = (int)std::min<int64_t>(8, std::max<int64_t>(1, (int64_t)gl.tiles.size() / (3 * 4 * 256)));
+  std::vector<GemmTile> out;
+  for (const GemmTile& t : gl.tiles) {
+    const int n = (gl.probs[t.prob].N + UPD64_TILE - 1) / UPD64_TILE;
+    if (t.tj % nj == 0) out.push_back(GemmTile{t.prob, t.ti, t.tj, std::min(nj, n - t.tj)});
+  }
+  gl.tiles.swap(out);
+}
 
+// The lists of the updates of a group, one per class of blocks, made as they are needed
+struct Update64Lists {
+  int list[UPD64_CLASSES];
+  Update64Lists() { for (int& l : list) l = -1; }
+  void add(adapm_ctx* c, const GemmProblem& p, int32_t block) {
+    const adapm_block_t& b = c->table[block];
+    const int cls = update64_class(p.N, std::max(p.K1, p.K2), b.grad_dtype == ADAPM_BF16, b.param_dtype == ADAPM_BF16, b.v_mode == ADAPM_V_ELEMENT);
+    if (list[cls] < 0) {
+      list[cls] = (int)c->gemms.size();
+      c->gemms.emplace_back();
+      c->gemms.back().cls = cls;
+    }
+    add_update64(c->gemms[list[cls]], p, block);
+  }
+  // cG, cC: the coefficients of G and of the m x n term in m^c
+  void finish(adapm_ctx* c, std::vector<Op>& seq, float cG, float cC) {
+    for (int l : list) {
+      if (l < 0) continue;
+      walk_update64(c->gemms[l]);
+      deal_to_xcds(c->gemms[l], c->gemms[l].probs.size());
+      seq.push_back(Op{OP_UPDATE64, l, cG, cC, "update_lowrank_f64"});
+    }
+  }
+};
 // most segments a Gram-type product over K columns is cut into (sizes the partial sums; a group may use fewer, longer ones)
 int gram_segments(int64_t K) {
   const int64_t nch = (K + 63) / 64;
@@ -320,6 +405,12 @@ std::vector<double> effective_step_sizes(int K) {
     if (eta != 0.0) out.push_back(eta);
   }
   return out;
+}
+
+// Exact path: the last GD iteration writes the new factors to the state, without a launch of their own.  The iteration that
+// copies the previous step's factors must be another one, and a re-gauge stores its own results.
+bool stores_direct(const adapm_hparams_t& hp) {
+  return hp.refresh_period_T <= 1 && effective_step_sizes(hp.refresh_iters_K).size() >= 2;
 }
 
 // Alg. 2 + eq. 3-4 for the low-rank blocks of one contraction path.
@@ -363,9 +454,17 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
     }
   }
   // Exact path: 32 x 32 tiles of the Gram matrices once they make four workgroups per compute unit, else 16 x 16
-  int64_t gram_tiles = 0;
-  for (int64_t i : ids) gram_tiles += 4ll * ((c->table[i].rank + 31) / 32) * ((c->table[i].rank + 31) / 32);
-  const bool gram_small = gram_tiles < 4 * 256;
+  int64_t gram_tiles = 0, gram16 = 0, upd16 = 0, regauge16 = 0;
+  for (int64_t i : ids) {
+    const adapm_block_t& b = c->table[i];
+    const int64_t rt = tiles_of(b.rank);
+    gram_tiles += 4ll * ((b.rank + 31) / 32) * ((b.rank + 31) / 32);
+    gram16 += 4 * rt * rt;
+    regauge16 += rt * (rt + 1) / 2;
+    upd16 += rt * (tiles_of(b.rows) + tiles_of(b.cols));
+  }
+  const int gram_waves = waves64(gram16), upd_waves = waves64(upd16), regauge_waves = waves64(regauge16);
+  const bool gram_small = gram_tiles < 4 * 256 || gram_waves > 4, upd_small = upd_waves > 4, regauge_small = regauge_waves > 4;
   // this group's lists
   const int grp = c->n_groups++;
   c->cp.emplace_back(); c->rub.emplace_back(); c->qt.emplace_back(); c->chol.emplace_back();
@@ -379,7 +478,10 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
     return (int)c->gemms.size() - 1;
   };
   std::vector<int> listA(n_eff), listB(n_eff);
-  for (int e = 0; e < n_eff; ++e) { listA[e] = new_list(fast); listB[e] = new_list(fast); }
+  for (int e = 0; e < n_eff; ++e) {
+    listA[e] = new_list(fast); listB[e] = new_list(fast);
+    c->gemms[listA[e]].waves = gram_waves; c->gemms[listB[e]].waves = upd_waves;
+  }
   const int gnorm0 = (int)c->gnorm.size();          // this path's normaliser lists, one per iteration
   if (hp.refresh_normalise) c->gnorm.resize(gnorm0 + n_eff);
   // MFMA path: per GD iteration the images of (R, L^T) and, per rank class, the stripe problems
@@ -395,16 +497,20 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
   // run once per group on a fraction of the machine.
   const bool group_regauge = hp.refresh_period_T > 1 && !fast;
   const int l_pre = (n_eff == 0 && group_regauge) ? new_list(fast) : -1;
-  const int l_epi = fast ? -1 : new_list(false);      // m x n term of eq. 3-4 (the MFMA path never forms it)
+  Update64Lists l_epi;                                // m x n term of eq. 3-4 (the MFMA path never forms it)
   const int l_gram = group_regauge ? new_list(false) : -1;
-  const int l_fin = (!fast && (group_regauge || n_eff > 0)) ? new_list(false) : -1;
+  if (l_gram >= 0) c->gemms[l_gram].waves = regauge_waves;
+  const int l_fin = (!fast && (group_regauge || (n_eff > 0 && !c->lay[ids[0]].direct))) ? new_list(false) : -1;
   for (int64_t i : ids) {
     const adapm_block_t& b = c->table[i];
     const Layout& L = c->lay[i];
     const int m = (int)b.rows, n = (int)b.cols, r = b.rank;
     const int gdt = b.grad_dtype == ADAPM_BF16 ? DT_BF16 : DT_F32;
     const Mat G = mat(SP_GRAD, (int32_t)i, 0, n, 1, gdt);
-    const Mat Lp = mat(SP_STATE, 0, L.sL, r, 1, DT_F32), Rp = mat(SP_STATE, 0, L.sR, n, 1, DT_F32);
+    Mat Lp = mat(SP_STATE, 0, L.sL, r, 1, DT_F32), Rp = mat(SP_STATE, 0, L.sR, n, 1, DT_F32);
+    // Exact path without a re-gauge: the first iteration leaves a copy of the previous step's factors in the scratch, and the
+    // last one writes the new ones to the state itself (all its other readers have the copy by then)
+    const bool direct = L.direct;
     auto T = [](const Mat& a) { Mat t = a; t.s0 = a.s1; t.s1 = a.s0; return t; };
     // Where the GD step rides on the stripe products, a workgroup reads and writes only the factor rows behind its own
     // stripe (everything else comes from the images), so the iterations after the first update one working copy in
@@ -520,15 +626,20 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
         p.A2 = Lc; p.B2 = T(Grr); p.K2 = r; p.a2 = e > 0 ? -eta : eta * b1 - eta;
         if (e > 0) { p.A3 = Lp; p.B3 = T(Gpr); p.K3 = r; p.a3 = eta * b1; }
         p.X = Lc; p.g = 1.0; p.Out = Ln; p.off_s = off_s;
-        add_problem(Bl, shape64(p, G64_KK));
+        if (direct && e == 0) { p.Out2 = mat(SP_WS, 0, L.wLp, r, 1, DT_F32); p.g2 = 1.0; }
+        if (direct && e + 1 == n_eff) { p.Out2 = mat(SP_STATE, 0, L.sL, r, 1, DT_F32); p.dup = 1; }
+        add_problem(Bl, shape64(p, G64_KK, upd_small));
         p = problem(r, n);
         p.A1 = T(Lc); p.B1 = G; p.K1 = m; p.a1 = eta * (1.0 - b1); p.scale_g = 1;
         p.A2 = T(Gll); p.B2 = Rc; p.K2 = r; p.a2 = e > 0 ? -eta : eta * b1 - eta;
         if (e > 0) { p.A3 = T(Glp); p.B3 = Rp; p.K3 = r; p.a3 = eta * b1; }
         p.X = Rc; p.g = 1.0; p.Out = Rn; p.off_s = off_s;
-        add_problem(Bl, shape64(p, G64_IJ));
+        if (direct && e == 0) { p.Out2 = mat(SP_WS, 0, L.wRp, n, 1, DT_F32); p.g2 = 1.0; }
+        if (direct && e + 1 == n_eff) { p.Out2 = mat(SP_STATE, 0, L.sR, n, 1, DT_F32); p.dup = 1; }
+        add_problem(Bl, shape64(p, G64_IJ, upd_small));
       }
       Lc = Ln; Rc = Rn;
+      if (direct && e == 0) { Lp = mat(SP_WS, 0, L.wLp, r, 1, DT_F32); Rp = mat(SP_WS, 0, L.wRp, n, 1, DT_F32); }
     }
     if (l_pre >= 0) {      // no effective iteration but an in-place re-gauge ahead: work on a copy
       p = problem(m, r); p.X = Lp; p.g = 1.0; p.Out = fL(0); add_problem(c->gemms[l_pre], p);
@@ -559,7 +670,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       } else {
         p.A1 = Lc; p.B1 = Rc; p.K1 = r; p.a1 = 1.0;
       }
-      add_update64(c->gemms[l_epi], p, (int32_t)i);
+      l_epi.add(c, p, (int32_t)i);
     }
     if (fast && hp.refresh_period_T > 1) {
       // the pass over all blocks that follows the last group: Gram matrix of the stored R in fp64, Cholesky, in place
@@ -574,7 +685,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       // product-preserving orthonormalisation of R, always in fp64
       const Mat G64 = mat(SP_WS, 0, L.wG64, r, 1, DT_F64), Cinv = mat(SP_WS, 0, L.wCinv, r, 1, DT_F64);
       p = problem(r, r); p.A1 = Rc; p.B1 = T(Rc); p.K1 = n; p.a1 = 1.0; p.Out = G64;
-      add_problem(c->gemms[l_gram], shape64(p, G64_KK, r <= 16), true);      // the Cholesky factorisation reads the lower triangle only
+      add_problem(c->gemms[l_gram], shape64(p, G64_KK, r <= 16 || regauge_small), true);      // the Cholesky factorisation reads the lower triangle only
       c->chol[chol_id].h.push_back(CholItem{L.wG64, L.wCinv, r, 0});
       // C^-1 and C are lower triangular
       p = problem(r, n); p.A1 = Cinv; p.B1 = Rc; p.K1 = r; p.a1 = 1.0; p.tri = 1; p.Out = Rp; add_problem(c->gemms[l_fin], shape64(p, G64_KJ));
@@ -585,7 +696,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
           c->cp[grp].h.push_back(CopyItem{Lc.ref, Lp.ref, f, (int32_t)std::min<int64_t>(COPY_CHUNK, (int64_t)m * r - f), 0});
         for (int64_t f = 0; f < (int64_t)r * n; f += COPY_CHUNK)
           c->cp[grp].h.push_back(CopyItem{Rc.ref, Rp.ref, f, (int32_t)std::min<int64_t>(COPY_CHUNK, (int64_t)r * n - f), 0});
-      } else {
+      } else if (!direct) {
         p = problem(m, r); p.X = Lc; p.g = 1.0; p.Out = Lp; add_problem(c->gemms[l_fin], p);
         p = problem(r, n); p.X = Rc; p.g = 1.0; p.Out = Rp; add_problem(c->gemms[l_fin], p);
       }
@@ -636,6 +747,11 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       seq.push_back(Op{gk, listB[e], 0, 0, fast ? "alg2_update_mfma" : "alg2_update_f64"});
   }
   if (l_pre >= 0) seq.push_back(Op{gk, l_pre, 0, 0, "copy_factors"});
+  if (!fast) {
+    for (int e = 0; e < n_eff; ++e) { deal_to_xcds(c->gemms[listA[e]], ids.size()); deal_to_xcds(c->gemms[listB[e]], ids.size()); }
+    for (int l : {l_pre, l_gram, l_fin})
+      if (l >= 0) deal_to_xcds(c->gemms[l], ids.size());
+  }
   const float cG = hp.bias_correction ? 1.f : 0.f;
   const float cC = hp.bias_correction ? (float)(b1 / (1.0 - b1)) : 1.f;
   if (fast) {
@@ -672,7 +788,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       seq.push_back(Op{OP_REFRESH_UPDATE, ru0 + cls, cG, cC, names[(cls >> 1) % 3], grp});
     }
   } else {
-    seq.push_back(Op{OP_UPDATE64, l_epi, cG, cC, "update_lowrank_f64"});
+    l_epi.finish(c, seq, cG, cC);
   }
   if (l_gram >= 0) {
     seq.push_back(Op{OP_GEMM, l_gram, 0, 0, "regauge_gram_f64"});
@@ -692,7 +808,11 @@ void plan_lowrank_project_f64(adapm_ctx* c, const std::vector<int64_t>& ids) {
   const double b1 = hp.beta1;
   if (ids.empty()) return;
   auto new_list = [&]() { c->gemms.emplace_back(); return (int)c->gemms.size() - 1; };
-  const int l_p = new_list(), l_c = new_list();
+  const int l_p = new_list();
+  Update64Lists l_c;
+  int64_t proj16 = 0;
+  for (int64_t i : ids) proj16 += tiles_of(c->table[i].rank) * tiles_of(c->table[i].rows);
+  const int waves = c->gemms[l_p].waves = waves64(proj16);
   for (int64_t i : ids) {
     const adapm_block_t& b = c->table[i];
     const Layout& L = c->lay[i];
@@ -707,12 +827,13 @@ void plan_lowrank_project_f64(adapm_ctx* c, const std::vector<int64_t>& ids) {
     p = problem(m, r); p.A1 = G; p.B1 = Qt; p.K1 = n; p.a1 = 1.0; p.scale_g = 1; p.X = Ls;
     p.Out = D; p.g = b1; p.s0 = hp.bias_correction ? -b1 : 1.0 - b1;
     p.Out2 = Ls; p.g2 = b1; p.s2 = 1.0 - b1;
-    add_problem(c->gemms[l_p], shape64(p, G64_KK));
-    p = problem(m, n); p.A1 = D; p.B1 = Q; p.K1 = r; p.a1 = 1.0; add_update64(c->gemms[l_c], p, (int32_t)i);
+    add_problem(c->gemms[l_p], shape64(p, G64_KK, waves > 4));
+    p = problem(m, n); p.A1 = D; p.B1 = Q; p.K1 = r; p.a1 = 1.0; l_c.add(c, p, (int32_t)i);
   }
+  deal_to_xcds(c->gemms[l_p], ids.size());
   std::vector<Op>& seq = c->seq_project;
   seq.push_back(Op{OP_GEMM, l_p, 0, 0, "project_f64"});
-  seq.push_back(Op{OP_UPDATE64, l_c, hp.bias_correction ? 1.f : 0.f, 1.f, "update_lowrank_f64"});
+  l_c.finish(c, seq, hp.bias_correction ? 1.f : 0.f, 1.f);
 }
 
 // step with R held, MFMA path: Q^T split once, then one fused launch per rank class.  Stripes of one
@@ -800,6 +921,7 @@ size_t layout_block_scratch(const adapm_block_t& b, const adapm_hparams_t& hp, L
   // F64 path: every intermediate of a step stays in fp64, only the state is rounded to fp32
   const size_t es = fast ? 4 : 8;
   T.wLa = walloc(es * m * r); T.wRa = walloc(es * r * n);
+  if (L.direct) { T.wLp = walloc(4 * m * r); T.wRp = walloc(4 * r * n); }
   // the second working copy of the factors: only where the GD step runs as batched GEMMs (see plan_lowrank_refresh)
   if (!stripes) { T.wLb = walloc(es * m * r); T.wRb = walloc(es * r * n); }
   // G R^T and L^T G: blocks whose GD step rides on the stripe products never store them
@@ -941,7 +1063,16 @@ size_t choose_stripes(adapm_ctx* c) {
     L.stripes = true;
     L.stripes = block_scratch(c, i, false) <= limit;
   }
-  const size_t at = fixed_part(c).scratch_at, budget = scratch_budget(c, at, false);
+  const size_t at = fixed_part(c).scratch_at;
+  // the copies that spare the exact path its launch for the store are scratch too: without them where they would not fit
+  for (Layout& L : c->lay) L.direct = L.path == PATH_F64 && stores_direct(c->hp);
+  size_t budget = scratch_budget(c, at, false);
+  if (in_static && budget > STATIC_SCRATCH_BYTES - at) budget = STATIC_SCRATCH_BYTES - at;
+  bool fits = true;
+  for (size_t i = 0; i < c->table.size(); ++i) fits = fits && (!c->lay[i].direct || block_scratch(c, i, false) <= budget);
+  if (fits) return budget;
+  for (Layout& L : c->lay) L.direct = false;
+  budget = scratch_budget(c, at, false);
   return in_static ? std::min(budget, STATIC_SCRATCH_BYTES - at) : budget;
 }
 
@@ -1276,14 +1407,14 @@ adapm_status_t run_op(adapm_ctx* c, const Op& op, Bases& bs, const StepScalars& 
       break;
     case OP_GEMM: {
       const GemmList& g = c->gemms[op.index];
-      launch_gemm64(g.d_probs, g.d_tiles, (int64_t)g.tiles.size(), bs, s);
+      launch_gemm64(g.waves, g.d_probs, g.d_tiles, (int64_t)g.tiles.size(), bs, s);
       break;
     }
     case OP_UPDATE64: {
       StepScalars x = sc;
       x.cG = op.cG; x.cC = op.cC;
       const GemmList& g = c->gemms[op.index];
-      launch_update64(g.d_probs, g.d_tiles, (int64_t)g.tiles.size(), c->blocks.d, bs, x, s);
+      launch_update64(g.cls, g.d_probs, g.d_tiles, (int64_t)g.tiles.size(), g.steps, c->blocks.d, bs, x, s);
       break;
     }
     case OP_GEMM_MFMA: {

@@ -90,14 +90,17 @@ struct GemmProblem {
   int32_t tri;       // fp64 kernel: 1 = A1 is lower triangular, 2 = B1 is lower triangular (zero part of the contraction skipped)
   int64_t off_s;     // >= 0: workspace offset of the device scalar s (double); -1: s = s0
   double s0;
-  // fp64 kernel, optional second result of the same sums: Out2 = g2 X + s2 (...); may be X itself
+  // fp64 kernel, optional second result of the same sums: Out2 = g2 X + s2 (...), or with dup the first one again; may be X itself
   Mat Out2;
   double g2, s2;
+  int32_t dup, pad2;
 };
 
+constexpr uint32_t GEMM_TILE_NONE = 0xffffffffu;
 struct GemmTile {
-  uint32_t prob;
+  uint32_t prob;     // GEMM_TILE_NONE: padding (fp64 kernels)
   int32_t ti, tj;    // output tile coordinates
+  int32_t nj;        // update of the exact path: tiles from tj on that the workgroup walks
 };
 
 // ---------------------------------------------------------------------------
@@ -287,7 +290,7 @@ struct RegaugeItem {
 };
 
 // launchers (defined next to their kernels)
-void launch_gemm64(const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, Bases b, hipStream_t s);
+void launch_gemm64(int waves, const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, Bases b, hipStream_t s);
 void launch_vstat(const BlockDev* blocks, const VsItem* items, int64_t nitems, double* partials, Bases b,
                   float beta2, hipStream_t s);
 void launch_vfinal(const BlockDev* blocks, const VfItem* items, int64_t nitems, const double* partials, Bases b,
@@ -298,7 +301,9 @@ void launch_update_grouped(const BlockDev* blocks, const GrpItem* items, int64_t
 void launch_gradnorm_final(const double* partials, int64_t nparts, float max_norm, float* out, hipStream_t s);
 // update of the low-rank blocks of the exact path (k_update64.hip): 64 x 64 tiles of problems whose sums are the m x n term
 constexpr int UPD64_TILE = 64;
-void launch_update64(const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, const BlockDev* blocks, Bases b,
+int update64_class(int64_t N, int64_t K, bool g16, bool w16, bool vel);
+constexpr int UPD64_CLASSES = 9;
+void launch_update64(int cls, const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, int steps, const BlockDev* blocks, Bases b,
                      StepScalars sc, hipStream_t s);
 void launch_update(const BlockDev* blocks, const EwItem* items, int64_t nitems, Bases b, StepScalars sc,
                    hipStream_t s);

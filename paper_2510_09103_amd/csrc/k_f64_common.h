@@ -22,6 +22,7 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 struct __attribute__((packed, aligned(8))) f64x2_a8 { double x, y; };
 struct __attribute__((packed, aligned(4))) f32x2_a4 { float x, y; };
 struct __attribute__((packed, aligned(2))) u32_a2 { uint32_t x; };
+struct __attribute__((packed, aligned(2))) u32x2_a2 { uint32_t x, y; };
 
 __device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
@@ -110,9 +111,13 @@ struct RawVec<DT_BF16, N> {
         const u32x4_a2 q = reinterpret_cast<const u32x4_a2*>(p)[i];
         r[4 * i] = q.x; r[4 * i + 1] = q.y; r[4 * i + 2] = q.z; r[4 * i + 3] = q.w;
       }
+    } else if constexpr (N == 4) {
+      const u32x2_a2 q = *reinterpret_cast<const u32x2_a2*>(p);
+      r[0] = q.x; r[1] = q.y;
     } else if constexpr (N == 2) {
       r[0] = reinterpret_cast<const u32_a2*>(p)->x;
     } else {
+      static_assert(N == 1, "lengths that occur");
       r[0] = *reinterpret_cast<const uint16_t*>(p);
     }
   }
@@ -136,7 +141,7 @@ struct Operand {
   static constexpr int ES = elem_bytes(DT);
   RawVec<DT, KFAST ? V : T> q[KFAST ? T : V];
   struct Where {                       // fixed per workgroup tile
-    const char* p[KFAST ? T : 1];      // KFAST: row of each tile; otherwise the first of the lane's T columns
+    const char* p[KFAST ? T : 1];      // KFAST: row of each tile; otherwise the first of the lane's T columns; moved along by step()
     int64_t sk;                        // bytes from k to k + 1
     bool shift;                        // !KFAST, T = 2: the lane's last column is the last one that exists
   };
@@ -160,17 +165,23 @@ struct Operand {
     }
     return w;
   }
-  // k: this lane's first value of the contraction index
-  __device__ __forceinline__ void load(const Where& w, int k) {
+  // on by k values
+  static __device__ __forceinline__ void step(Where& w, int k) {
+#pragma unroll
+    for (int t = 0; t < (KFAST ? T : 1); ++t) w.p[t] += (int64_t)k * w.sk;
+  }
+  // from this lane's first value of the contraction index, where w stands
+  __device__ __forceinline__ void load(const Where& w) {
     if constexpr (KFAST) {
 #pragma unroll
-      for (int t = 0; t < T; ++t) q[t].load(w.p[t] + (int64_t)k * ES);
+      for (int t = 0; t < T; ++t) q[t].load(w.p[t]);
     } else {
 #pragma unroll
-      for (int v = 0; v < V; ++v) q[v].load(w.p[0] + (int64_t)(k + v) * w.sk);
+      for (int v = 0; v < V; ++v) q[v].load(w.p[0] + v * w.sk);
     }
   }
-  // the same for a step that ends at or beyond ke: values past the end read a valid element and become zero
+  // a step that ends at or beyond ke, k: this lane's first value of it (w stands at the row's start): values past the end read
+  // a valid element and become zero
   __device__ __forceinline__ void load_edge(const Where& w, int k, int ke) {
     if constexpr (KFAST) {
 #pragma unroll

@@ -207,6 +207,18 @@ def test_exact_path_at_the_edges_of_its_tiles(gd, many, T):
     run(exact_edges_table(gd, many), 4, dict(T=T), tol_state=TOL32, tol_param=TOL32)
 
 
+@pytest.mark.parametrize("copies", [1, 12, 30])
+@pytest.mark.parametrize("hp", [dict(T=1), dict(T=2), dict(T=1, K=2), dict(T=1, K=3, normalise=1)])
+def test_exact_path_for_every_number_of_waves_on_a_tile(copies, hp):
+    """Launches of few output tiles split a contraction over 16 or 8 waves, the others over 4 and deal whole blocks to an XCD;
+    with two GD iterations or more the last one writes the factors to the state, with one (K = 2) a launch of its own.  Sums in
+    fp64 whatever the split: the fp32 tolerance."""
+    sizes = [(17, 33, 1), (33, 17, 17), (64, 31, 31), (97, 63, 33)]
+    wl = WL.Workload("exact_waves", tuple(BlockSpec(f"b{k}_{m}x{n}_r{r}", m, n, "f32", "bf16" if k % 2 else "f32", "lowrank", r, "element", 1, 1.0, 0.1)
+                                          for k in range(copies) for m, n, r in sizes), steps=3, seed=43, signal_rank=24)
+    run(wl, 3, hp, tol_state=TOL32, tol_param=TOL32)
+
+
 @pytest.mark.parametrize("pd,gd,vm,clip", [("f32", "bf16", "element", None), ("bf16", "f32", "rowgroup", 0.5), ("bf16", "bf16", "element", None),
                                            ("f32", "f32", "whole", None)])
 @pytest.mark.parametrize("hp", [dict(T=1), dict(T=3), dict(T=2, bias_correction=0), dict(T=2, K=1)])
