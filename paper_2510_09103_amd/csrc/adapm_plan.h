@@ -221,7 +221,7 @@ struct GramItem {          // one workgroup: X S^T and S S^T, both r x r, from t
   int32_t c0, c1, seg, nseg;
   int64_t off_part;
 };
-struct GramFinItem {       // one workgroup: the sum of the nseg partial results of one pair of products -> results and images
+struct GramFinItem {       // eight workgroups of 16 rows each (rank class 128): the sum of the nseg partial results of one pair of products -> results and images
   int64_t off_part;
   int64_t off_out_ss;
   int64_t off_img_xs, off_img_ss;

@@ -1700,7 +1700,7 @@ __global__ __launch_bounds__(256) void qf_image_kernel(const ImgItem* __restrict
 // (chunks c0 .. c1 - 1): a segment leaves its partial sums for gram_finish_kernel.
 template <int RT>
 __device__ __forceinline__ void gram_emit(const float* Mss, const float* Mxs, const Bases& bs, int64_t off_out_ss,
-                                          int64_t off_img_ss, int64_t off_img_xs, int r, bool same, int nthreads);
+                                          int64_t off_img_ss, int64_t off_img_xs, int r, bool same);
 
 template <int RT>
 __device__ __forceinline__ void gram_body(const GramItem& it, const Bases& bs, unsigned char* smem) {
@@ -1849,7 +1849,7 @@ __device__ __forceinline__ void gram_body(const GramItem& it, const Bases& bs, u
         }
   }
   __syncthreads();
-  gram_emit<RT>(Mss, Mxs, bs, it.off_out_ss, it.off_img_ss, it.off_img_xs, it.r, same, 512);
+  gram_emit<RT>(Mss, Mxs, bs, it.off_out_ss, it.off_img_ss, it.off_img_xs, it.r, same);
 }
 
 // Results of a pair of Gram-type products, complete in LDS as [R][R] fp32 each: S S^T itself where somebody reads it (the
@@ -1857,15 +1857,15 @@ __device__ __forceinline__ void gram_body(const GramItem& it, const Bases& bs, u
 // qf_image_kernel writes), 64-wide chunks of the contraction index k: lane l of a piece holds result[64 c + 16 kk + 8 (l / 32) .. + 7][32 tile + l % 32].
 template <int RT>
 __device__ __forceinline__ void gram_emit(const float* Mss, const float* Mxs, const Bases& bs, int64_t off_out_ss,
-                                          int64_t off_img_ss, int64_t off_img_xs, int r, bool same, int nthreads) {
+                                          int64_t off_img_ss, int64_t off_img_xs, int r, bool same) {
   constexpr int R = 32 * RT;
   constexpr int QF = qf_chunk_bytes(R);
   if (off_out_ss >= 0) {
     float* __restrict__ Oss = reinterpret_cast<float*>(bs.ws + off_out_ss);
-    for (int id = threadIdx.x; id < r * r; id += nthreads) Oss[id] = Mss[(id / r) * R + id % r];
+    for (int id = threadIdx.x; id < r * r; id += 512) Oss[id] = Mss[(id / r) * R + id % r];
   }
   const int nk2 = (r + BK - 1) / BK;
-  for (int p = threadIdx.x; p < (same ? 1 : 2) * nk2 * (BK / 16) * RT * 64; p += nthreads) {   // same: one image serves both
+  for (int p = threadIdx.x; p < (same ? 1 : 2) * nk2 * (BK / 16) * RT * 64; p += 512) {   // same: one image serves both
     const int ln = p & 63, rest = p >> 6, tile = rest % RT, kk = (rest / RT) % (BK / 16), kc = (rest / (RT * (BK / 16))) % nk2;
     const int which = rest / (RT * (BK / 16) * nk2);
     const float* M = (which ? Mxs : Mss) + 32 * tile + (ln & 31);
@@ -1891,56 +1891,75 @@ __global__ __launch_bounds__(512) void gram_kernel(const GramItem* __restrict__ 
 }
 
 // Sum of the partial results that the segments of a long contraction left (fixed order: segment 0, 1, ...), then the
-// same results and images a single-segment workgroup writes itself.
+// same results and images a single-segment workgroup writes itself.  One workgroup per 16 rows of the two r x r results: the
+// 16 values of the contraction index that a k-step of the images holds.  (One workgroup per pair of results, the sums of all
+// 128 rows in its registers, kept 24 CUs busy with half a megabyte each and spilled: 31 us a launch at 12 layers of the
+// 1600 / 6400 table, 8 now; 28 -> 7 at 16 layers without a re-gauge.)
+constexpr int GF_ROWS = 16, GF_NT = 256;
 template <int RT>
-__device__ __forceinline__ void gram_finish_body(const GramFinItem& it, const Bases& bs, unsigned char* smem) {
-  constexpr int R = 32 * RT;
-  float* const Mss = reinterpret_cast<float*>(smem);
-  float* const Mxs = Mss + R * R;
-  // 16 bytes per load, every load of a thread independent of the others: the launch is a few latencies long
-  const float4* __restrict__ part = reinterpret_cast<const float4*>(bs.ws + it.off_part);
-  constexpr int Q = R * R / 4;                       // float4 per matrix
-  constexpr int PER = (Q + 511) / 512;               // per thread: 8 at R = 128
-  float4 a[PER], x[PER];
+__device__ __forceinline__ void gram_finish_body(const GramFinItem& it, int part, const Bases& bs, float* smem) {
+  constexpr int R = 32 * RT, QF = qf_chunk_bytes(R), LD = R + 1;
+  const int tid = threadIdx.x, row0 = GF_ROWS * part;
+  // rows of the images that the results have (rank class 32: half a chunk) are zeros beyond them
+  const int r = it.r;
+  if (row0 >= (r + BK - 1) / BK * BK) return;        // the images end with the chunk that holds row r - 1
+  constexpr int Q = GF_ROWS * R / 4;                 // float4 per matrix
+  constexpr int PER = Q / GF_NT > 0 ? Q / GF_NT : 1; // per thread: 2 at R = 128
+  const int nm = it.same ? 1 : 2;                    // same: one product serves both results
+  const float4* __restrict__ src = reinterpret_cast<const float4*>(bs.ws + it.off_part) + row0 * R / 4;
+  float4 a[2][PER];
 #pragma unroll
-  for (int u = 0; u < PER; ++u) a[u] = x[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int sg = 0; sg < it.nseg; ++sg) {
-    float4 pa[PER], px[PER];
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int u = 0; u < PER; ++u) a[m][u] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int sg = 0; sg < (row0 < R ? it.nseg : 0); ++sg) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        const int id = tid + GF_NT * u;
+        if (id < Q && m < nm) {
+          const float4 p = src[(int64_t)(2 * sg + m) * (R * R / 4) + id];
+          a[m][u].x += p.x; a[m][u].y += p.y; a[m][u].z += p.z; a[m][u].w += p.w;
+        }
+      }
+  }
+  float* const M = smem;                             // [2][16][LD]
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const int id = threadIdx.x + 512 * u;
-      if (id < Q) {
-        pa[u] = part[(int64_t)sg * 2 * Q + id];
-        if (!it.same) px[u] = part[(int64_t)sg * 2 * Q + Q + id];
+      const int id = tid + GF_NT * u;
+      if (id < Q && m < nm) {
+        float* o = M + (m * GF_ROWS + id / (R / 4)) * LD + (id % (R / 4)) * 4;
+        o[0] = a[m][u].x; o[1] = a[m][u].y; o[2] = a[m][u].z; o[3] = a[m][u].w;
       }
     }
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int id = threadIdx.x + 512 * u;
-      if (id < Q) {
-        a[u].x += pa[u].x; a[u].y += pa[u].y; a[u].z += pa[u].z; a[u].w += pa[u].w;
-        if (!it.same) { x[u].x += px[u].x; x[u].y += px[u].y; x[u].z += px[u].z; x[u].w += px[u].w; }
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int id = threadIdx.x + 512 * u;
-    if (id < Q) {
-      reinterpret_cast<float4*>(Mss)[id] = a[u];
-      reinterpret_cast<float4*>(Mxs)[id] = it.same ? a[u] : x[u];
-    }
-  }
   __syncthreads();
-  gram_emit<RT>(Mss, Mxs, bs, it.off_out_ss, it.off_img_ss, it.off_img_xs, it.r, it.same != 0, 512);
+  if (it.off_out_ss >= 0) {
+    float* __restrict__ Oss = reinterpret_cast<float*>(bs.ws + it.off_out_ss);
+    for (int id = tid; id < GF_ROWS * r; id += GF_NT)
+      if (row0 + id / r < r) Oss[(row0 + id / r) * r + id % r] = M[(id / r) * LD + id % r];
+  }
+  const int kc = row0 / BK, kk = (row0 % BK) / 16;
+  for (int p = tid; p < nm * RT * 64; p += GF_NT) {
+    const int ln = p & 63, tile = (p >> 6) % RT, which = (p >> 6) / RT;
+    const float* src = M + (which * GF_ROWS + 8 * (ln >> 5)) * LD + 32 * tile + (ln & 31);
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) split_pair(src[(2 * e) * LD], src[(2 * e + 1) * LD], h[e], l[e]);
+    char* dst = bs.ws + (which ? it.off_img_xs : it.off_img_ss) + (int64_t)kc * QF + ((int64_t)((kk * RT + tile) * 2) * 64 + ln) * 16;
+    *reinterpret_cast<uint4*>(dst) = make_uint4(h[0], h[1], h[2], h[3]);
+    *reinterpret_cast<uint4*>(dst + 1024) = make_uint4(l[0], l[1], l[2], l[3]);
+  }
 }
 
-__global__ __launch_bounds__(512) void gram_finish_kernel(const GramFinItem* __restrict__ items, Bases bs) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * 128 * 128 * 4];
+__global__ __launch_bounds__(GF_NT) void gram_finish_kernel(const GramFinItem* __restrict__ items, Bases bs) {
+  __shared__ float smem[2 * GF_ROWS * (128 + 1)];
   const GramFinItem it = items[blockIdx.x];
-  if (it.rc == 32) gram_finish_body<1>(it, bs, smem);
-  else if (it.rc == 64) gram_finish_body<2>(it, bs, smem);
-  else gram_finish_body<4>(it, bs, smem);
+  if (it.rc == 32) gram_finish_body<1>(it, blockIdx.y, bs, smem);
+  else if (it.rc == 64) gram_finish_body<2>(it, blockIdx.y, bs, smem);
+  else gram_finish_body<4>(it, blockIdx.y, bs, smem);
 }
 
 template <int RT>
@@ -1982,7 +2001,7 @@ void launch_gram(const GramItem* items, int64_t nitems, Bases b, hipStream_t s) 
 
 void launch_gram_finish(const GramFinItem* items, int64_t nitems, Bases b, hipStream_t s) {
   if (nitems <= 0) return;
-  hipLaunchKernelGGL(gram_finish_kernel, dim3((unsigned)nitems), dim3(512), 0, s, items, b);
+  hipLaunchKernelGGL(gram_finish_kernel, dim3((unsigned)nitems, 128 / GF_ROWS), dim3(GF_NT), 0, s, items, b);
 }
 
 void launch_qt_image(const ImgItem* items, int64_t nitems, Bases b, hipStream_t s) {

@@ -272,6 +272,16 @@ def test_orthonormalisation_for_every_number_of_rank_steps(ranks):
         assert float((ortho["L"] @ ortho["R"] - want).norm()) <= 1e-6 * float(want.norm()), b.name
 
 
+@pytest.mark.parametrize("hp", [dict(T=1), dict(T=2), dict(T=1, normalise=1)])
+def test_sums_of_gram_segments_in_every_rank_class(hp):
+    """Contractions of more than 25 chunks of 64 columns are cut into segments whose partial r x r sums a second launch adds, 16
+    rows to a workgroup: ranks inside, at the end of and beyond a group of 16 rows and a chunk, in all three rank classes."""
+    wl = WL.Workload("gram_segments", tuple(BlockSpec(f"b{m}x{n}_r{r}", m, n, "bf16", "bf16", "lowrank", r, "element", 1, 1.0, 0.1)
+                                            for m, n, r in [(136, 1704, 15), (1701, 72, 32), (72, 1664, 33), (136, 1704, 64), (136, 1800, 65), (1668, 136, 113),
+                                                            (136, 3304, 128)]), steps=3, seed=47, signal_rank=24)
+    run(wl, 3, hp, tol_state=TOLX, tol_param=TOLX)
+
+
 def random_table(rng, case):
     """A few low-rank bf16-gradient blocks with random sizes (mostly multiples of 8, rows of whole vectors; otherwise any
     size, which the stripe products finish behind their loops), ranks on and between the class and vector boundaries, every
