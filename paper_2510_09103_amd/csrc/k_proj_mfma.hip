@@ -771,7 +771,7 @@ __global__ __launch_bounds__(NT, 1) void proj_kernel(const ProjItem* __restrict_
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const unsigned e = eoff[i] + (unsigned)(pj * BK);
-      gq[i] = buf_load16(rG, ok ? e * 2u : OOB);
+      gq[i] = buf_load16_last(rG, ok ? e * 2u : OOB);
 #pragma unroll
       for (int k = 0; k < WV; ++k) wq[i][k] = buf_load16(rW, ok ? e * WE + 16u * k : OOB);
       if (VEL) {
@@ -1281,7 +1281,7 @@ __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* _
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const unsigned e = at(h, s);
-        g[h] = buf_load16(rG, ok ? e * 2u : OOB);
+        g[h] = buf_load16_last(rG, ok ? e * 2u : OOB);
 #pragma unroll
         for (int k = 0; k < WV; ++k) w[h][k] = buf_load16(rW, ok ? e * WE + 16u * k : OOB);
       }
