@@ -141,7 +141,7 @@ struct adapm_ctx {
   std::vector<DevList<GramItem>> gram;  //   ... per GD iteration: the four r x r Gram-type products, from the images, in pairs that share one
   std::vector<DevList<GnormItem>> gnorm; // optional scale-normalised Alg. 2: per (path, GD iteration) the normalisers
   // per group of low-rank blocks (a group runs Alg. 2 from start to end in one region of scratch, see build_plan):
-  std::vector<DevList<CopyItem>> cp;    // T = 1, MFMA path: the factors Alg. 2 leaves in the workspace -> state
+  std::vector<DevList<CopyItem>> cp;    // MFMA path: R from the workspace to the state, where the stripes cannot write it there
   std::vector<DevList<RuBlockDev>> rub; // fused update after Alg. 2 (MFMA path): blocks, images of R^T, stripes
   std::vector<DevList<ImgItem>> qt;
   std::vector<DevList<ProjItem>> ru;    //   12 per group: (rank class 32 / 64 / 128) x (fp32 / bf16 parameters) x (blockwise / per-element v)
@@ -522,6 +522,12 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
     const Mat Grr = mat(SP_WS, 0, L.wGrr, r, 1, idt), Gpr = mat(SP_WS, 0, L.wGpr, r, 1, idt);
     const Mat Gll = mat(SP_WS, 0, L.wGll, r, 1, idt), Glp = mat(SP_WS, 0, L.wGlp, r, 1, idt);
     Mat Lc = Lp, Rc = Rp;
+    // MFMA path: the factors reach the state without a copy.  The last iteration's stripes of G^T write R there, each the columns
+    // whose old values it alone has read; the update, which still reads L', writes L.  Rows that are no whole vectors need the old
+    // columns of R in the update, and blocks on the GEMMs read all of R everywhere: theirs is copied.  Copying both factors of every
+    // block took 247 us of a literal step of 48 layers of 1600 / 6400 at r = 128 (now 0; the step 15.54 -> 15.17 ms), 184 us of
+    // 24 layers of 2048 / 5461 (now 33), 51 us of 24 layers of 1024 / 4096 at r = 64 (now 0).
+    const bool r_direct = L.stripes && n % 8 == 0;
     GemmProblem p;
     for (int e = 0; e < n_eff; ++e) {
       const double eta = etas[e];
@@ -572,13 +578,13 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
         sp.c1 = (float)-eta; sp.c2 = (float)(eta * b1); sp.cp = (float)(eta * (1.0 - b1));
         sp.a = G.ref; sp.transpose_out = 0; sp.off_img = iR;
         if (e == 0 && v_fusable(b)) { sp.v_rows = b.v_group_rows; sp.off_v = L.sv; sp.beta2 = hp.beta2; }
-        sp.x_cur = Lc.ref; sp.x_prev = Lp.ref; sp.off_b1 = L.wB[0]; sp.off_b2 = L.wB[1]; sp.off_out = Ln.ref.off;
+        sp.x_cur = Lc.ref; sp.x_prev = Lp.ref; sp.off_b1 = L.wB[0]; sp.off_b2 = L.wB[1]; sp.out = Ln.ref;
         sp.off_next = iLn; sp.off_timg = -1; sp.off_timg_prev = -1;
         c->sprob.h.push_back(sp);
         swork[3 * e + cls].push_back(StripeWork{(int)c->sprob.h.size() - 1, m, n});
         sp.M = n; sp.K = m; sp.transpose_out = 1; sp.off_img = iL;
         sp.v_rows = 0;
-        sp.x_cur = Rc.ref; sp.x_prev = Rp.ref; sp.off_b1 = L.wB[2]; sp.off_b2 = L.wB[3]; sp.off_out = Rn.ref.off;
+        sp.x_cur = Rc.ref; sp.x_prev = Rp.ref; sp.off_b1 = L.wB[2]; sp.off_b2 = L.wB[3]; sp.out = r_direct && e + 1 == n_eff ? Rp.ref : Rn.ref;
         sp.off_next = iRn;
         sp.off_timg = e + 1 == n_eff ? L.wT2 : -1;     // the last iteration leaves the image of R_t^T for the fused update
         sp.off_timg_prev = (e == 0 && hp.bias_correction) ? L.wT1 : -1;   // ... the first one that of R_{t-1}^T
@@ -655,6 +661,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       else { d.v_kind = 2; d.v_group_rows = b.v_mode == ADAPM_V_WHOLE ? (int32_t)b.rows : b.v_group_rows; }
       d.param_dtype = b.param_dtype; d.lr_scale = b.lr_scale; d.wd = b.weight_decay;
       d.a1 = hp.bias_correction ? 1.f : 0.f; d.a2 = hp.bias_correction ? -1.f : 1.f;
+      d.store_l = n_eff > 0 ? 1 : 0;
       d.l1 = Lp.ref; d.l2 = Lc.ref; d.q1 = Rp.ref; d.q2 = Rc.ref; d.off_img1 = L.wT1; d.off_img2 = L.wT2; d.off_v = L.sv;
       c->rub[grp].h.push_back(d);
       for (int ch = 0; ch < (n + 63) / 64; ++ch) {
@@ -692,10 +699,9 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       p = problem(m, r); p.A1 = Lc; p.B1 = G64; p.K1 = r; p.a1 = 1.0; p.tri = 2; p.Out = Lp; add_problem(c->gemms[l_fin], shape64(p, G64_KJ));
     } else if (n_eff > 0) {
       if (fast) {
-        for (int64_t f = 0; f < (int64_t)m * r; f += COPY_CHUNK)
-          c->cp[grp].h.push_back(CopyItem{Lc.ref, Lp.ref, f, (int32_t)std::min<int64_t>(COPY_CHUNK, (int64_t)m * r - f), 0});
-        for (int64_t f = 0; f < (int64_t)r * n; f += COPY_CHUNK)
-          c->cp[grp].h.push_back(CopyItem{Rc.ref, Rp.ref, f, (int32_t)std::min<int64_t>(COPY_CHUNK, (int64_t)r * n - f), 0});
+        if (!r_direct)
+          for (int64_t f = 0; f < (int64_t)r * n; f += COPY_CHUNK)
+            c->cp[grp].h.push_back(CopyItem{Rc.ref, Rp.ref, f, (int32_t)std::min<int64_t>(COPY_CHUNK, (int64_t)r * n - f), 0});
       } else if (!direct) {
         p = problem(m, r); p.X = Lc; p.g = 1.0; p.Out = Lp; add_problem(c->gemms[l_fin], p);
         p = problem(r, n); p.X = Rc; p.g = 1.0; p.Out = Rp; add_problem(c->gemms[l_fin], p);

@@ -182,7 +182,7 @@ struct StripeProb {
   int32_t transpose_out;   // 0: Out is M x r (row stride r); 1: Out is r x M (row stride M)
   int32_t rc, upd;         // rank class of the image: 32, 64 or 128 >= r; upd: the factor update of Alg. 2 follows
   int64_t off_img;         // workspace: fragment image of Q
-  int64_t off_out;         // workspace: fp32 result
+  Ref out;                 // fp32 result
   // upd != 0: Out = X + s (c1 X B1 + c2 X' B2 + cp A Q^T), the GD step of Alg. 2 on the factor X (X' = the factor of
   // the previous step), all three in the layout of Out; B1, B2 = r x r matrices given as fragment images of their
   // transposes (image row a, column k = B[k][a]); s = the double at workspace offset off_s (1 if off_s < 0)
@@ -256,6 +256,7 @@ struct RuBlockDev {
   int32_t param_dtype;
   float lr_scale, wd, a1, a2;
   Ref l1, l2;              // fp32, m x r, row stride r
+  int32_t store_l, pad;    // 1: l2 also takes the place of l1 (the state): each workgroup has read its rows of both
   Ref q1, q2;              // fp32, r x n, row stride n (read for a row's last n mod 8 columns only)
   int64_t off_img1, off_img2;   // workspace: images of Q1^T, Q2^T (layout of the held-R kernel's second image)
   int64_t off_v;           // state

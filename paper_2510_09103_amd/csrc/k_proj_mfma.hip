@@ -1129,7 +1129,9 @@ __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* _
     const bool vec4 = (r & 3) == 0;
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
-      const float* __restrict__ Lp = reinterpret_cast<const float*>(resolve(p == 0 ? B.l1 : B.l2, bs));
+      const float* Lp = reinterpret_cast<const float*>(resolve(p == 0 ? B.l1 : B.l2, bs));
+      // the new factor takes the old one's place: these rows are this workgroup's alone, every thread has read what it replaces
+      float* const Ls = p == 1 && B.store_l ? reinterpret_cast<float*>(resolve(B.l1, bs)) : nullptr;
       const float a = p == 0 ? B.a1 : B.a2;
       uint16_t* Dh = reinterpret_cast<uint16_t*>(smem + (2 * p) * D_ONE);
       uint16_t* Dl = reinterpret_cast<uint16_t*>(smem + (2 * p + 1) * D_ONE);
@@ -1138,14 +1140,20 @@ __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* _
         const int id = tid + NT * i, row = id / (R / 4), c4 = (id % (R / 4)) * 4;
         float d[4] = {0.f, 0.f, 0.f, 0.f};
         if (row0 + row < m && c4 < r && a != 0.f) {
-          const float* lp = Lp + (int64_t)(row0 + row) * r + c4;
+          const int64_t at = (int64_t)(row0 + row) * r + c4;
+          const float* lp = Lp + at;
           if (vec4) {
             const float4 t = *reinterpret_cast<const float4*>(lp);
             d[0] = a * t.x; d[1] = a * t.y; d[2] = a * t.z; d[3] = a * t.w;
+            if (Ls) *reinterpret_cast<float4*>(Ls + at) = t;
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (c4 + e < r) d[e] = a * lp[e];
+              if (c4 + e < r) {
+                const float t = lp[e];
+                d[e] = a * t;
+                if (Ls) Ls[at + e] = t;
+              }
           }
         }
         uint32_t h0, l0, h1, l1;
@@ -1484,7 +1492,7 @@ __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, co
     }
   }
   float* Ps = reinterpret_cast<float*>(smem);
-  float* Out = reinterpret_cast<float*>(bs.ws + P.off_out);
+  float* Out = reinterpret_cast<float*>(resolve(P.out, bs));
   // with the GD step, the new factor values (zeros outside the factor) go back into P for the image below
   const bool emit_f = P.upd && P.off_next >= 0, emit_t = P.upd && P.off_timg >= 0, emit = emit_f || emit_t;
   if (!TRA) {

@@ -129,6 +129,17 @@ def test_every_row_remainder_in_the_stripe_products(first, hp):
     run(wl, 4, dict(hp, contraction=B.ADAPM_CONTRACT_BF16X2), tol_state=TOL16, tol_param=TOL16, check_every=2)
 
 
+@pytest.mark.parametrize("hp", [dict(K=1), dict(K=2), dict(K=3), dict(K=1, bias_correction=0), dict(K=2, T=2)])
+def test_factors_that_reach_the_state_without_a_copy(hp):
+    """Where rows are whole vectors the last iteration's stripes write R over the old one, elsewhere it is copied; L is written
+    by the update, which reads the old one.  Stripes that end inside, at and past a chunk, ranks that are no multiple of 4."""
+    wl = WL.Workload("stored", tuple(
+        BlockSpec(f"{m}x{n}_r{r}", m, n, "bf16", "bf16", "lowrank", r, v, 1, 1.0, 0.1)
+        for m, n, r, v in ((70, 8, 5, "element"), (128, 64, 32, "rowgroup"), (129, 264, 70, "whole"), (257, 520, 128, "element"),
+                           (136, 263, 64, "rowgroup"), (40, 256, 33, "rowgroup"))), steps=4, seed=23, signal_rank=8)
+    run(wl, 4, dict(dict(T=1, contraction=B.ADAPM_CONTRACT_BF16X2), **hp), tol_state=TOL16, tol_param=TOL16, check_every=1)
+
+
 @pytest.mark.parametrize("hp", [dict(T=1), dict(T=3)])
 def test_rows_a_multiple_of_the_chunks_with_ragged_columns(hp):
     """The other end of a gradient whose rows are no whole vectors: rows that fill the last chunk of the transposed product
