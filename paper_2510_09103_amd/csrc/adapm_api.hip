@@ -148,6 +148,7 @@ struct adapm_ctx {
   int n_groups = 0;
   int rg_gram = -1, rg_chol = -1;       // T > 1, MFMA path: the re-expression of all blocks' factors after the last group
   DevList<RegaugeItem> rg_apply;
+  int64_t gw_bytes = 0;                 // gradients and parameters of the whole table
   std::vector<GemmList> gemms;
   std::vector<Op> seq_refresh, seq_project;
 
@@ -413,6 +414,14 @@ bool stores_direct(const adapm_hparams_t& hp) {
   return hp.refresh_period_T <= 1 && effective_step_sizes(hp.refresh_iters_K).size() >= 2;
 }
 
+// Is the fused updates' read of G non-temporal?  Where the table streams through the last-level cache (256 MiB) and the rows are
+// whole cache lines: 48 layers of 1600 / 6400 at r = 128, R held, 3.05 -> 3.00 ms, 24 layers of 1024 / 4096 at r = 64 0.986 ->
+// 0.974.  Rows that are not have lines in two tiles, and the second one fetches them again (1672 / 6688 at r = 84 2.82 -> 2.90 ms);
+// a table that stays in the caches is sent out of them (ten layers of 192 / 512 32.3 -> 33.5 us, six of 128 / 341 18.2 -> 19.9).
+int32_t last_read(const adapm_ctx* c, const adapm_block_t& b) {
+  return b.cols % 64 == 0 && c->gw_bytes > ((int64_t)256 << 20);
+}
+
 // Alg. 2 + eq. 3-4 for the low-rank blocks of one contraction path.
 //   fast = false: batched GEMMs on the fp64 matrix cores, every intermediate kept in fp64;
 //   fast = true : split-bf16 matrix instructions, fp32 intermediates: stripe products, or batched GEMMs for the blocks
@@ -662,6 +671,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
       d.param_dtype = b.param_dtype; d.lr_scale = b.lr_scale; d.wd = b.weight_decay;
       d.a1 = hp.bias_correction ? 1.f : 0.f; d.a2 = hp.bias_correction ? -1.f : 1.f;
       d.store_l = n_eff > 0 ? 1 : 0;
+      d.g_last = last_read(c, b);
       d.l1 = Lp.ref; d.l2 = Lc.ref; d.q1 = Rp.ref; d.q2 = Rc.ref; d.off_img1 = L.wT1; d.off_img2 = L.wT2; d.off_v = L.sv;
       c->rub[grp].h.push_back(d);
       for (int ch = 0; ch < (n + 63) / 64; ++ch) {
@@ -860,6 +870,7 @@ void plan_lowrank_project_fast(adapm_ctx* c) {
     else if (v_fusable(b)) { d.v_kind = 1; d.v_group_rows = b.v_group_rows; }
     else { d.v_kind = 2; d.v_group_rows = b.v_mode == ADAPM_V_WHOLE ? (int32_t)b.rows : b.v_group_rows; }
     d.param_dtype = b.param_dtype; d.lr_scale = b.lr_scale; d.wd = b.weight_decay;
+    d.g_last = last_read(c, b);
     lr_of[i] = (int64_t)c->lrb.h.size();
     c->lrb.h.push_back(d);
     for (int ch = 0; ch < (int)((b.cols + 63) / 64); ++ch) c->qs.h.push_back(QsItem{(int32_t)lr_of[i], ch});
@@ -1118,6 +1129,8 @@ void build_plan(adapm_ctx* c) {
     L.sv = salloc(4 * L.nv);
   }
   c->state_bytes = so;
+  for (const adapm_block_t& b : c->table)
+    c->gw_bytes += b.rows * b.cols * ((b.grad_dtype == ADAPM_BF16 ? 2 : 4) + (b.param_dtype == ADAPM_BF16 ? 2 : 4));
   const size_t budget = choose_stripes(c);
 
   // device block table, element-wise chunks, v statistics

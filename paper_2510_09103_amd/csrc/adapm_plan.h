@@ -161,6 +161,7 @@ struct LrBlockDev {
   int32_t param_dtype;
   float lr_scale, wd;
   int32_t rc;              // rank class the kernels are compiled for: 32, 64 or 128 >= r (images are zero-padded to it)
+  int32_t g_last, pad;     // 1: the second read of G is non-temporal
 };
 
 struct ProjItem {          // one workgroup: 128 rows of one block; lr < 0 = padding
@@ -256,7 +257,8 @@ struct RuBlockDev {
   int32_t param_dtype;
   float lr_scale, wd, a1, a2;
   Ref l1, l2;              // fp32, m x r, row stride r
-  int32_t store_l, pad;    // 1: l2 also takes the place of l1 (the state): each workgroup has read its rows of both
+  int32_t g_last;          // 1: G is read non-temporally
+  int32_t store_l;         // 1: l2 also takes the place of l1 (the state): each workgroup has read its rows of both
   Ref q1, q2;              // fp32, r x n, row stride n (read for a row's last n mod 8 columns only)
   int64_t off_img1, off_img2;   // workspace: images of Q1^T, Q2^T (layout of the held-R kernel's second image)
   int64_t off_v;           // state

@@ -768,10 +768,17 @@ __global__ __launch_bounds__(NT, 1) void proj_kernel(const ProjItem* __restrict_
   auto fetch_gw = [&](int j, uint4 (&gq)[2], uint4 (&wq)[2][WV], uint4 (&vq)[2][VV]) {
     const int pj = nc - 1 - j;
     const bool ok = (unsigned)pj < (unsigned)nc && pj * BK + c8 < n8;
+    const unsigned e0 = eoff[0] + (unsigned)(pj * BK), e1 = eoff[1] + (unsigned)(pj * BK);
+    if (B.g_last) {
+      gq[0] = buf_load16_last(rG, ok ? e0 * 2u : OOB);
+      gq[1] = buf_load16_last(rG, ok ? e1 * 2u : OOB);
+    } else {
+      gq[0] = buf_load16(rG, ok ? e0 * 2u : OOB);
+      gq[1] = buf_load16(rG, ok ? e1 * 2u : OOB);
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const unsigned e = eoff[i] + (unsigned)(pj * BK);
-      gq[i] = buf_load16_last(rG, ok ? e * 2u : OOB);
+      const unsigned e = i ? e1 : e0;
 #pragma unroll
       for (int k = 0; k < WV; ++k) wq[i][k] = buf_load16(rW, ok ? e * WE + 16u * k : OOB);
       if (VEL) {
@@ -1286,10 +1293,16 @@ __global__ __launch_bounds__(NT, 1) void refresh_update_kernel(const ProjItem* _
     };
     auto fetch = [&](int s, uint4 (&g)[2], uint4 (&w)[2][WV]) {     // pair s = tiles 2 s and 2 s + 1
       const bool ok = s * 64 + c8 < n8;
+      if (B.g_last) {
+        g[0] = buf_load16_last(rG, ok ? at(0, s) * 2u : OOB);
+        g[1] = buf_load16_last(rG, ok ? at(1, s) * 2u : OOB);
+      } else {
+        g[0] = buf_load16(rG, ok ? at(0, s) * 2u : OOB);
+        g[1] = buf_load16(rG, ok ? at(1, s) * 2u : OOB);
+      }
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const unsigned e = at(h, s);
-        g[h] = buf_load16_last(rG, ok ? e * 2u : OOB);
 #pragma unroll
         for (int k = 0; k < WV; ++k) w[h][k] = buf_load16(rW, ok ? e * WE + 16u * k : OOB);
       }

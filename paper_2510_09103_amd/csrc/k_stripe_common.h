@@ -36,9 +36,8 @@ __device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, unsigned o
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-// the same for data whose last reader this is (G in the update): non-temporal, it leaves the caches first (held-R kernel, 48 layers
-// of 1600 / 6400 at r = 128 3.05 -> 3.00 ms, 24 of 1024 / 4096 at r = 64 0.986 -> 0.974, ragged rows of 5461 unchanged; on W as well it gains another
-// 1 % on rows of whole cache lines and loses 9 % on ragged ones, on the stripes of Alg. 2 it loses 2 % at r = 64)
+// the same for data whose last reader this is (G in the update): non-temporal, it leaves the caches first (see last_read for where;
+// on W as well it gains another 1 % on rows of whole cache lines and loses 9 % on others, on the stripes of Alg. 2 it loses 2 % at r = 64)
 __device__ __forceinline__ uint4 buf_load16_last(__amdgpu_buffer_rsrc_t r, unsigned off) {
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 2);   // non-temporal
   return make_uint4(v.x, v.y, v.z, v.w);
