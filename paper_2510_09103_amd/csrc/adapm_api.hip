@@ -1133,6 +1133,14 @@ void build_plan(adapm_ctx* c) {
     c->gw_bytes += b.rows * b.cols * ((b.grad_dtype == ADAPM_BF16 ? 2 : 4) + (b.param_dtype == ADAPM_BF16 ? 2 : 4));
   const size_t budget = choose_stripes(c);
 
+  // full / no momentum blocks with a blockwise v whose groups fit a wavefront's registers: one fused kernel
+  auto is_grouped = [&](int64_t i) {
+    const adapm_block_t& b = c->table[i];
+    return c->lay[i].path == PATH_NONE && b.v_mode != ADAPM_V_ELEMENT && group_elems(b) <= GRP_MAX_ELEMS && group_elems(b) % 8 == 0 &&
+           b.grad_dtype == ADAPM_BF16 && b.param_dtype == ADAPM_BF16;
+  };
+  int64_t ngrouped = 0;
+  for (int64_t i = 0; i < nb; ++i) if (is_grouped(i)) ngrouped += c->lay[i].nv;
   // device block table, element-wise chunks, v statistics
   int64_t npart = 0;
   for (int64_t i = 0; i < nb; ++i) {
@@ -1146,11 +1154,11 @@ void build_plan(adapm_ctx* c) {
     d.mom_mode = b.mom_mode; d.v_mode = b.v_mode;
     d.lr_scale = b.lr_scale; d.wd = b.weight_decay;
     c->blocks.h.push_back(d);
-    // full / no momentum blocks with a blockwise v whose groups fit a wavefront's registers: one fused kernel
-    const bool grouped = L.path == PATH_NONE && b.v_mode != ADAPM_V_ELEMENT && d.group_elems <= GRP_MAX_ELEMS &&
-                         d.group_elems % 8 == 0 && b.grad_dtype == ADAPM_BF16 && b.param_dtype == ADAPM_BF16;
-    if (grouped) {
-      const int64_t per = std::max<int64_t>(4, 32768 / d.group_elems);      // groups per workgroup (4 waves)
+    if (is_grouped(i)) {
+      // Groups per workgroup: a wave takes its groups one after another, each a memory latency, so few groups are spread over all
+      // the workgroups that the chip holds (2048) before a workgroup gets 32768 elements
+      // (2316 rows of 192 53 -> 8 us, the norms and heads of six layers of 168 / 672 51 -> 5; 50257 rows of 1600 keep 20 a workgroup).
+      const int64_t per = std::max<int64_t>(4, std::min<int64_t>(32768 / d.group_elems, (ngrouped + 8191) / 8192 * 4));
       for (int64_t g0 = 0; g0 < L.nv; g0 += per)
         c->grp.h.push_back(GrpItem{g0, (int32_t)i, (int32_t)std::min<int64_t>(per, L.nv - g0)});
       continue;

@@ -140,6 +140,16 @@ def test_factors_that_reach_the_state_without_a_copy(hp):
     run(wl, 4, dict(dict(T=1, contraction=B.ADAPM_CONTRACT_BF16X2), **hp), tol_state=TOL16, tol_param=TOL16, check_every=1)
 
 
+@pytest.mark.parametrize("groups", [1, 5, 8189, 8190, 8193, 20000])
+def test_groups_dealt_to_workgroups(groups):
+    """Few groups are spread over the chip, four to a workgroup, more of them where there are many: counts at which the share
+    of a workgroup changes (the smaller block adds three), and last workgroups with one group."""
+    wl = WL.Workload("dealt", (
+        BlockSpec("rows", groups, 16, "bf16", "bf16", "full", 0, "rowgroup", 1, 1.0, 0.1),
+        BlockSpec("wide", 3, 2048, "bf16", "bf16", "none", 0, "rowgroup", 1, 1.0, 0.1)), steps=2, seed=31)
+    run(wl, 2, dict(T=1), tol_state=TOL16, tol_param=TOL16, check_every=1)
+
+
 @pytest.mark.parametrize("hp", [dict(T=1), dict(T=3)])
 def test_rows_a_multiple_of_the_chunks_with_ragged_columns(hp):
     """The other end of a gradient whose rows are no whole vectors: rows that fill the last chunk of the transposed product
