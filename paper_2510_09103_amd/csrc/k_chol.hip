@@ -79,6 +79,14 @@ __device__ __forceinline__ Frag frag(const double* blk, int l16, int kq) {
   return f;
 }
 
+// Between LDS writes and reads of the same places by other lanes of the same wave.  The hardware keeps a wave's LDS accesses in
+// order; this tells the compiler, which sees one lane and may move accesses past each other that only lanes apart from it share.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // diagonal block p, as it stands in LDS: its lower factor to global memory, its inverse in its place
 __device__ __forceinline__ void diagonal(double* blk, double* A, int r, int p, int lane, int* bad) {
   const int i = lane & 15;                       // this lane's row (the four copies do the same)
@@ -104,6 +112,7 @@ __device__ __forceinline__ void diagonal(double* blk, double* A, int r, int p, i
     for (int c = 0; c < a; ++c) s -= lane_value(row[c], a) * x[c];
     x[a] = s / lane_value(row[a], a);
   }
+  wave_lds_order();                              // every lane has read its row
   if (wrong) *bad = 1;
   if (lane < CB) {
 #pragma unroll
@@ -148,6 +157,7 @@ __global__ __launch_bounds__(256, 2) void chol_inv_kernel(const CholItem* __rest
   for (int p = 0; p < nb; ++p) {
     if (wave == 0) {
       if (p > 0) trailing(p, p, p - 1);
+      wave_lds_order();                              // its rows go to other lanes
       diagonal(S + block_at(p, p), A, r, p, lane, &bad);
     } else if (p > 0) {
       int n = 0;
