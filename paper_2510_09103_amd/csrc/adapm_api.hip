@@ -304,17 +304,22 @@ int64_t tiles_of(int64_t x) { return (x + 15) / 16; }
 // fetches a factor or gradient once for all tiles that read it; largest blocks first, to the least loaded XCD.  The list
 // holds the problems of its blocks one after the other, `nblocks` times the same number of them.  Gram matrices of 56 blocks at
 // r = 32 30 -> 22 us, G R^T 63 -> 56 us.  Launches of fewer tiles than three per compute unit keep their order: whole blocks
-// leave some XCDs idle (update of 7 small blocks 10.9 -> 13.8 us).
+// leave some XCDs idle (update of 7 small blocks 10.9 -> 13.8 us).  So does a list whose fullest XCD would get over a tenth more than the
+// mean, because its blocks are few or a few of them large: two blocks of 4096 x 4096 at r = 128 took 7408 us on two XCDs and take 2060
+// in their order, a layer of 2048 / 8192 8087 and 3290, one of 1024 / 4096 at r = 64 1102 and 594.
 void deal_to_xcds(GemmList& gl, size_t nblocks) {
   constexpr int NXCD = 8;
   if (nblocks < 2 || gl.probs.size() % nblocks != 0 || gl.tiles.size() < 768) return;
   const size_t each = gl.probs.size() / nblocks;
   std::vector<std::vector<GemmTile>> of(nblocks);
   std::vector<double> cost(nblocks, 0.0);
+  double total = 0.0;
   for (const GemmTile& t : gl.tiles) {
     const GemmProblem& p = gl.probs[t.prob];
+    const double c = ((double)p.K1 + p.K2 + p.K3) * t.nj;
     of[t.prob / each].push_back(t);
-    cost[t.prob / each] += (double)p.K1 + p.K2 + p.K3;
+    cost[t.prob / each] += c;
+    total += c;
   }
   std::vector<size_t> order(nblocks);
   for (size_t i = 0; i < nblocks; ++i) order[i] = i;
@@ -327,6 +332,7 @@ void deal_to_xcds(GemmList& gl, size_t nblocks) {
     per[x].insert(per[x].end(), of[i].begin(), of[i].end());
     load[x] += cost[i];
   }
+  if (*std::max_element(load, load + NXCD) * NXCD > 1.1 * total) return;
   size_t longest = 0;
   for (auto& v : per) {
     std::stable_sort(v.begin(), v.end(), [&](const GemmTile& a, const GemmTile& b) { return gl.probs[a.prob].K1 > gl.probs[b.prob].K1; });

@@ -1,0 +1,122 @@
+"""Work lists that the planner makes, read out of a context on the host: no GPU."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+from paper_2510_09103_amd import binding as B
+from paper_2510_09103_amd.build import CSRC, FLAGS
+from paper_2510_09103_amd.optimizer import make_hparams
+
+PROBE = r'''
+#include "adapm_api.hip"
+// One row of `out` per workgroup of launch `op` of a step: problem (-1: padding), ti, tj, nj, M, N, tile height, tile width, length of
+// the contractions.  Returns the number of rows, -1 past the last launch, 0 for launches that are no tiles of the exact path.
+extern "C" int64_t probe_tiles(const adapm_ctx* c, int held, int64_t op, const char** label, int64_t* out, int64_t cap) {
+  const std::vector<Op>& seq = held ? c->seq_project : c->seq_refresh;
+  if (op >= (int64_t)seq.size()) return -1;
+  *label = seq[op].label;
+  if (seq[op].kind != OP_GEMM && seq[op].kind != OP_UPDATE64) return 0;
+  const GemmList& gl = c->gemms[seq[op].index];
+  if ((int64_t)gl.tiles.size() > cap) return -2;
+  for (const GemmTile& t : gl.tiles) {
+    if (t.prob == GEMM_TILE_NONE) { *out = -1; out += 9; continue; }
+    const GemmProblem& p = gl.probs[t.prob];
+    const int64_t row[9] = {t.prob, t.ti, t.tj, t.nj, p.M, p.N, 16 * p.tm, 16 * p.tn, (int64_t)p.K1 + p.K2 + p.K3};
+    for (int64_t x : row) *out++ = x;
+  }
+  return (int64_t)gl.tiles.size();
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    d = tmp_path_factory.mktemp("probe")
+    (d / "probe.hip").write_text(PROBE)
+    lib = d / "libprobe.so"
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *FLAGS, "-O1", "-shared", "-I", CSRC, str(d / "probe.hip"), "-o", str(lib),
+                    "-L" + os.path.dirname(B.LIB_PATH), "-l:" + os.path.basename(B.LIB_PATH), "-Wl,-rpath," + os.path.dirname(B.LIB_PATH)], check=True, stderr=subprocess.DEVNULL)
+    return C.CDLL(str(lib))
+
+
+class Plan:
+    def __init__(self, lib, table, hp):
+        self.lib, self.ctx = lib, C.c_void_p()
+        arr = (B.adapm_block_t * len(table))(*table)
+        assert lib.adapm_init(C.byref(self.ctx), arr, C.c_int64(len(table)), C.byref(hp)) == B.ADAPM_OK
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, *_):
+        self.lib.adapm_destroy(self.ctx)
+
+    def launches(self, held):
+        """(label, rows of probe_tiles) of the step's launches of tiles"""
+        self.lib.probe_tiles.restype = C.c_int64
+        cap = 200000
+        out, label = (C.c_int64 * (9 * cap))(), C.c_char_p()
+        op = 0
+        while True:
+            n = self.lib.probe_tiles(self.ctx, C.c_int(held), C.c_int64(op), C.byref(label), out, C.c_int64(cap))
+            assert n != -2
+            if n < 0:
+                return
+            if n > 0:
+                yield label.value.decode(), [tuple(out[9 * i:9 * i + 9]) for i in range(n)]
+            op += 1
+
+
+DT = {"f32": B.ADAPM_F32, "bf16": B.ADAPM_BF16}
+
+
+def lowrank(m, n, r, pd="f32", gd="bf16", v=B.ADAPM_V_ELEMENT):
+    return B.adapm_block_t(rows=m, cols=n, param_dtype=DT[pd], grad_dtype=DT[gd], mom_mode=B.ADAPM_MOM_LOWRANK, rank=r, v_mode=v,
+                           v_group_rows=1, lr_scale=1.0, weight_decay=0.1)
+
+
+def layers(d, f, r, count, up=1, attention=4):
+    return count * ([lowrank(d, d, r)] * attention + [lowrank(f, d, r)] * up + [lowrank(d, f, r)])
+
+
+FEW = {
+    "one": [lowrank(4096, 4096, 128)],
+    "two": 2 * [lowrank(4096, 4096, 128)],
+    "three_unlike": [lowrank(4096, 1024, 64), lowrank(512, 512, 64), lowrank(1000, 3001, 100)],
+    "layer_2048": layers(2048, 8192, 128, 1),
+    "layer_2048_two_lowrank": layers(2048, 8192, 128, 1, attention=2),
+    "layer_1024_gated": layers(1024, 2731, 64, 1, up=2),
+    "layer_512_gated": layers(512, 1376, 32, 1, up=2),
+    "two_layers_1024": layers(1024, 4096, 64, 2),
+    "fourteen": layers(1024, 2731, 64, 2, up=2),
+    "eight_layers_512": layers(512, 1376, 32, 8, up=2),
+}
+
+
+@pytest.mark.parametrize("T", [1, 10])
+@pytest.mark.parametrize("name", FEW)
+def test_tiles_of_the_exact_path_fill_the_xcds_evenly(probe, name, T):
+    """Workgroup i runs on XCD i mod 8.  A launch that fills the chip puts no more than 1.15 times the mean of its multiply-adds on any
+    XCD, and every tile of every result is there exactly once."""
+    seen = 0
+    with Plan(probe, FEW[name], make_hparams(T=T)) as plan:
+        for held in range(2 if T > 1 else 1):
+            for label, rows in plan.launches(held):
+                load, covered, shape = [0.0] * 8, {}, {}
+                for i, (prob, ti, tj, nj, M, N, th, tw, K) in enumerate(rows):
+                    if prob < 0:
+                        continue
+                    load[i % 8] += K * nj
+                    shape[prob] = (-(-M // th), -(-N // tw))
+                    covered.setdefault(prob, []).extend((ti, tj + k) for k in range(nj))
+                for prob, (nti, ntj) in shape.items():
+                    want = {(a, b) for a in range(nti) for b in range(ntj)}
+                    got = covered[prob]
+                    assert len(got) == len(set(got)), label
+                    assert set(got) == want or (label == "regauge_gram_f64" and set(got) == {(a, b) for a, b in want if b <= a}), label
+                if sum(r[0] >= 0 for r in rows) >= 768:
+                    seen += 1
+                    assert max(load) * 8 <= 1.15 * sum(load), (label, len(rows), [round(8 * x / sum(load), 2) for x in load])
+    assert seen or name in ("layer_512_gated", "three_unlike")
