@@ -93,7 +93,8 @@ struct GemmProblem {
   // fp64 kernel, optional second result of the same sums: Out2 = g2 X + s2 (...), or with dup the first one again; may be X itself
   Mat Out2;
   double g2, s2;
-  int32_t dup, pad2;
+  int32_t dup;
+  int32_t cls;       // update of the exact path: class of the block (update64_class)
 };
 
 constexpr uint32_t GEMM_TILE_NONE = 0xffffffffu;
@@ -305,7 +306,7 @@ void launch_gradnorm_final(const double* partials, int64_t nparts, float max_nor
 // update of the low-rank blocks of the exact path (k_update64.hip): 64 x 64 tiles of problems whose sums are the m x n term
 constexpr int UPD64_TILE = 64;
 int update64_class(int64_t N, int64_t K, bool g16, bool w16, bool vel);
-constexpr int UPD64_CLASSES = 9;
+constexpr int UPD64_CLASSES = 9, UPD64_MIXED = 9;      // ... and launches of several classes
 void launch_update64(int cls, const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, int steps, const BlockDev* blocks, Bases b,
                      StepScalars sc, hipStream_t s);
 void launch_update(const BlockDev* blocks, const EwItem* items, int64_t nitems, Bases b, StepScalars sc,

@@ -111,17 +111,11 @@ __device__ __forceinline__ void multiply(const Factors& f, int kb, int ke, int k
   }
 }
 
-// One kernel per type of G and W and kind of second moment (a table of one type is one launch).  cap: steps of A that a wave's
-// part of the dynamic LDS holds; KEEP: they hold all of A of every block of the list, which is then staged once.
+// One body per type of G and W and kind of second moment.  cap: steps of A that a wave's part of the LDS holds; KEEP: they hold all of A of
+// every block of the list, which is then staged once.
 template <int GDT, int WDT, bool VEL, bool KEEP>
-__global__ __launch_bounds__(64 * UW, 3) void update64_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
-                                                              const BlockDev* __restrict__ blocks, Bases bs, StepScalars sc, int cap) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char upd_lds[];
-  f64x2_a8* const lds = reinterpret_cast<f64x2_a8*>(upd_lds);
-  const GemmTile tile = tiles[blockIdx.x];
-  if (tile.prob == GEMM_TILE_NONE) return;
-  const GemmProblem& P = probs[tile.prob];
-  const BlockDev& blk = blocks[P.Out.ref.block];
+__device__ __forceinline__ void update64_body(const GemmProblem& P, const GemmTile& tile, const BlockDev& blk, const Bases& bs, const StepScalars& sc,
+                                              int cap, f64x2_a8* lds) {
   const int M = P.M, N = P.N, block = P.Out.ref.block;
   const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -238,12 +232,7 @@ __global__ __launch_bounds__(64 * UW, 3) void update64_kernel(const GemmProblem*
 
 // Blocks whose rows are shorter than a lane's four columns, or so long that a wave's rows or a factor pass 4 GiB: one thread per
 // element, the sums in fp64 one product after the other
-__global__ __launch_bounds__(64 * UW) void update64_elements_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
-                                                                    const BlockDev* __restrict__ blocks, Bases bs, StepScalars sc) {
-  const GemmTile tile = tiles[blockIdx.x];
-  if (tile.prob == GEMM_TILE_NONE) return;
-  const GemmProblem& P = probs[tile.prob];
-  const BlockDev& blk = blocks[P.Out.ref.block];
+__device__ __forceinline__ void update64_elements(const GemmProblem& P, const GemmTile& tile, const BlockDev& blk, const Bases& bs, const StepScalars& sc) {
   const int N = P.N, block = P.Out.ref.block;
   const char* G = global_ptr((const char*)bs.grads[block]);
   char* W = global_ptr((char*)bs.params[block]);
@@ -279,10 +268,53 @@ __global__ __launch_bounds__(64 * UW) void update64_elements_kernel(const GemmPr
   }
 }
 
+// One kernel per class of blocks (a table of one class is one launch)
+template <int GDT, int WDT, bool VEL, bool KEEP>
+__global__ __launch_bounds__(64 * UW, 3) void update64_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
+                                                              const BlockDev* __restrict__ blocks, Bases bs, StepScalars sc, int cap) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char upd_lds[];
+  const GemmTile tile = tiles[blockIdx.x];
+  if (tile.prob == GEMM_TILE_NONE) return;
+  const GemmProblem& P = probs[tile.prob];
+  update64_body<GDT, WDT, VEL, KEEP>(P, tile, blocks[P.Out.ref.block], bs, sc, cap, reinterpret_cast<f64x2_a8*>(upd_lds));
+}
+
+__global__ __launch_bounds__(64 * UW) void update64_elements_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
+                                                                    const BlockDev* __restrict__ blocks, Bases bs, StepScalars sc) {
+  const GemmTile tile = tiles[blockIdx.x];
+  if (tile.prob == GEMM_TILE_NONE) return;
+  const GemmProblem& P = probs[tile.prob];
+  update64_elements(P, tile, blocks[P.Out.ref.block], bs, sc);
+}
+
+// ... and one for all of them, for few tiles of several classes (UPD64_MIXED).  Its workgroups walk one tile, so that staging A by and by
+// costs nothing.
+__global__ __launch_bounds__(64 * UW, 2) void update64_mixed_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
+                                                                    const BlockDev* __restrict__ blocks, Bases bs, StepScalars sc, int cap) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char upd_lds[];
+  const GemmTile tile = tiles[blockIdx.x];
+  if (tile.prob == GEMM_TILE_NONE) return;
+  const GemmProblem& P = probs[tile.prob];
+  const BlockDev& blk = blocks[P.Out.ref.block];
+  f64x2_a8* const lds = reinterpret_cast<f64x2_a8*>(upd_lds);
+  switch (P.cls) {
+    case 0: update64_body<DT_F32, DT_F32, false, false>(P, tile, blk, bs, sc, cap, lds); break;
+    case 1: update64_body<DT_BF16, DT_F32, false, false>(P, tile, blk, bs, sc, cap, lds); break;
+    case 2: update64_body<DT_F32, DT_BF16, false, false>(P, tile, blk, bs, sc, cap, lds); break;
+    case 3: update64_body<DT_BF16, DT_BF16, false, false>(P, tile, blk, bs, sc, cap, lds); break;
+    case 4: update64_body<DT_F32, DT_F32, true, false>(P, tile, blk, bs, sc, cap, lds); break;
+    case 5: update64_body<DT_BF16, DT_F32, true, false>(P, tile, blk, bs, sc, cap, lds); break;
+    case 6: update64_body<DT_F32, DT_BF16, true, false>(P, tile, blk, bs, sc, cap, lds); break;
+    case 7: update64_body<DT_BF16, DT_BF16, true, false>(P, tile, blk, bs, sc, cap, lds); break;
+    default: update64_elements(P, tile, blk, bs, sc);
+  }
+}
+
+constexpr int CAP = 8;                         // steps of A in LDS: 64 KB, two workgroups per CU
+
 template <int GDT, int WDT, bool VEL>
 void launch_class(dim3 grid, int steps, const GemmProblem* probs, const GemmTile* tiles, const BlockDev* blocks, Bases b, StepScalars sc,
                   hipStream_t s) {
-  constexpr int CAP = 8;                       // 64 KB of LDS, two workgroups per CU
   if (steps <= CAP) {
     const int cap = steps < 1 ? 1 : steps;
     hipLaunchKernelGGL((update64_kernel<GDT, WDT, VEL, true>), grid, dim3(64 * UW), (size_t)UW * cap * STEP_BYTES, s, probs, tiles, blocks, b, sc, cap);
@@ -313,6 +345,11 @@ void launch_update64(int cls, const GemmProblem* probs, const GemmTile* tiles, i
     case 5: launch_class<DT_BF16, DT_F32, true>(grid, steps, probs, tiles, blocks, b, sc, s); break;
     case 6: launch_class<DT_F32, DT_BF16, true>(grid, steps, probs, tiles, blocks, b, sc, s); break;
     case 7: launch_class<DT_BF16, DT_BF16, true>(grid, steps, probs, tiles, blocks, b, sc, s); break;
+    case UPD64_MIXED: {
+      const int cap = steps < 1 ? 1 : (steps < CAP ? steps : CAP);
+      hipLaunchKernelGGL(update64_mixed_kernel, grid, dim3(64 * UW), (size_t)UW * cap * STEP_BYTES, s, probs, tiles, blocks, b, sc, cap);
+      break;
+    }
     default: hipLaunchKernelGGL(update64_elements_kernel, grid, dim3(64 * UW), 0, s, probs, tiles, blocks, b, sc);
   }
 }

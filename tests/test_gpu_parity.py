@@ -240,6 +240,17 @@ def test_exact_path_for_every_number_of_waves_on_a_tile(copies, hp):
     run(wl, 3, hp, tol_state=TOL32, tol_param=TOL32)
 
 
+@pytest.mark.parametrize("hp", [dict(T=1), dict(T=2)])
+def test_every_type_of_block_in_one_update_of_the_exact_path(hp):
+    """Both types of G and W, both kinds of second moment and blocks of fewer columns than a lane updates, in one launch of few tiles:
+    sizes at and beside the edges of a tile, ranks whose factors fit the launch's LDS, fill it and pass it."""
+    sizes = [(64, 64, 8), (65, 63, 31), (130, 67, 65), (97, 200, 70), (63, 129, 16), (33, 2, 2), (129, 3, 3), (16, 4, 4)]
+    kinds = [(pd, gd, v) for pd in ("f32", "bf16") for gd in ("f32", "bf16") for v in ("element", "rowgroup")]
+    wl = WL.Workload("types", tuple(BlockSpec(f"b{k}_{m}x{n}_r{r}", m, n, pd, gd, "lowrank", min(r, m, n), v, 1, 1.0, 0.1)
+                                    for k, (m, n, r) in enumerate(sizes) for pd, gd, v in kinds[k % 2::2]), steps=3, seed=53, signal_rank=24)
+    run(wl, 3, dict(hp, contraction=B.ADAPM_CONTRACT_F64), tol_state=TOL32, tol_param=TOL32)
+
+
 @pytest.mark.parametrize("pd,gd,vm,clip", [("f32", "bf16", "element", None), ("bf16", "f32", "rowgroup", 0.5), ("bf16", "bf16", "element", None),
                                            ("f32", "f32", "whole", None)])
 @pytest.mark.parametrize("hp", [dict(T=1), dict(T=3), dict(T=2, bias_correction=0), dict(T=2, K=1)])

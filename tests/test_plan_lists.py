@@ -120,3 +120,14 @@ def test_tiles_of_the_exact_path_fill_the_xcds_evenly(probe, name, T):
                     seen += 1
                     assert max(load) * 8 <= 1.15 * sum(load), (label, len(rows), [round(8 * x / sum(load), 2) for x in load])
     assert seen or name in ("layer_512_gated", "three_unlike")
+
+
+@pytest.mark.parametrize("side,launches", [(256, 1), (1024, 4)])
+def test_few_tiles_of_several_types_are_one_update(probe, side, launches):
+    """A kernel per type of G, W and second moment costs a launch each: where all of them together are few tiles, one launch takes
+    them all."""
+    V = (B.ADAPM_V_ELEMENT, B.ADAPM_V_ROWGROUP)
+    table = [lowrank(side, side, 8, "f32", gd, v) for gd in ("f32", "bf16") for v in V] * 6
+    with Plan(probe, table, make_hparams(T=10)) as plan:
+        rows = [r for label, r in plan.launches(1) if label == "update_lowrank_f64"]
+    assert len(rows) == launches
