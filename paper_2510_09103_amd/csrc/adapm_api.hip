@@ -293,12 +293,29 @@ GemmProblem& shape64(GemmProblem& p, int layout, bool small = false) {
   return p;
 }
 
-// Waves that share the contraction of one output tile in a launch of the fp64 kernel whose results are `tiles16` tiles of 16 x 16
-// (measured: k_gemm64.hip).  One workgroup of 16 waves or two of 8 fill a compute unit's 128-register slots; above two rounds
-// of those, four waves on 32 x 32 tiles load half as much per multiply-add: the updates of 56 blocks at r = 32, 9760 tiles, take
-// 98 us that way and 146 us with 8 waves.
-int waves64(int64_t tiles16) { return tiles16 <= 256 ? 16 : (tiles16 <= 1024 ? 8 : 4); }
 int64_t tiles_of(int64_t x) { return (x + 15) / 16; }
+
+// How many workgroups of a launch of the fp64 kernel on tiles of up to 32 x 32 run beside its longest contraction: the tiles, each
+// counted by its contraction against the longest one.
+struct Fill64 {
+  double work = 0.0, longest = 1.0;
+  void add(int64_t M, int64_t N, int64_t K) {
+    auto tiles = [](int64_t x) { return x <= 16 ? 1 : (x + 31) / 32; };
+    work += (double)tiles(M) * tiles(N) * K;
+    longest = std::max(longest, (double)K);
+  }
+  double tiles() const { return work / longest; }
+};
+// Waves that share the contraction of one output tile in a launch of the fp64 kernel.  Four on 32 x 32 tiles load half as much per
+// multiply-add as eight on 16 x 16 ones, which are done in half the time where the launch does not fill the chip.  The line lies where
+// those meet, over 60 tables of 1 .. 200 blocks of 64 .. 8192 at r = 8 .. 128: for the factor updates 128 tiles are 4 - 15 % of a literal step
+// faster with eight waves (one block of 2048 x 2048 at r = 16 157 us, 175 with four), 160 to 224 3 - 6 % slower (five of 512 x 512 at
+// r = 16 95 and 89), 256 up to 19 % (four of 1024 x 1024 at r = 32 187 and 157); for G R^T, which has one operand of its own per tile, 128 tiles 9 %
+// faster, 160 to 230 within 3 % but for padded ranks (r = 48 5 % faster), 240 and 256 7 - 15 % slower.  Gram matrices, always on
+// 16 x 16 tiles while they are few, differ by 1 % up to 256 tiles (7 % where a contraction is long) and lose 1 % beyond; those
+// of the re-gauge, one per block, gain 1 - 4 % up to a thousand.
+constexpr double UPDATE64_FILL = 144, PROJECT64_FILL = 232;
+int waves64(bool few) { return few ? 8 : 4; }
 
 // Order of the tiles of a launch of the exact path: whole blocks to one XCD (workgroup i runs on XCD i mod 8), whose L2 then
 // fetches a factor or gradient once for all tiles that read it; largest blocks first, to the least loaded XCD.  The list
@@ -478,16 +495,18 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
     }
   }
   // Exact path: 32 x 32 tiles of the Gram matrices once they make four workgroups per compute unit, else 16 x 16
-  int64_t gram_tiles = 0, gram16 = 0, upd16 = 0, regauge16 = 0;
+  int64_t gram_tiles = 0, gram16 = 0, regauge16 = 0;
+  Fill64 update;
   for (int64_t i : ids) {
     const adapm_block_t& b = c->table[i];
     const int64_t rt = tiles_of(b.rank);
     gram_tiles += 4ll * ((b.rank + 31) / 32) * ((b.rank + 31) / 32);
     gram16 += 4 * rt * rt;
     regauge16 += rt * (rt + 1) / 2;
-    upd16 += rt * (tiles_of(b.rows) + tiles_of(b.cols));
+    update.add(b.rows, b.rank, b.cols);
+    update.add(b.rank, b.cols, b.rows);
   }
-  const int gram_waves = waves64(gram16), upd_waves = waves64(upd16), regauge_waves = waves64(regauge16);
+  const int gram_waves = waves64(gram16 <= 256), upd_waves = waves64(update.tiles() < UPDATE64_FILL), regauge_waves = waves64(regauge16 <= 1024);
   const bool gram_small = gram_tiles < 4 * 256 || gram_waves > 4, upd_small = upd_waves > 4, regauge_small = regauge_waves > 4;
   // this group's lists
   const int grp = c->n_groups++;
@@ -841,9 +860,9 @@ void plan_lowrank_project_f64(adapm_ctx* c, const std::vector<int64_t>& ids) {
   auto new_list = [&]() { c->gemms.emplace_back(); return (int)c->gemms.size() - 1; };
   const int l_p = new_list();
   Update64Lists l_c;
-  int64_t proj16 = 0;
-  for (int64_t i : ids) proj16 += tiles_of(c->table[i].rank) * tiles_of(c->table[i].rows);
-  const int waves = c->gemms[l_p].waves = waves64(proj16);
+  Fill64 project;
+  for (int64_t i : ids) project.add(c->table[i].rows, c->table[i].rank, c->table[i].cols);
+  const int waves = c->gemms[l_p].waves = waves64(project.tiles() < PROJECT64_FILL);
   for (int64_t i : ids) {
     const adapm_block_t& b = c->table[i];
     const Layout& L = c->lay[i];

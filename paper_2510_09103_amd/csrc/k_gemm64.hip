@@ -10,10 +10,10 @@
 // through) and add their partial tiles through LDS in wave order.  Operands go from memory to the registers of the matrix
 // instruction (k_f64_common.h); a step's loads are in flight while the previous step is multiplied.
 //   4 waves, tiles of 16 tm x 16 tn (tm, tn = 1 or 2): launches of more tiles than the chip takes at once;
-//   8 or 16 waves, 16 x 16: launches of at most 1024 or 256 such tiles (waves64 in adapm_api.hip), whose contraction would
-//   otherwise keep a few waves busy on a nearly empty chip: 7 blocks of at most 256 x 1024 at r = 8, Gram matrices of an
-//   iteration 11 -> 8.5 us, factor updates 16 -> 12, G R^T with R held 12.9 -> 7.9; Gram matrices of 56 blocks of 512 x 512 ..
-//   1376 x 512 at r = 32 33 -> 24 us.  What is left of such a launch is the look-up of its problem and a cold instruction cache.
+//   8 waves, 16 x 16: launches that leave compute units idle (waves64 in adapm_api.hip), whose contraction would otherwise
+//   keep a few waves busy on a nearly empty chip: 7 blocks of at most 256 x 1024 at r = 8, Gram matrices of an iteration
+//   11.6 -> 8.5 us, factor updates 16.8 -> 11.7, G R^T with R held 12.3 -> 7.7.  (16 waves were no better in any of 60 tables and 3 - 4 us a literal
+//   step slower in most.)  What is left of such a launch is the look-up of its problem and a cold instruction cache.
 // Measured against 64 x 64 tiles on the vector units with operands staged in LDS (one workgroup walking the whole
 // contraction): G R^T, L^T G and the Gram matrices of one GD iteration with the factor updates, the 56 blocks: 454 -> 122 us
 // (of which 98 us, 36 TFLOP/s, for the updates; the matrix cores are busy half of that); the 7 small ones 157 -> 21 us.
@@ -228,8 +228,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 4) void gemm64_kernel(const 
 void launch_gemm64(int waves, const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, Bases b, hipStream_t s) {
   if (ntiles <= 0) return;
   const dim3 grid((unsigned)ntiles);
-  if (waves == 16) hipLaunchKernelGGL(gemm64_kernel<16>, grid, dim3(1024), 0, s, probs, tiles, b);
-  else if (waves == 8) hipLaunchKernelGGL(gemm64_kernel<8>, grid, dim3(512), 0, s, probs, tiles, b);
+  if (waves == 8) hipLaunchKernelGGL(gemm64_kernel<8>, grid, dim3(512), 0, s, probs, tiles, b);
   else hipLaunchKernelGGL(gemm64_kernel<4>, grid, dim3(256), 0, s, probs, tiles, b);
 }
 

@@ -231,7 +231,7 @@ def test_exact_path_at_the_edges_of_its_tiles(gd, many, T):
 @pytest.mark.parametrize("copies", [1, 12, 30])
 @pytest.mark.parametrize("hp", [dict(T=1), dict(T=2), dict(T=1, K=2), dict(T=1, K=3, normalise=1)])
 def test_exact_path_for_every_number_of_waves_on_a_tile(copies, hp):
-    """Launches of few output tiles split a contraction over 16 or 8 waves, the others over 4 and deal whole blocks to an XCD;
+    """Launches of few output tiles split a contraction over 8 waves, the others over 4 and may deal whole blocks to an XCD;
     with two GD iterations or more the last one writes the factors to the state, with one (K = 2) a launch of its own.  Sums in
     fp64 whatever the split: the fp32 tolerance."""
     sizes = [(17, 33, 1), (33, 17, 17), (64, 31, 31), (97, 63, 33)]

@@ -31,6 +31,17 @@ extern "C" int64_t probe_tiles(const adapm_ctx* c, int held, int64_t op, const c
 '''
 
 
+# Waves of a workgroup of launch `op`, 0 for launches of another kind, -1 past the last one
+PROBE += r'''
+extern "C" int64_t probe_launch(const adapm_ctx* c, int held, int64_t op, const char** label) {
+  const std::vector<Op>& seq = held ? c->seq_project : c->seq_refresh;
+  if (op >= (int64_t)seq.size()) return -1;
+  *label = seq[op].label;
+  return seq[op].kind == OP_GEMM ? c->gemms[seq[op].index].waves : 0;
+}
+'''
+
+
 @pytest.fixture(scope="module")
 def probe(tmp_path_factory):
     d = tmp_path_factory.mktemp("probe")
@@ -66,6 +77,19 @@ class Plan:
                 return
             if n > 0:
                 yield label.value.decode(), [tuple(out[9 * i:9 * i + 9]) for i in range(n)]
+            op += 1
+
+
+    def waves(self, held):
+        """{label: what probe_launch says of its launches}"""
+        self.lib.probe_launch.restype = C.c_int64
+        out, label, op = {}, C.c_char_p(), 0
+        while True:
+            w = self.lib.probe_launch(self.ctx, C.c_int(held), C.c_int64(op), C.byref(label))
+            if w < 0:
+                return out
+            if w > 0:
+                out.setdefault(label.value.decode(), set()).add(w)
             op += 1
 
 
@@ -131,3 +155,15 @@ def test_few_tiles_of_several_types_are_one_update(probe, side, launches):
     with Plan(probe, table, make_hparams(T=10)) as plan:
         rows = [r for label, r in plan.launches(1) if label == "update_lowrank_f64"]
     assert len(rows) == launches
+
+
+@pytest.mark.parametrize("k,m,n,r,update,project", [
+    (1, 256, 256, 8, 8, 8), (2, 512, 512, 32, 8, 8), (1, 1024, 1024, 64, 8, 8), (1, 8192, 2048, 8, 8, 4), (16, 128, 128, 8, 8, 8),
+    (5, 512, 512, 16, 4, 8), (10, 256, 256, 16, 4, 8), (4, 1024, 1024, 32, 4, 8), (2, 2048, 2048, 16, 4, 8), (16, 256, 256, 32, 4, 8), (36, 128, 128, 16, 4, 8),
+    (60, 128, 128, 16, 4, 4), (4, 1024, 1024, 64, 4, 4), (1, 2048, 2048, 128, 4, 4), (100, 64, 64, 8, 4, 8)])
+def test_waves_follow_from_how_a_launch_fills_the_chip(probe, k, m, n, r, update, project):
+    """Eight waves on small tiles only where a launch leaves compute units idle: every table here was measured both ways."""
+    with Plan(probe, [lowrank(m, n, r) for _ in range(k)], make_hparams(T=10)) as plan:
+        assert plan.waves(0)["alg2_update_f64"] == {update}
+        assert plan.waves(1)["project_f64"] == {project}
+        assert all(w <= {4, 8} for w in plan.waves(0).values())
