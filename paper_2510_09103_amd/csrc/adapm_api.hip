@@ -80,6 +80,7 @@ struct GemmList {
   GemmTile* d_tiles = nullptr;
   bool mfma = false;  // split-bf16 kernel (else fp64)
   int waves = 4;      // fp64 kernel: waves of a workgroup (waves64)
+  bool ahead = true;  // ... which request the operands of a step during the one before it (ahead64)
   int steps = 0;      // update of the exact path: most steps of 16 in the contractions of a block
   int cls = 0;        // ... and the class of its blocks (update64_class)
 };
@@ -316,6 +317,13 @@ struct Fill64 {
 // of the re-gauge, one per block, gain 1 - 4 % up to a thousand.
 constexpr double UPDATE64_FILL = 144, PROJECT64_FILL = 232;
 int waves64(bool few) { return few ? 8 : 4; }
+// Operands of a step are requested during the one before it, which takes registers that a fourth wave of the SIMD could have (152 against
+// 120).  Where the factor updates fill the chip several times and no contraction is long beside that, the fourth wave hides more; the
+// group's Gram matrices and the application of the re-gauge go the same way.  Literal steps, ahead and not: six blocks of 512 x 512 at r =
+// 128 265 and 250 us (260 before there was a request ahead), 16 at r = 64 240 and 224, 200 of 96 x 96 at r = 12 112 and 97, eight
+// layers of 512 / 1376 545 and 522; but one block of 2048 x 2048 at r = 128 336 and 350, four of 1024 x 1024 at r = 32 153 and 166.
+// G R^T with R held gains from the request whatever the fill (eight layers of 768 / 2048 203 and 205).
+bool ahead64(const Fill64& update) { return update.tiles() < 400 || 2 * update.tiles() < update.longest; }
 
 // Order of the tiles of a launch of the exact path: whole blocks to one XCD (workgroup i runs on XCD i mod 8), whose L2 then
 // fetches a factor or gradient once for all tiles that read it; largest blocks first, to the least loaded XCD.  The list
@@ -507,6 +515,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
     update.add(b.rank, b.cols, b.rows);
   }
   const int gram_waves = waves64(gram16 <= 256), upd_waves = waves64(update.tiles() < UPDATE64_FILL), regauge_waves = waves64(regauge16 <= 1024);
+  const bool ahead = ahead64(update);
   const bool gram_small = gram_tiles < 4 * 256 || gram_waves > 4, upd_small = upd_waves > 4, regauge_small = regauge_waves > 4;
   // this group's lists
   const int grp = c->n_groups++;
@@ -524,6 +533,7 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
   for (int e = 0; e < n_eff; ++e) {
     listA[e] = new_list(fast); listB[e] = new_list(fast);
     c->gemms[listA[e]].waves = gram_waves; c->gemms[listB[e]].waves = upd_waves;
+    c->gemms[listA[e]].ahead = c->gemms[listB[e]].ahead = ahead;
   }
   const int gnorm0 = (int)c->gnorm.size();          // this path's normaliser lists, one per iteration
   if (hp.refresh_normalise) c->gnorm.resize(gnorm0 + n_eff);
@@ -542,8 +552,9 @@ void plan_lowrank_refresh(adapm_ctx* c, bool fast, const std::vector<int64_t>& i
   const int l_pre = (n_eff == 0 && group_regauge) ? new_list(fast) : -1;
   Update64Lists l_epi;                                // m x n term of eq. 3-4 (the MFMA path never forms it)
   const int l_gram = group_regauge ? new_list(false) : -1;
-  if (l_gram >= 0) c->gemms[l_gram].waves = regauge_waves;
+  if (l_gram >= 0) { c->gemms[l_gram].waves = regauge_waves; c->gemms[l_gram].ahead = ahead; }
   const int l_fin = (!fast && (group_regauge || (n_eff > 0 && !c->lay[ids[0]].direct))) ? new_list(false) : -1;
+  if (l_fin >= 0) c->gemms[l_fin].ahead = ahead;
   for (int64_t i : ids) {
     const adapm_block_t& b = c->table[i];
     const Layout& L = c->lay[i];
@@ -1468,7 +1479,7 @@ adapm_status_t run_op(adapm_ctx* c, const Op& op, Bases& bs, const StepScalars& 
       break;
     case OP_GEMM: {
       const GemmList& g = c->gemms[op.index];
-      launch_gemm64(g.waves, g.d_probs, g.d_tiles, (int64_t)g.tiles.size(), bs, s);
+      launch_gemm64(g.waves, g.ahead, g.d_probs, g.d_tiles, (int64_t)g.tiles.size(), bs, s);
       break;
     }
     case OP_UPDATE64: {

@@ -294,7 +294,7 @@ struct RegaugeItem {
 };
 
 // launchers (defined next to their kernels)
-void launch_gemm64(int waves, const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, Bases b, hipStream_t s);
+void launch_gemm64(int waves, bool ahead, const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, Bases b, hipStream_t s);
 void launch_vstat(const BlockDev* blocks, const VsItem* items, int64_t nitems, double* partials, Bases b,
                   float beta2, hipStream_t s);
 void launch_vfinal(const BlockDev* blocks, const VfItem* items, int64_t nitems, const double* partials, Bases b,

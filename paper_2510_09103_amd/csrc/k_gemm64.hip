@@ -29,7 +29,7 @@ __device__ __forceinline__ double load_el(const char* base, int dtype, int64_t i
 
 // acc += alpha * A B over this wave's share of k in [kb, ke); `first`: the step that wave 0 would take if the steps of all
 // products were numbered through (a short product then falls to the waves that the one before it left out)
-template <int NW, int TM, int TN, int ADT, int BDT, int LAY>
+template <int NW, bool AHEAD, int TM, int TN, int ADT, int BDT, int LAY>
 __device__ __forceinline__ void product(const Mat& A, const Mat& B, double alpha, int M, int N, int kb, int ke, int i0, int j0,
                                         const Bases& bs, f64x4 (&acc)[TM][TN], int& first) {
   constexpr bool AK = LAY != G64_IJ, BK_ = LAY == G64_KK;
@@ -62,7 +62,20 @@ __device__ __forceinline__ void product(const Mat& A, const Mat& B, double alpha
   const int nfull = (ke - kb) / KS, mine = (wave - first) & (NW - 1);
   const bool edge = kb + nfull * KS < ke;
   const int k1 = kb + V * kq;
-  if (mine < nfull) {
+  if constexpr (!AHEAD) {
+    if (mine < nfull) {
+      for (int t = mine; t < nfull; t += NW) {
+        typename OA::Where pa = wa;
+        typename OB::Where pb = wb;
+        OA::step(pa, k1 + t * KS);
+        OB::step(pb, k1 + t * KS);
+        a[0].load(pa);
+        b[0].load(pb);
+        mma(a[0], b[0]);
+      }
+      mfma_f64_results(acc);
+    }
+  } else if (mine < nfull) {
     typename OA::Where pa = wa;
     typename OB::Where pb = wb;
     OA::step(pa, k1 + mine * KS);
@@ -100,11 +113,11 @@ __device__ __forceinline__ void product(const Mat& A, const Mat& B, double alpha
 }
 
 // the operand types that occur, per layout and tile (the planner makes no others)
-template <int NW, int TM, int TN, int LAY>
+template <int NW, bool AHEAD, int TM, int TN, int LAY>
 __device__ __forceinline__ void product_any(const Mat& A, const Mat& B, double alpha, int M, int N, int kb, int ke, int i0, int j0,
                                             const Bases& bs, f64x4 (&acc)[TM][TN], int& first) {
 #define ADAPM_CASE(ADT, BDT) \
-  if (A.dtype == ADT && B.dtype == BDT) return product<NW, TM, TN, ADT, BDT, LAY>(A, B, alpha, M, N, kb, ke, i0, j0, bs, acc, first)
+  if (A.dtype == ADT && B.dtype == BDT) return product<NW, AHEAD, TM, TN, ADT, BDT, LAY>(A, B, alpha, M, N, kb, ke, i0, j0, bs, acc, first)
   ADAPM_CASE(DT_F64, DT_F64);
   ADAPM_CASE(DT_F32, DT_F64);
   ADAPM_CASE(DT_F32, DT_F32);
@@ -120,7 +133,7 @@ __device__ __forceinline__ void product_any(const Mat& A, const Mat& B, double a
 #undef ADAPM_CASE
 }
 
-template <int NW, int TM, int TN, int LAY>
+template <int NW, bool AHEAD, int TM, int TN, int LAY>
 __device__ __forceinline__ void tile_body(const GemmProblem& P, const GemmTile& t, const Bases& bs, double* red) {
   const int i0 = 16 * TM * t.ti, j0 = 16 * TN * t.tj;
   const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
@@ -153,10 +166,10 @@ __device__ __forceinline__ void tile_body(const GemmProblem& P, const GemmTile& 
     // identically zero for this tile: rows i0 .. of A1 end at column i0 + 16 TM - 1, columns j0 .. of B1 start at row j0
     const int ke = P.tri == 1 ? (P.K1 < i0 + 16 * TM ? P.K1 : i0 + 16 * TM) : P.K1;
     const int kb = P.tri == 2 ? j0 : 0;
-    product_any<NW, TM, TN, LAY>(P.A1, P.B1, P.a1 * (P.scale_g ? (double)grad_scale(bs) : 1.0), P.M, P.N, kb, ke, i0, j0, bs, acc, first);
+    product_any<NW, AHEAD, TM, TN, LAY>(P.A1, P.B1, P.a1 * (P.scale_g ? (double)grad_scale(bs) : 1.0), P.M, P.N, kb, ke, i0, j0, bs, acc, first);
   }
-  if (P.K2 > 0) product_any<NW, TM, TN, LAY>(P.A2, P.B2, P.a2, P.M, P.N, 0, P.K2, i0, j0, bs, acc, first);
-  if (P.K3 > 0) product_any<NW, TM, TN, LAY>(P.A3, P.B3, P.a3, P.M, P.N, 0, P.K3, i0, j0, bs, acc, first);
+  if (P.K2 > 0) product_any<NW, AHEAD, TM, TN, LAY>(P.A2, P.B2, P.a2, P.M, P.N, 0, P.K2, i0, j0, bs, acc, first);
+  if (P.K3 > 0) product_any<NW, AHEAD, TM, TN, LAY>(P.A3, P.B3, P.a3, P.M, P.N, 0, P.K3, i0, j0, bs, acc, first);
   // the waves' partial tiles, added in wave order
 #pragma unroll
   for (int a = 0; a < TM; ++a)
@@ -196,7 +209,7 @@ __device__ __forceinline__ void tile_body(const GemmProblem& P, const GemmTile& 
   }
 }
 
-template <int NW>
+template <int NW, bool AHEAD>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 4) void gemm64_kernel(const GemmProblem* __restrict__ probs,
                                                                           const GemmTile* __restrict__ tiles, Bases bs) {
   __shared__ double red[NW * (NW == 4 ? 16 : 4) * 64];
@@ -204,32 +217,33 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 4) void gemm64_kernel(const 
   if (t.prob == GEMM_TILE_NONE) return;
   const GemmProblem& P = probs[t.prob];
   if constexpr (NW > 4) {
-    if (P.layout == G64_KK) tile_body<NW, 1, 1, G64_KK>(P, t, bs, red);
-    else tile_body<NW, 1, 1, G64_IJ>(P, t, bs, red);
+    if (P.layout == G64_KK) tile_body<NW, AHEAD, 1, 1, G64_KK>(P, t, bs, red);
+    else tile_body<NW, AHEAD, 1, 1, G64_IJ>(P, t, bs, red);
   } else {
     const int shape = 2 * P.tm + P.tn;     // 3: 16 x 16, 4: 16 x 32, 5: 32 x 16, 6: 32 x 32
     if (P.layout == G64_KK) {
-      if (shape == 6) tile_body<NW, 2, 2, G64_KK>(P, t, bs, red);
-      else if (shape == 5) tile_body<NW, 2, 1, G64_KK>(P, t, bs, red);
-      else tile_body<NW, 1, 1, G64_KK>(P, t, bs, red);
+      if (shape == 6) tile_body<NW, AHEAD, 2, 2, G64_KK>(P, t, bs, red);
+      else if (shape == 5) tile_body<NW, AHEAD, 2, 1, G64_KK>(P, t, bs, red);
+      else tile_body<NW, AHEAD, 1, 1, G64_KK>(P, t, bs, red);
     } else if (P.layout == G64_IJ) {
-      if (shape == 6) tile_body<NW, 2, 2, G64_IJ>(P, t, bs, red);
-      else if (shape == 4) tile_body<NW, 1, 2, G64_IJ>(P, t, bs, red);
-      else tile_body<NW, 1, 1, G64_IJ>(P, t, bs, red);
+      if (shape == 6) tile_body<NW, AHEAD, 2, 2, G64_IJ>(P, t, bs, red);
+      else if (shape == 4) tile_body<NW, AHEAD, 1, 2, G64_IJ>(P, t, bs, red);
+      else tile_body<NW, AHEAD, 1, 1, G64_IJ>(P, t, bs, red);
     } else {
-      if (shape == 6) tile_body<NW, 2, 2, G64_KJ>(P, t, bs, red);
-      else tile_body<NW, 2, 1, G64_KJ>(P, t, bs, red);
+      if (shape == 6) tile_body<NW, AHEAD, 2, 2, G64_KJ>(P, t, bs, red);
+      else tile_body<NW, AHEAD, 2, 1, G64_KJ>(P, t, bs, red);
     }
   }
 }
 
 }  // namespace
 
-void launch_gemm64(int waves, const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, Bases b, hipStream_t s) {
+void launch_gemm64(int waves, bool ahead, const GemmProblem* probs, const GemmTile* tiles, int64_t ntiles, Bases b, hipStream_t s) {
   if (ntiles <= 0) return;
   const dim3 grid((unsigned)ntiles);
-  if (waves == 8) hipLaunchKernelGGL(gemm64_kernel<8>, grid, dim3(512), 0, s, probs, tiles, b);
-  else hipLaunchKernelGGL(gemm64_kernel<4>, grid, dim3(256), 0, s, probs, tiles, b);
+  if (waves == 8) hipLaunchKernelGGL((gemm64_kernel<8, true>), grid, dim3(512), 0, s, probs, tiles, b);
+  else if (ahead) hipLaunchKernelGGL((gemm64_kernel<4, true>), grid, dim3(256), 0, s, probs, tiles, b);
+  else hipLaunchKernelGGL((gemm64_kernel<4, false>), grid, dim3(256), 0, s, probs, tiles, b);
 }
 
 }  // namespace adapm

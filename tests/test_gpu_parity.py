@@ -241,6 +241,17 @@ def test_exact_path_for_every_number_of_waves_on_a_tile(copies, hp):
 
 
 @pytest.mark.parametrize("hp", [dict(T=1), dict(T=2)])
+@pytest.mark.parametrize("gd", ["f32", "bf16"])
+def test_exact_path_without_requests_ahead(gd, hp):
+    """Launches that fill the chip several times load the operands of a step where they use them: contractions of less than a step, of
+    whole steps and beside them, shares of one to seven steps per wave."""
+    sizes = [(16, 48, 8), (17, 33, 15), (64, 15, 15), (97, 63, 33), (130, 112, 64), (48, 130, 17)]
+    wl = WL.Workload("filled", tuple(BlockSpec(f"b{k}_{m}x{n}_r{r}", m, n, "f32", gd, "lowrank", r, "element", 1, 1.0, 0.1)
+                                     for k in range(24) for m, n, r in sizes), steps=2, seed=59, signal_rank=24)
+    run(wl, 2, hp, tol_state=TOL32, tol_param=TOL32)
+
+
+@pytest.mark.parametrize("hp", [dict(T=1), dict(T=2)])
 def test_every_type_of_block_in_one_update_of_the_exact_path(hp):
     """Both types of G and W, both kinds of second moment and blocks of fewer columns than a lane updates, in one launch of few tiles:
     sizes at and beside the edges of a tile, ranks whose factors fit the launch's LDS, fill it and pass it."""

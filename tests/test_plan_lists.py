@@ -31,13 +31,13 @@ extern "C" int64_t probe_tiles(const adapm_ctx* c, int held, int64_t op, const c
 '''
 
 
-# Waves of a workgroup of launch `op`, 0 for launches of another kind, -1 past the last one
+# Waves of a workgroup of launch `op` (plus 100 where they request operands a step ahead), 0 for launches of another kind, -1 past the last one
 PROBE += r'''
 extern "C" int64_t probe_launch(const adapm_ctx* c, int held, int64_t op, const char** label) {
   const std::vector<Op>& seq = held ? c->seq_project : c->seq_refresh;
   if (op >= (int64_t)seq.size()) return -1;
   *label = seq[op].label;
-  return seq[op].kind == OP_GEMM ? c->gemms[seq[op].index].waves : 0;
+  return seq[op].kind == OP_GEMM ? c->gemms[seq[op].index].waves + 100 * c->gemms[seq[op].index].ahead : 0;
 }
 '''
 
@@ -164,6 +164,15 @@ def test_few_tiles_of_several_types_are_one_update(probe, side, launches):
 def test_waves_follow_from_how_a_launch_fills_the_chip(probe, k, m, n, r, update, project):
     """Eight waves on small tiles only where a launch leaves compute units idle: every table here was measured both ways."""
     with Plan(probe, [lowrank(m, n, r) for _ in range(k)], make_hparams(T=10)) as plan:
-        assert plan.waves(0)["alg2_update_f64"] == {update}
-        assert plan.waves(1)["project_f64"] == {project}
-        assert all(w <= {4, 8} for w in plan.waves(0).values())
+        assert {w % 100 for w in plan.waves(0)["alg2_update_f64"]} == {update}
+        assert {w % 100 for w in plan.waves(1)["project_f64"]} == {project}
+        assert all(w % 100 in (4, 8) for ws in plan.waves(0).values() for w in ws)
+
+
+@pytest.mark.parametrize("k,m,n,r,ahead", [(1, 2048, 2048, 128, True), (4, 1024, 1024, 32, True), (1, 4096, 4096, 8, True), (1, 256, 256, 8, True),
+                                           (100, 64, 64, 8, False), (6, 512, 512, 128, False), (16, 512, 512, 64, False), (200, 96, 96, 12, False)])
+def test_operands_are_requested_ahead_where_a_launch_does_not_fill_the_chip(probe, k, m, n, r, ahead):
+    """... and not where it does, where the registers serve a fourth wave better; with R held always."""
+    with Plan(probe, [lowrank(m, n, r) for _ in range(k)], make_hparams(T=10)) as plan:
+        assert {w > 100 for w in plan.waves(0)["alg2_update_f64"]} == {ahead}
+        assert {w > 100 for w in plan.waves(1)["project_f64"]} == {True}
