@@ -80,17 +80,20 @@ class Plan:
             op += 1
 
 
-    def waves(self, held):
-        """{label: what probe_launch says of its launches}"""
+    def labels(self, held):
+        """(label, what probe_launch says of it) of every launch of a step"""
         self.lib.probe_launch.restype = C.c_int64
-        out, label, op = {}, C.c_char_p(), 0
-        while True:
-            w = self.lib.probe_launch(self.ctx, C.c_int(held), C.c_int64(op), C.byref(label))
-            if w < 0:
-                return out
-            if w > 0:
-                out.setdefault(label.value.decode(), set()).add(w)
+        label, op = C.c_char_p(), 0
+        while (w := self.lib.probe_launch(self.ctx, C.c_int(held), C.c_int64(op), C.byref(label))) >= 0:
+            yield label.value.decode(), w
             op += 1
+
+    def waves(self, held):
+        out = {}
+        for label, w in self.labels(held):
+            if w > 0:
+                out.setdefault(label, set()).add(w)
+        return out
 
 
 DT = {"f32": B.ADAPM_F32, "bf16": B.ADAPM_BF16}
@@ -176,3 +179,25 @@ def test_operands_are_requested_ahead_where_a_launch_does_not_fill_the_chip(prob
     with Plan(probe, [lowrank(m, n, r) for _ in range(k)], make_hparams(T=10)) as plan:
         assert {w > 100 for w in plan.waves(0)["alg2_update_f64"]} == {ahead}
         assert {w > 100 for w in plan.waves(1)["project_f64"]} == {True}
+
+
+@pytest.mark.parametrize("m,n,r", [(1024, 1024, 64), (512, 2048, 128), (700, 300, 17), (4096, 64, 8), (2048, 2048, 128)])
+def test_copies_of_the_factors_do_not_split_a_group(probe, m, n, r):
+    """From two GD iterations on the exact path keeps the previous factors in its scratch (K = 5; not with one, K = 2).  Tables of a
+    small state, whose scratch has a fixed bound, run in as many groups either way, inside the array of adapm_step_static where
+    they did."""
+    def plan_of(k, K):
+        with Plan(probe, [lowrank(m, n, r, v=B.ADAPM_V_ROWGROUP) for _ in range(k)], make_hparams(T=1, K=K)) as plan:
+            probe.adapm_workspace_bytes.restype = probe.adapm_state_bytes.restype = C.c_size_t
+            runs = sum(label == "alg2_update_f64" for label, _ in plan.labels(0))
+            return runs // (4 if K == 5 else 1), probe.adapm_workspace_bytes(plan.ctx), probe.adapm_state_bytes(plan.ctx)
+    seen = set()
+    for k in range(1, 400):
+        one, ws_one, state = plan_of(k, 2)
+        if state > 32 << 20:
+            break
+        many, ws_many, _ = plan_of(k, 5)
+        assert many <= one, k
+        assert ws_one > B.adapm_static_scratch_bytes() or ws_many <= B.adapm_static_scratch_bytes(), k
+        seen.add(one)
+    assert len(seen) > 1
