@@ -462,6 +462,12 @@ int32_t last_read(const adapm_ctx* c, const adapm_block_t& b) {
   return b.cols % 64 == 0 && c->gw_bytes > ((int64_t)256 << 20);
 }
 
+// ... and that of the element-wise and grouped updates, whose rows lie in no two tiles: where a step touches more than the last-level cache
+// keeps.  Full momentum, one v per element, 18 M elements (216 MiB with the state) 62 us and 77 non-temporal, 24 M (288) 95 and
+// 100, 32 M (384) 145 and 135, 48 M 218 and 214; no momentum, one v per row, 64 M (256 MiB) 64 and 67, 80 M (320) 84 and 83, 128 M 156 and
+// 125.  Gradients in fp32 are read as they are.
+int32_t element_last_read(const adapm_ctx* c) { return c->gw_bytes + (int64_t)c->state_bytes > ((int64_t)304 << 20); }
+
 // Alg. 2 + eq. 3-4 for the low-rank blocks of one contraction path.
 //   fast = false: batched GEMMs on the fp64 matrix cores, every intermediate kept in fp64;
 //   fast = true : split-bf16 matrix instructions, fp32 intermediates: stripe products, or batched GEMMs for the blocks
@@ -1204,6 +1210,7 @@ void build_plan(adapm_ctx* c) {
     d.param_dtype = b.param_dtype; d.grad_dtype = b.grad_dtype;
     d.mom_mode = b.mom_mode; d.v_mode = b.v_mode;
     d.lr_scale = b.lr_scale; d.wd = b.weight_decay;
+    d.g_last = element_last_read(c); d.pad = 0;
     c->blocks.h.push_back(d);
     if (is_grouped(i)) {
       // Groups per workgroup: a wave takes its groups one after another, each a memory latency, so few groups are spread over all

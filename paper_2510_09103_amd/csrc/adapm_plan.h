@@ -114,6 +114,7 @@ struct BlockDev {
   int64_t off_v;         // state byte offset of v
   int32_t param_dtype, grad_dtype, mom_mode, v_mode;
   float lr_scale, wd;
+  int32_t g_last, pad;   // 1: the update's read of a bf16 gradient is non-temporal
 };
 
 struct EwItem {          // one workgroup: `count` elements from `start` of `block`

@@ -22,7 +22,7 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// 16 bytes of a gradient whose last reader this is: non-temporal, they leave the caches first (grouped update of 163 M elements 435 -> 424 us)
+// 16 bytes of a bf16 gradient whose last reader this is: non-temporal, they leave the caches first (for which tables: g_last in adapm_api.hip)
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 load16_last(const char* p) {
   const u32x4_t q = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
@@ -167,6 +167,7 @@ __global__ __launch_bounds__(256) void update_grouped_kernel(const BlockDev* __r
   const UpdCoef cf = make_coef(sc.lr, blk.lr_scale, blk.wd, sc.clip);
   const float ob1 = 1.f - sc.beta1;
   const float gs = grad_scale(b);                 // global clipping: the method sees gs * G
+  const bool last = blk.g_last;
   const int ge = (int)blk.group_elems, nvec = ge >> 3;
   for (int64_t g = item.g0 + wave; g < item.g0 + item.ngroups; g += 4) {
     const int64_t base = g * ge;
@@ -174,11 +175,20 @@ __global__ __launch_bounds__(256) void update_grouped_kernel(const BlockDev* __r
     // converted afterwards (W and m do not depend on v): one memory latency per group.  bf16 G and W only.
     uint4 gq[4], wq[4];
     float4 ma[4], mb[4];
+    auto at = [&](int k) {
+      const int iv = lane + 64 * k;
+      return base + (int64_t)(iv < nvec ? iv : nvec - 1) * 8;
+    };
+    if (last) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) gq[k] = load16_last(G + at(k) * 2);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) gq[k] = *reinterpret_cast<const uint4*>(G + at(k) * 2);
+    }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int iv = lane + 64 * k;
-      const int64_t e0 = base + (int64_t)(iv < nvec ? iv : nvec - 1) * 8;
-      gq[k] = load16_last(G + e0 * 2);
+      const int64_t e0 = at(k);
       wq[k] = *reinterpret_cast<const uint4*>(W + e0 * 2);
       if (m) {
         ma[k] = *reinterpret_cast<const float4*>(m + e0);
@@ -267,6 +277,7 @@ __global__ __launch_bounds__(256) void update_kernel(const BlockDev* __restrict_
   const UpdCoef cf = make_coef(sc.lr, blk.lr_scale, blk.wd, sc.clip);
   const float ob1 = 1.f - sc.beta1, ob2 = 1.f - sc.beta2;
   const float gs = grad_scale(b);                 // global clipping: the method sees gs * G
+  const bool last = blk.g_last;
   const int nvec = (item.count + 7) >> 3;
   const int64_t end = item.start + item.count;
   // group index of this thread's first vector; later vectors advance by 2048 elements
@@ -281,7 +292,8 @@ __global__ __launch_bounds__(256) void update_kernel(const BlockDev* __restrict_
     const int64_t e = item.start + (int64_t)iv * 8;
     if (e + 8 <= end) {
       float g[8], w[8], inv[8], mc[8];
-      load8<true>(G, blk.grad_dtype, e, g);
+      if (last) load8<true>(G, blk.grad_dtype, e, g);
+      else load8(G, blk.grad_dtype, e, g);
       if (gs != 1.f) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) g[k] *= gs;

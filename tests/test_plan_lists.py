@@ -33,6 +33,8 @@ extern "C" int64_t probe_tiles(const adapm_ctx* c, int held, int64_t op, const c
 
 # Waves of a workgroup of launch `op` (plus 100 where they request operands a step ahead), 0 for launches of another kind, -1 past the last one
 PROBE += r'''
+// is block i's gradient read non-temporally by the update of blocks without low-rank momentum?
+extern "C" int64_t probe_last_read(const adapm_ctx* c, int64_t i) { return c->blocks.h[i].g_last; }
 extern "C" int64_t probe_launch(const adapm_ctx* c, int held, int64_t op, const char** label) {
   const std::vector<Op>& seq = held ? c->seq_project : c->seq_refresh;
   if (op >= (int64_t)seq.size()) return -1;
@@ -201,3 +203,16 @@ def test_copies_of_the_factors_do_not_split_a_group(probe, m, n, r):
         assert ws_one > B.adapm_static_scratch_bytes() or ws_many <= B.adapm_static_scratch_bytes(), k
         seen.add(one)
     assert len(seen) > 1
+
+
+@pytest.mark.parametrize("mom,v,side,last", [
+    (B.ADAPM_MOM_FULL, B.ADAPM_V_ELEMENT, 18, 0), (B.ADAPM_MOM_FULL, B.ADAPM_V_ELEMENT, 32, 1), (B.ADAPM_MOM_NONE, B.ADAPM_V_ROWGROUP, 64, 0),
+    (B.ADAPM_MOM_NONE, B.ADAPM_V_ROWGROUP, 128, 1), (B.ADAPM_MOM_FULL, B.ADAPM_V_ROWGROUP, 32, 0), (B.ADAPM_MOM_FULL, B.ADAPM_V_ROWGROUP, 48, 1)])
+def test_gradients_of_tables_that_stay_in_the_caches_are_not_sent_out_of_them(probe, mom, v, side, last):
+    """Blocks of 2^20 elements without low-rank momentum: the non-temporal read of G costs up to a fifth of a step whose gradients, parameters
+    and state fit the last-level cache (256 MiB) and pays where they do not."""
+    table = [B.adapm_block_t(rows=1024, cols=1024, param_dtype=B.ADAPM_BF16, grad_dtype=B.ADAPM_BF16, mom_mode=mom, rank=0, v_mode=v, v_group_rows=1,
+                             lr_scale=1.0, weight_decay=0.1) for _ in range(side)]
+    with Plan(probe, table, make_hparams()) as plan:
+        probe.probe_last_read.restype = C.c_int64
+        assert {probe.probe_last_read(plan.ctx, C.c_int64(i)) for i in range(side)} == {last}
