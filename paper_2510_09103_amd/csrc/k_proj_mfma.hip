@@ -1421,6 +1421,9 @@ __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, co
     src.rG = make_rsrc_uniform(A + (int64_t)row0 * K, rows_valid * (unsigned)K * 2u);
     src.n = K; src.nv = K & ~7;
   }
+  // looked up here: behind the products, where it is used, every workgroup would wait for the look-up's loads one after another
+  // (six layers of 128 / 341 at r = 64 24.3 -> 23.8 us a launch, a literal step 193.8 -> 192.0)
+  float* const Out = reinterpret_cast<float*>(global_ptr((P.out.space == SP_STATE ? bs.state : bs.ws) + P.out.off));
   const int r = P.r;                  // rows of Q actually present (the image is zero-padded to R)
   float gs = uniform(grad_scale(bs));   // global gradient clipping: A is the gradient (or its transpose)
   const float gs2 = gs * gs;
@@ -1505,7 +1508,6 @@ __device__ __forceinline__ void stripe_body(unsigned char* smem, float* rsum, co
     }
   }
   float* Ps = reinterpret_cast<float*>(smem);
-  float* Out = reinterpret_cast<float*>(resolve(P.out, bs));
   // with the GD step, the new factor values (zeros outside the factor) go back into P for the image below
   const bool emit_f = P.upd && P.off_next >= 0, emit_t = P.upd && P.off_timg >= 0, emit = emit_f || emit_t;
   if (!TRA) {
