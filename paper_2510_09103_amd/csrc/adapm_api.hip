@@ -1213,10 +1213,13 @@ void build_plan(adapm_ctx* c) {
     d.g_last = element_last_read(c); d.pad = 0;
     c->blocks.h.push_back(d);
     if (is_grouped(i)) {
-      // Groups per workgroup: a wave takes its groups one after another, each a memory latency, so few groups are spread over all
-      // the workgroups that the chip holds (2048) before a workgroup gets 32768 elements
-      // (2316 rows of 192 53 -> 8 us, the norms and heads of six layers of 168 / 672 51 -> 5; 50257 rows of 1600 keep 20 a workgroup).
-      const int64_t per = std::max<int64_t>(4, std::min<int64_t>(32768 / d.group_elems, (ngrouped + 8191) / 8192 * 4));
+      // Groups per workgroup: a wave takes its groups one after another, each a memory latency, so few groups are spread over the chip
+      // before a workgroup gets 32768 elements (2316 rows of 192 53 -> 8 us, the norms and heads of six layers of 168 / 672 51 -> 5; 50257
+      // rows of 1600 keep 20 a workgroup): four to a workgroup, one per wave, while all of them run at once (4096 groups, 1024
+      // workgroups), eight up to 8192 groups and then as many as leave between 1024 and 2048 workgroups.  (8192 rows of 1024 with full
+      // momentum: four 21.6 us, eight 19.0, 32 18.7; 12000 rows of 512: four 9.8, eight 9.0, 64 17.2.)
+      const int64_t share = ngrouped <= 4096 ? 4 : std::max<int64_t>(8, (ngrouped + 8191) / 8192 * 4);
+      const int64_t per = std::max<int64_t>(4, std::min<int64_t>(32768 / d.group_elems, share));
       for (int64_t g0 = 0; g0 < L.nv; g0 += per)
         c->grp.h.push_back(GrpItem{g0, (int32_t)i, (int32_t)std::min<int64_t>(per, L.nv - g0)});
       continue;

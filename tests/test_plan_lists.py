@@ -33,6 +33,8 @@ extern "C" int64_t probe_tiles(const adapm_ctx* c, int held, int64_t op, const c
 
 # Waves of a workgroup of launch `op` (plus 100 where they request operands a step ahead), 0 for launches of another kind, -1 past the last one
 PROBE += r'''
+// groups of the workgroup `i` of the grouped update, -1 past the last one
+extern "C" int64_t probe_groups(const adapm_ctx* c, int64_t i) { return i < (int64_t)c->grp.h.size() ? c->grp.h[i].ngroups : -1; }
 // is block i's gradient read non-temporally by the update of blocks without low-rank momentum?
 extern "C" int64_t probe_last_read(const adapm_ctx* c, int64_t i) { return c->blocks.h[i].g_last; }
 extern "C" int64_t probe_launch(const adapm_ctx* c, int held, int64_t op, const char** label) {
@@ -216,3 +218,20 @@ def test_gradients_of_tables_that_stay_in_the_caches_are_not_sent_out_of_them(pr
     with Plan(probe, table, make_hparams()) as plan:
         probe.probe_last_read.restype = C.c_int64
         assert {probe.probe_last_read(plan.ctx, C.c_int64(i)) for i in range(side)} == {last}
+
+
+@pytest.mark.parametrize("rows,cols,share", [(1, 64, 1), (3000, 192, 4), (4096, 1024, 4), (4097, 1024, 8), (8192, 1024, 8), (8193, 64, 8), (16384, 512, 8),
+                                             (16385, 512, 12), (50257, 1600, 20), (40000, 2048, 16)])
+def test_groups_are_spread_over_the_chip(probe, rows, cols, share):
+    """One group per wave while all run at once, two of them up to 8192 groups, then between 1024 and 2048 workgroups until one has
+    32768 elements."""
+    table = [B.adapm_block_t(rows=rows, cols=cols, param_dtype=B.ADAPM_BF16, grad_dtype=B.ADAPM_BF16, mom_mode=B.ADAPM_MOM_FULL, rank=0,
+                             v_mode=B.ADAPM_V_ROWGROUP, v_group_rows=1, lr_scale=1.0, weight_decay=0.1)]
+    with Plan(probe, table, make_hparams()) as plan:
+        probe.probe_groups.restype = C.c_int64
+        got, i = [], 0
+        while (n := probe.probe_groups(plan.ctx, C.c_int64(i))) >= 0:
+            got.append(n)
+            i += 1
+    assert sum(got) == rows and set(got[:-1]) <= {share} and got[-1] <= share and max(got) == share
+    assert len(got) >= min(512, rows // 4)
