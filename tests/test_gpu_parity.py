@@ -240,6 +240,18 @@ def test_exact_path_for_every_number_of_waves_on_a_tile(copies, hp):
     run(wl, 3, hp, tol_state=TOL32, tol_param=TOL32)
 
 
+@pytest.mark.parametrize("v", ["element", "rowgroup"])
+@pytest.mark.parametrize("hp", [dict(T=1), dict(T=2)])
+def test_exact_path_at_ranks_whose_factors_pass_the_lds_of_the_update(hp, v):
+    """The update stages 128 values of k of a factor at a time: one less and one more, and second and third shares of whole steps with
+    and without an edge, in the kernel of one type and in the one of several."""
+    sizes = [(140, 150, 127), (140, 150, 129), (150, 210, 144), (210, 263, 200), (300, 280, 272)]
+    for types in (["f32"], ["f32", "bf16"]):
+        wl = WL.Workload("wide", tuple(BlockSpec(f"b{k}_{m}x{n}_r{r}", m, n, "f32", types[k % len(types)], "lowrank", r, v, 1, 1.0, 0.1)
+                                       for k, (m, n, r) in enumerate(sizes)), steps=2, seed=61, signal_rank=24)
+        run(wl, 2, hp, tol_state=TOL32, tol_param=TOL32)
+
+
 @pytest.mark.parametrize("hp", [dict(T=1), dict(T=2)])
 @pytest.mark.parametrize("gd", ["f32", "bf16"])
 def test_exact_path_without_requests_ahead(gd, hp):
