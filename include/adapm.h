@@ -54,7 +54,7 @@ typedef enum { ADAPM_MOM_NONE = 0, ADAPM_MOM_FULL = 1, ADAPM_MOM_LOWRANK = 2 } a
 typedef enum { ADAPM_V_ELEMENT = 0, ADAPM_V_ROWGROUP = 1, ADAPM_V_WHOLE = 2 } adapm_vmode_t;
 
 /* Arithmetic of the low-rank contractions (G R^T, L^T G, Gram matrices, L R):
- *  F64     - operands exact, fp64 accumulation on the vector ALUs;
+ *  F64     - operands exact, fp64 accumulation on the fp64 matrix cores;
  *  BF16X2  - bf16 MFMA with fp32 accumulation, every fp32 factor operand carried
  *            as a (hi, lo) pair of bf16 values (relative operand error 2^-17);
  *            requires bf16 gradients.  Implemented for rank <= 128 (a block runs in

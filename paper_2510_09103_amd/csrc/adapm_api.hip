@@ -388,7 +388,8 @@ void add_update64(GemmList& gl, GemmProblem p, int32_t block) {
   add_problem(gl, p);
 }
 // ... and how many tiles along a row one workgroup walks: a longer walk costs the look-up of its problem and the staging of its
-// factor rows once, as long as the launch still holds three rounds of the four workgroups per compute unit.
+// factor rows once, as long as the launch still holds twelve workgroups per compute unit, four rounds of the three that run at once
+// (two where the factor rows take 64 KB of LDS).
 int update64_walk(size_t tiles) { return (int)std::min<size_t>(8, std::max<size_t>(1, tiles / (3 * 4 * 256))); }
 void walk_update64(GemmList& gl) {
   const int nj = update64_walk(gl.tiles.size());
@@ -456,7 +457,7 @@ bool stores_direct(const adapm_hparams_t& hp) {
 
 // Is the fused updates' read of G non-temporal?  Where the table streams through the last-level cache (256 MiB) and the rows are
 // whole cache lines: 48 layers of 1600 / 6400 at r = 128, R held, 3.05 -> 3.00 ms, 24 layers of 1024 / 4096 at r = 64 0.986 ->
-// 0.974.  Rows that are not have lines in two tiles, and the second one fetches them again (1672 / 6688 at r = 84 2.82 -> 2.90 ms);
+// 0.974, no more than the runs of one side differ by: there it does no harm.  Rows that are not have lines in two tiles, and the second one fetches them again (1672 / 6688 at r = 84 2.82 -> 2.90 ms);
 // a table that stays in the caches is sent out of them (ten layers of 192 / 512 32.3 -> 33.5 us, six of 128 / 341 18.2 -> 19.9).
 int32_t last_read(const adapm_ctx* c, const adapm_block_t& b) {
   return b.cols % 64 == 0 && c->gw_bytes > ((int64_t)256 << 20);

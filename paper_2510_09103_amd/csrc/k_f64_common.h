@@ -10,7 +10,8 @@
 // which free index sits in which lane as long as the store knows: a lane therefore takes V consecutive values of a
 // contiguous contraction index (one wide load feeds V instructions: instruction v covers k0 + V (l / 16) + v), and T
 // consecutive values of a contiguous free index (one load feeds T output tiles: tile t of lane l is index T (l % 16) + t).
-// Every operand element is used once per wave, so nothing is staged in LDS.
+// Every operand element is used once per wave, so nothing is staged in LDS; k_update64.hip, whose waves multiply the same rows of A
+// with chunk after chunk of B, keeps those in LDS.
 #pragma once
 #include "adapm_plan.h"
 #include "ew_math.h"
@@ -34,8 +35,8 @@ __device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
 // source waits itself: 20 states, held in place by the two rows of ties.  What may still come before it are copies from
 // register to register; tests/test_fp64_listings.py checks the distance of those in the listings of every build.
 //
-// The kernels ask for two workgroups of four waves per CU, that is at most 256 registers, because the compiler then lets the
-// instruction work on ordinary registers.  With more it keeps the accumulators in the second half of the file and copies
+// The kernels ask for two or more waves per SIMD (two, three or four: 256, 168 or 128 registers at most), because the compiler
+// lets the instruction work on ordinary registers up to 256.  With more it keeps the accumulators in the second half of the file and copies
 // them there and back in every step of a loop, and every copy is such a read.
 template <int N>
 __device__ __forceinline__ void mfma_f64_tie(f64x4 (&acc)[N]) {
