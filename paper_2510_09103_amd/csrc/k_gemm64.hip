@@ -15,8 +15,8 @@
 //   11.6 -> 8.5 us, factor updates 16.8 -> 11.7, G R^T with R held 12.3 -> 7.7.  (16 waves were no better in any of 60 tables and 3 - 4 us a literal
 //   step slower in most.)  What is left of such a launch is the look-up of its problem and a cold instruction cache.
 // Measured against 64 x 64 tiles on the vector units with operands staged in LDS (one workgroup walking the whole
-// contraction): G R^T, L^T G and the Gram matrices of one GD iteration with the factor updates, the 56 blocks: 454 -> 122 us
-// (of which 98 us, 36 TFLOP/s, for the updates; the matrix cores are busy half of that); the 7 small ones 157 -> 21 us.
+// contraction): G R^T, L^T G and the Gram matrices of one GD iteration with the factor updates, the 56 blocks: 454 -> 110 us
+// (of which 86 us, 41 TFLOP/s, for the updates; the matrix cores are busy half of that; 24 us for the Gram matrices); the 7 small ones 157 -> 21 us.
 #include "k_f64_common.h"
 
 namespace adapm {
