@@ -330,7 +330,9 @@ def main():
         "n_gpus": 1, "steps": K, "warmup": W, "ms_per_step": ms_per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f32",
-        "precision_note": "fp32 arithmetic and state; bf16 parameters and gradients; contractions on bf16 MFMA with every "
+        "precision_note": "fp32 arithmetic, state and parameters; contractions in fp64 on exact operands"
+                          if all(b.param_dtype == "f32" for b in wl.blocks if b.rank) else
+                          "fp32 arithmetic and state; bf16 parameters and gradients; contractions on bf16 MFMA with every "
                           "fp32 operand as a (hi, lo) bf16 pair, fp32 accumulation",
         "data": "synthetic",
         "config": {"workload": args.workload, "blocks": len(wl.blocks), "params": wl.numel, "refresh_period_T": args.T,
